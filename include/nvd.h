@@ -250,7 +250,11 @@ nvd_status nvd_project(nvd_graph* g, int32_t k, const double* P,
  *   delta_j (mean zero on every component).  With NVD_WARM_START it also
  *   supplies the starting guess.
  * info: host array of k nvd_pair_info or NULL.
- * Synchronous with respect to `stream` (see Streams).  On a connected graph
+ * Synchronous with respect to `stream` (see Streams).  With the Jacobi
+ * preconditioner, no warm start and tile_k = 0, graphs whose vector fits one
+ * CU's LDS (up to 32,768 nodes in mixed precision, 17,408 in FP64) are solved
+ * by one block per pair where that is estimated faster (environment:
+ * NVD_COLUMN=0 never, NVD_COLUMN=1 wherever it fits).  Else on a connected graph
  * with the Jacobi preconditioner and no warm start, a tile of up to about
  * 1e6 vector elements (n times the tile) is solved by one kernel launch
  * (one block, or a cooperative launch of up to 256 blocks); NVD_E_DEVICE if

@@ -349,12 +349,16 @@ nvd_status nvd_distances(nvd_graph* h, int32_t k, const double* P, const double*
   sp.achol = (o.flags & NVD_PRECOND_ACHOL) != 0;
   sp.tree = sp.achol || use_tree(g, o.flags);
   sp.out_dsq = (o.flags & NVD_OUT_DSQ) != 0;
-  int tile = o.tile_k;
-  if (tile == 0) tile = choose_tile(g, k, o.precision, s);
   std::vector<nvd_pair_info> hinfo(k);
   nvd_status agg = NVD_OK;
   nvd_status st = NVD_OK;
-  for (int c0 = 0; c0 < k && st == NVD_OK;) {
+  // small graphs: every pair by a block of its own (a tile asked for by the
+  // caller keeps the paths that solve tiles)
+  const bool column = o.tile_k == 0 && use_column(g, k, sp);
+  if (column) st = solve_column(g, k, P, Q, ld, sp, d_out, X, ldx, hinfo.data(), s);
+  int tile = o.tile_k;
+  if (tile == 0 && !column) tile = choose_tile(g, k, o.precision, s);
+  for (int c0 = column ? k : 0; c0 < k && st == NVD_OK;) {
     int T = tile;
     while (T > k - c0) T >>= 1;
     sp.nl = tuned_nl(g, o.precision, T);
@@ -455,8 +459,10 @@ nvd_status nvd_graph_set_weights(nvd_graph* h, const double* w, void* stream) {
   if (g->achol) g->bytes -= g->achol->bytes;
   free_achol(g->achol);
   g->achol = nullptr;
-  // the slices of the one-column apply hold copies of the weights
+  // the slices of the one-column apply hold copies of the weights, as does
+  // the one-block-per-column solver's layout (refreshed on its next use)
   free_slices(g);
+  column_weights_changed(g);
   g->h_w.resize(std::max(g->nnz, 1));
   if (hipMemcpy(g->h_w.data(), g->w64, sizeof(double) * g->nnz, hipMemcpyDeviceToHost) != hipSuccess) {
     set_error("nvd_graph_set_weights: copying the weights back failed");

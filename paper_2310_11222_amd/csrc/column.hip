@@ -1,0 +1,725 @@
+// One block per column: the whole solve of one pair on a graph of up to a few
+// ten thousand nodes in one block of 1024 threads, whose CG direction lives
+// in that CU's LDS.
+//
+// On such graphs an iteration of the multi-kernel path, or of the
+// cooperative launch with its grid barriers, is bound by launches and by
+// coherent round trips between XCDs (24-34 us at n = 10^4), not by its few
+// hundred kilobytes.  A column that stays in one CU needs neither: its
+// gathers are LDS reads, its sums are register moves between lanes and one
+// block barrier, and the other columns run on other CUs at the same time.
+// What it gives up is the sharing of the graph between columns; the
+// neighbour lists are 16-bit positions, read from L2 by every block.
+//
+// Measured per call, host included (before: cooperative launch, or the
+// multi-kernel path on several components): BA n = 10^3, one pair, FP64, 337
+// -> 106 us (1.8 us an iteration on a lattice of that size, 2.7 with hubs;
+// ~32 us around them); ER n = 10^4, average degree 4, 214 components, 8 pairs
+// mixed, 2025 -> 403 us; WS n = 10^4 of degree 16, weighted, 5 pairs FP64,
+// 2868 -> 1091 us.  At n = 10^4 an FP64 iteration of 19 us is bound by the LDS
+// (a random 64-lane gather of 8 bytes takes ~8.4 cycles of the CU, 160K
+// entries ~9 us) and by the vector work of ten elements a thread (~6 us).
+//
+// The arithmetic is that of the other paths (same recurrences, stopping and
+// refinement rules, same edge-difference form of L x); sums have a fixed
+// order, so results repeat bit for bit.
+#include <algorithm>
+#include <cstdlib>
+#include <cstring>
+#include <numeric>
+#include <vector>
+
+#include "column_dev.hpp"
+
+namespace nvd {
+
+// LDS for the gathered vector and the heavy rows' sums (a CU has 160 KB;
+// the block's partial sums are static).
+constexpr int kColLds = 152 * 1024;
+// Rows with more neighbours than this (and more than twice the mean) are
+// heavy, and cut into parts of at least kColPart neighbours, so many that at
+// most kColMaxParts are needed.
+constexpr int kColHeavyDeg = 16;
+constexpr int kColPart = 16;
+constexpr int kColMaxParts = 2048;
+// Rows of more neighbours than this count as hubs in the choice of solver.
+constexpr int kColHubDeg = 64;
+constexpr int kColMaxEPT = 32;   // FP64: 17, what LDS holds
+// Columns of one launch (one CU each).
+constexpr int kColChunk = 256;
+// Status of a pair between the mixed launch and the FP64 one (never returned).
+constexpr int kColResume = -1;
+
+template <bool MIXED, bool UNIT, int EPT>
+__global__ __launch_bounds__(kColBS) void k_column(ColArgs a) {
+  extern __shared__ double lds[];
+  __shared__ ColShared S;
+  int t = thread_here();
+  int turn = 0;
+  ColGraph g;
+  ColJob job;
+  if (a.jobs) {
+    job = a.jobs[blockIdx.x];
+    g = a.graphs[job.graph];
+  } else {
+    g = a.g;
+    job.out = blockIdx.x;
+    job.voff = a.col0 + blockIdx.x;
+    job.ld = a.ld;
+    job.xoff = job.voff;
+    job.ldx = a.ldx;
+  }
+  make_scalar(g);
+  const int n = g.n;
+  double* const hq = lds;                       // [nv], ahead of the vector
+  double* const buf = lds + ((g.nv + 1) & ~1);
+  double* const b = a.vec + (size_t)blockIdx.x * 4 * a.stride;
+  double* const x = b + a.stride;
+  double* const r = x + a.stride;
+  double* const cm = a.cmean + (size_t)blockIdx.x * a.cstride;
+
+  int status = kStOk, iters = 0, refine = 0, fb = 0;
+  if (!MIXED && a.resume) {
+    if (a.info[job.out].status != kColResume) return;
+    iters = a.info[job.out].iters;
+    refine = a.info[job.out].refine_steps;
+    fb = 1;
+  }
+  double init[2] = {0.0, 0.0};
+  double rv[MIXED ? 1 : EPT];
+  if (!MIXED && a.resume) {
+    // b and x are those of the mixed launch; r is the residual of x
+    col_resid<UNIT>(g, x, b, r, buf, a.lds_n, hq);
+    t = thread_here();
+#pragma unroll
+    for (int j = 0; j < EPT; ++j) {
+      const int e = t + j * kColBS;
+      if constexpr (!MIXED) rv[j] = 0.0;
+      if (e < n) {
+        const double v = r[e];
+        init[0] += b[e] * b[e];
+        init[1] += v * v * g.inv64[e];
+        if constexpr (!MIXED) rv[j] = v;
+      }
+      four_at_a_time<EPT>(j);
+    }
+    col_sum<2>(init, S, turn);
+  } else {
+    // (a2) delta_bar = (P - Q) minus its mean on every component
+    for (int e = t; e < g.slots * kColBS; e += kColBS) {
+      double v = 0.0;
+      if (e < n) {
+        const long at = job.voff + (long)g.perm[e] * job.ld;
+        v = a.P[at] - (a.Q ? a.Q[at] : 0.0);
+      }
+      b[e] = v;
+      x[e] = 0.0;
+      r[e] = 0.0;
+    }
+    __syncthreads();
+    const double mean0 = col_means(g, b, cm, S, turn);
+#pragma unroll
+    for (int j = 0; j < EPT; ++j) {
+      const int e = t + j * kColBS;
+      if constexpr (!MIXED) rv[j] = 0.0;
+      if (e < n) {
+        const double v = b[e] - col_mean(g, cm, mean0, e);
+        b[e] = v;
+        r[e] = v;
+        init[0] += v * v;
+        init[1] += v * v * g.inv64[e];
+        if constexpr (!MIXED) rv[j] = v;
+      }
+      four_at_a_time<EPT>(j);
+    }
+    col_sum<2>(init, S, turn);
+  }
+  const double bb = init[0];
+  double rho = init[1];
+  int open = bb > 0.0;
+  bool fp64_done = false;
+
+  if constexpr (MIXED) {
+    float* const x32 = reinterpret_cast<float*>(r + a.stride);
+    float* const p32 = reinterpret_cast<float*>(buf);
+    int stall = 0;
+    double orr = bb;
+    for (int step = 0; uniform(open != 0) && step <= a.max_refine; ++step) {
+      double m = 0.0;
+      if (step > 0) {
+        // (a7) FP64 outer residual, projected
+        col_resid<UNIT>(g, x, b, r, buf, a.lds_n, hq);
+        m = col_means(g, r, cm, S, turn);
+      }
+      float f[EPT];
+      t = thread_here();
+      double s3[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+      for (int j = 0; j < EPT; ++j) {
+        const int e = t + j * kColBS;
+        f[j] = 0.0f;
+        if (j < g.slots) x32[e] = 0.0f;
+        if (e < n) {
+          const double v = r[e] - (step > 0 ? col_mean(g, cm, m, e) : 0.0);
+          f[j] = (float)v;
+          const float z = f[j] * g.inv32[e];
+          s3[0] += v * v;
+          s3[1] += (double)f[j] * (double)z;
+          s3[2] += (double)f[j] * (double)f[j];
+        }
+        four_at_a_time<EPT>(j);
+      }
+      col_sum<3>(s3, S, turn);
+      const double rr = s3[0];
+      if (step > 0 && a.handover) stall = refine_stall_count(orr, rr, stall, a.stall_ratio2);
+      orr = rr;
+      if (uniform(step > 0 && rr <= a.rtol2 * bb)) {
+        open = 0;
+        break;
+      }
+      if (uniform(refine_hand_to_fp64(stall))) {
+        open = 0;
+        fb = 1;
+        break;
+      }
+      if (refine >= a.max_refine) {
+        open = 0;
+        status = kStNoconv;
+        break;
+      }
+      if (!uniform(s3[2] > 0.0)) {
+        open = 0;               // the residual rounds to zero in FP32
+        break;
+      }
+      refine += 1;
+      const double need2 = rr > 0.0 ? 0.09 * a.rtol2 * bb / rr : 0.0;
+      const double it2 = need2 > a.irtol2 ? (need2 < 0.25 ? need2 : 0.25) : a.irtol2;
+      const ColRun run = col_cg<float, UNIT, EPT>(g, p32, hq, f, x32, s3[1], s3[2], it2, a.max_iter, S, turn);
+      iters += run.iters;
+      if (run.status == kStOk) {
+        for (int e = t; e < n; e += kColBS) x[e] += (double)x32[e];
+      } else {
+        open = 0;
+        if (run.status == kStNoconv && a.handover)
+          fb = 1;               // FP64 finishes from the last good x
+        else
+          status = run.status;
+      }
+    }
+    if (fb) {
+      // left to the FP64 launch, which takes b and x from vec
+      if (t == 0) {
+        nvd_pair_info pi{};
+        pi.status = kColResume;
+        pi.iters = iters;
+        pi.refine_steps = refine;
+        a.info[job.out] = pi;
+      }
+      return;
+    }
+    // the last residual is that of the final x, whose shift to mean zero
+    // leaves L x as it is
+    __syncthreads();
+    const double mx = col_means(g, x, cm, S, turn);
+    for (int e = t; e < n; e += kColBS) x[e] -= col_mean(g, cm, mx, e);
+  } else {
+    fp64_done = true;
+    for (int restarts = 0; open; ++restarts) {
+      if (uniform(rho > 0.0)) {
+        const ColRun run =
+            col_cg<double, UNIT, EPT>(g, buf, hq, rv, x, rho, bb, a.rtol2, a.max_iter, S, turn);
+        iters += run.iters;
+        status = run.status;
+      }
+      const double mx = col_means(g, x, cm, S, turn);
+      for (int e = t; e < n; e += kColBS) x[e] -= col_mean(g, cm, mx, e);
+      col_resid<UNIT>(g, x, b, r, buf, a.lds_n, hq);
+      double s2[2] = {0.0, 0.0};
+      t = thread_here();
+#pragma unroll
+      for (int j = 0; j < EPT; ++j) {
+        const int e = t + j * kColBS;
+        if (e < n) {
+          rv[j] = r[e];
+          s2[0] += rv[j] * rv[j];
+          s2[1] += rv[j] * rv[j] * g.inv64[e];
+        }
+        four_at_a_time<EPT>(j);
+      }
+      col_sum<2>(s2, S, turn);
+      rho = s2[1];
+      open = status == kStOk && uniform(s2[0] > a.rtol2 * bb);
+      if (restarts >= 2) break;
+    }
+  }
+
+  // (a8) quadratic form, distance, per-pair info; x out
+  double dots[3] = {0.0, 0.0, 0.0};
+  for (int e = t; e < n; e += kColBS) {
+    const double xe = x[e], re = r[e];
+    dots[0] += b[e] * xe;
+    dots[1] += xe * re;
+    dots[2] += re * re;
+    if (a.X) a.X[job.xoff + (long)g.perm[e] * job.ldx] = xe;
+  }
+  col_sum<3>(dots, S, turn);
+  if (t == 0) {
+    const double dsq = bb > 0.0 ? dots[0] + dots[1] : 0.0;
+    if (fp64_done && status == kStOk && open) status = kStNoconv;
+    const double d0 = dsq > 0.0 ? dsq : 0.0;
+    a.d_out[a.col0 + job.out] = a.out_dsq ? d0 : sqrt(d0);
+    nvd_pair_info pi;
+    pi.status = status;
+    pi.iters = iters;
+    pi.refine_steps = refine;
+    pi.flags = fb ? NVD_INFO_FP64_FALLBACK : 0;
+    pi.rel_res = bb > 0.0 ? sqrt(dots[2] / bb) : 0.0;
+    pi.dsq_plain = bb > 0.0 ? dots[0] : 0.0;
+    pi.dsq = dsq;
+    a.info[job.out] = pi;
+  }
+}
+
+// Weights and 1 / degree in the block's order, from the graph's.
+__global__ void k_column_weights(int entries, const int* src, int n, int npad, const int* perm,
+                                 const double* w64, const double* invd64, const float* invd32, double* sw64,
+                                 float* sw32, double* inv64, float* inv32) {
+  const int step = gridDim.x * blockDim.x;
+  const int i0 = blockIdx.x * blockDim.x + threadIdx.x;
+  if (w64) {
+    for (int i = i0; i < entries; i += step) {
+      const double w = src[i] >= 0 ? w64[src[i]] : 0.0;
+      sw64[i] = w;
+      sw32[i] = (float)w;
+    }
+  }
+  for (int i = i0; i < npad; i += step) {
+    inv64[i] = i < n ? invd64[perm[i]] : 0.0;
+    inv32[i] = i < n ? invd32[perm[i]] : 0.0f;
+  }
+}
+
+// x of one column, by node (for the multi-kernel solver).
+__global__ void k_column_nodes(int n, const int* perm, const double* x, double* out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) out[perm[i]] = x[i];
+}
+__global__ void k_column_put(int n, const double* x, double* X, long ldx) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) X[(long)i * ldx] = x[i];
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+struct ColPlan {
+  ColGraph d{};
+  unsigned char* blob = nullptr;   // what the host laid out
+  double* weights = nullptr;       // what k_column_weights fills
+  const int* src = nullptr;
+  int entries = 0;
+  bool weighted = false;           // the copies are those of explicit weights
+  bool stale = true;               // the graph's weights changed since
+  int64_t bytes = 0;
+};
+
+// Scratch and result words of a call, kept with the graph (or the batch).
+nvd_status ensure_column_ws(ColWs* w, long stride, long cstride, int cols, int64_t* bytes) {
+  const size_t vec = (size_t)stride * 4 * cols, cm = (size_t)cstride * cols;
+  if (w->cap_vec < vec || w->cap_cm < cm) {
+    (void)hipFree(w->vec);
+    w->vec = nullptr;
+    if (bytes) *bytes -= (int64_t)(sizeof(double) * (w->cap_vec + w->cap_cm));
+    w->cap_vec = w->cap_cm = 0;
+    const size_t v = std::max(vec, w->cap_vec), c = std::max(cm, w->cap_cm);
+    NVD_HIP(hipMalloc((void**)&w->vec, sizeof(double) * (v + c)));
+    w->cap_vec = v;
+    w->cap_cm = c;
+    if (bytes) *bytes += (int64_t)(sizeof(double) * (v + c));
+  }
+  if (w->cap_info < cols) {
+    if (w->info) (void)hipHostFree(w->info);
+    w->info = nullptr;
+    w->cap_info = 0;
+    const int c = std::max(cols, 64);
+    NVD_HIP(hipHostMalloc((void**)&w->info, sizeof(nvd_pair_info) * c, hipHostMallocDefault));
+    w->cap_info = c;
+  }
+  return NVD_OK;
+}
+
+void free_column_ws(ColWs* w) {
+  if (w->vec) (void)hipFree(w->vec);
+  if (w->info) (void)hipHostFree(w->info);
+  *w = ColWs{};
+}
+
+void free_column(DevGraph* g) {
+  if (g->col) {
+    (void)hipFree(g->col->blob);
+    (void)hipFree(g->col->weights);
+    g->bytes -= g->col->bytes;
+    delete g->col;
+    g->col = nullptr;
+  }
+  if (g->col_ws.cap_vec) g->bytes -= (int64_t)(sizeof(double) * (g->col_ws.cap_vec + g->col_ws.cap_cm));
+  free_column_ws(&g->col_ws);
+}
+
+void column_weights_changed(DevGraph* g) {
+  if (g->col) g->col->stale = true;
+}
+
+namespace {
+
+// Parts of one host buffer that becomes one device allocation.
+struct Blob {
+  std::vector<unsigned char> h;
+  size_t put(const void* p, size_t bytes) {
+    const size_t at = (h.size() + 255) & ~(size_t)255;
+    h.resize(at + std::max<size_t>(bytes, 1));
+    if (bytes) std::memcpy(h.data() + at, p, bytes);
+    return at;
+  }
+};
+
+}  // namespace
+
+static nvd_status build_column(DevGraph* g) {
+  const int n = g->n;
+  const int* rp = g->h_rp.data();
+  const int* ci = g->h_ci.data();
+  // positions: nodes by falling degree, ties by node (counting sort)
+  std::vector<int> first(g->max_deg + 2, 0), perm(n), pos(n);
+  for (int i = 0; i < n; ++i) ++first[g->max_deg - (rp[i + 1] - rp[i]) + 1];
+  std::partial_sum(first.begin(), first.end(), first.begin());
+  for (int i = 0; i < n; ++i) {
+    const int at = first[g->max_deg - (rp[i + 1] - rp[i])]++;
+    perm[at] = i;
+    pos[i] = at;
+  }
+  auto deg = [&](int e) { return rp[perm[e] + 1] - rp[perm[e]]; };
+  const double heavy_at = std::max((double)kColHeavyDeg, 2.0 * g->nnz / n);
+  int nh = 0;
+  long hnnz = 0;
+  while (nh < n && nh < kColBS && deg(nh) > heavy_at) hnnz += deg(nh++);
+  int part = kColPart;
+  while (hnnz / part + nh > kColMaxParts) part *= 2;
+  std::vector<int> voff(nh + 1, 0);
+  for (int e = 0; e < nh; ++e) voff[e + 1] = voff[e] + (deg(e) + part - 1) / part;
+  const int nv = voff[nh];
+  const int slots = (n + kColBS - 1) / kColBS;
+  const int vslots = (nv + kColBS - 1) / kColBS;
+  std::vector<int> vown(std::max(1, vslots * kColBS), 0);
+  for (int e = 0; e < nh; ++e)
+    for (int v = voff[e]; v < voff[e + 1]; ++v) vown[v] = e;
+  // the neighbours of a lane's row: first entry, count, own position
+  struct Row { int lo, count, own; };
+  auto row_of = [&](int j, int w, int l) -> Row {
+    if (j < slots) {
+      const int e = j * kColBS + w * 64 + l;
+      if (e < nh || e >= n) return {0, 0, e};
+      return {rp[perm[e]], deg(e), e};
+    }
+    const int v = (j - slots) * kColBS + w * 64 + l;
+    if (v >= nv) return {0, 0, 0};
+    const int e = vown[v];
+    const int lo = rp[perm[e]] + (v - voff[e]) * part;
+    return {lo, std::min(part, rp[perm[e] + 1] - lo), e};
+  };
+  const int all = slots + vslots;
+  std::vector<int> soff(kColWaves * all + 1, 0);
+  for (int w = 0; w < kColWaves; ++w)
+    for (int j = 0; j < all; ++j) {
+      int most = 0;
+      for (int l = 0; l < 64; ++l) most = std::max(most, row_of(j, w, l).count);
+      soff[w * all + j + 1] = soff[w * all + j] + (most + 1) / 2;
+    }
+  const size_t entries = (size_t)(soff[kColWaves * all] + kColSpare) * 128;
+  std::vector<unsigned short> idx(entries, 0);
+  std::vector<int> src(entries, -1);
+  for (int w = 0; w < kColWaves; ++w)
+    for (int j = 0; j < all; ++j) {
+      const int at0 = soff[w * all + j], pairs = soff[w * all + j + 1] - at0;
+      for (int l = 0; l < 64; ++l) {
+        const Row r = row_of(j, w, l);
+        for (int i = 0; i < 2 * pairs; ++i) {
+          const size_t at = ((size_t)(at0 + i / 2) * 64 + l) * 2 + (i & 1);
+          idx[at] = (unsigned short)(i < r.count ? pos[ci[r.lo + i]] : r.own);
+          src[at] = i < r.count ? r.lo + i : -1;
+        }
+      }
+    }
+  // components, largest first
+  const int nc = g->n_comp;
+  std::vector<int> coff, cnode, ccomp;
+  int nc_block = 0, nc_wave = 0;
+  if (nc > 1) {
+    std::vector<int> size(nc, 0), order(nc), rank(nc);
+    for (int i = 0; i < n; ++i) ++size[g->h_comp[i]];
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return size[x] > size[y]; });
+    coff.assign(nc + 1, 0);
+    for (int c = 0; c < nc; ++c) {
+      rank[order[c]] = c;
+      coff[c + 1] = coff[c] + size[order[c]];
+      if (size[order[c]] > 512) nc_block = c + 1;
+      if (size[order[c]] > 16) nc_wave = c + 1;
+    }
+    cnode.resize(n);
+    ccomp.resize(n);
+    std::vector<int> at(coff.begin(), coff.end() - 1);
+    for (int e = 0; e < n; ++e) {
+      const int c = rank[g->h_comp[perm[e]]];
+      ccomp[e] = c;
+      cnode[at[c]++] = e;
+    }
+  }
+  Blob bl;
+  const size_t o_perm = bl.put(perm.data(), sizeof(int) * n);
+  const size_t o_soff = bl.put(soff.data(), sizeof(int) * soff.size());
+  const size_t o_idx = bl.put(idx.data(), sizeof(unsigned short) * entries);
+  const size_t o_src = bl.put(src.data(), sizeof(int) * src.size());
+  const size_t o_voff = bl.put(voff.data(), sizeof(int) * (nh + 1));
+  const size_t o_vown = bl.put(vown.data(), sizeof(int) * vown.size());
+  const size_t o_coff = bl.put(coff.data(), sizeof(int) * coff.size());
+  const size_t o_cnode = bl.put(cnode.data(), sizeof(int) * cnode.size());
+  const size_t o_ccomp = bl.put(ccomp.data(), sizeof(int) * ccomp.size());
+  ColPlan* cp = new ColPlan();
+  hipError_t e = hipMalloc((void**)&cp->blob, bl.h.size());
+  if (e == hipSuccess) e = hipMemcpy(cp->blob, bl.h.data(), bl.h.size(), hipMemcpyHostToDevice);
+  if (e != hipSuccess) {
+    (void)hipFree(cp->blob);
+    delete cp;
+    set_error(std::string("column plan: ") + hipGetErrorString(e));
+    return e == hipErrorOutOfMemory ? NVD_E_NOMEM : NVD_E_DEVICE;
+  }
+  cp->bytes = (int64_t)bl.h.size();
+  auto ip = [&](size_t o) { return reinterpret_cast<const int*>(cp->blob + o); };
+  cp->src = ip(o_src);
+  cp->entries = (int)entries;
+  cp->d.n = n;
+  cp->d.nh = nh;
+  cp->d.nc = nc;
+  cp->d.slots = slots;
+  cp->d.vslots = vslots;
+  cp->d.nv = nv;
+  cp->d.nc_block = nc_block;
+  cp->d.nc_wave = std::max(nc_wave, nc_block);
+  cp->d.perm = ip(o_perm);
+  cp->d.soff = ip(o_soff);
+  cp->d.idx = reinterpret_cast<const unsigned*>(cp->blob + o_idx);
+  cp->d.voff = ip(o_voff);
+  cp->d.vown = ip(o_vown);
+  cp->d.coff = ip(o_coff);
+  cp->d.cnode = ip(o_cnode);
+  cp->d.ccomp = ip(o_ccomp);
+  g->col = cp;
+  g->bytes += cp->bytes;
+  return NVD_OK;
+}
+
+// The plan with the graph's present weights.
+static nvd_status ensure_column(DevGraph* g, hipStream_t s) {
+  if (!g->col) NVD_TRY(build_column(g));
+  ColPlan* cp = g->col;
+  if (!cp->stale) return NVD_OK;
+  const int n = g->n;
+  if (!cp->weights || cp->weighted != g->weighted) {
+    (void)hipFree(cp->weights);
+    cp->weights = nullptr;
+    const size_t sw = g->weighted ? (size_t)cp->entries : 0, n2 = (size_t)cp->d.slots * kColBS;
+    NVD_HIP(hipMalloc((void**)&cp->weights, 12 * (sw + n2)));
+    cp->weighted = g->weighted;
+    cp->bytes += (int64_t)(12 * (sw + n2));
+    g->bytes += (int64_t)(12 * (sw + n2));
+    double* d = cp->weights;
+    float* f = reinterpret_cast<float*>(d + sw + n2);
+    cp->d.w64 = g->weighted ? reinterpret_cast<const double2*>(d) : nullptr;
+    cp->d.inv64 = d + sw;
+    cp->d.w32 = g->weighted ? reinterpret_cast<const float2*>(f) : nullptr;
+    cp->d.inv32 = f + sw;
+  }
+  const int npad = cp->d.slots * kColBS;
+  const int work = std::max(cp->entries, npad);
+  k_column_weights<<<std::min(1024, (work + 255) / 256), 256, 0, s>>>(
+      cp->entries, cp->src, n, npad, cp->d.perm, g->weighted ? g->w64 : nullptr, g->invd64, g->invd32,
+      (double*)cp->d.w64, (float*)cp->d.w32, (double*)cp->d.inv64, (float*)cp->d.inv32);
+  NVD_HIP(hipGetLastError());
+  cp->stale = false;
+  return NVD_OK;
+}
+
+static size_t parts_bytes(int nv) { return sizeof(double) * (size_t)((nv + 1) & ~1); }
+
+// Whether a column of n nodes fits one block: its elements in registers, its
+// gathered vector (FP64, or FP32 in mixed precision) in LDS beside the most
+// parts of heavy rows there can be.
+static bool column_fits(int n, bool mixed) {
+  const size_t npad = (size_t)(n + kColBS - 1) / kColBS * kColBS;
+  return npad <= (size_t)kColBS * kColMaxEPT && npad * (mixed ? 4 : 8) + parts_bytes(kColMaxParts) <= (size_t)kColLds;
+}
+
+// Which solver takes k pairs of a graph that fits: the one with the smaller
+// estimated time of a CG iteration (us), both fitted to measured times of
+// 45 graphs (BA, WS, ER, power law; n = 10^4 .. 3.2 10^4, average degree 4 to
+// 63, k = 1, 8, 64, both precisions).
+//   A block's iteration grows with its slots (vector work) and with the
+//   graph's entries (LDS gathers), not with k: its columns run side by side.
+//   The tiled paths pay a latency for every tile of the ragged k, more with
+//   long rows and hubs, then work that grows with n and k.
+// E.g. (us per pair set, block / tiled, mixed): ER n = 10^4 d = 4 k = 8
+// 379 / 1761; WS n = 10^4 d = 32 k = 1 829 / 1377; WS n = 3.2 10^4 d = 6 k = 8
+// 3312 / 2688, k = 64 3506 / 5994; BA n = 2.4 10^4 m = 8 k = 1 820 / 705.
+static bool column_is_faster(const DevGraph* g, int k) {
+  const double nnz = g->nnz, n = g->n;
+  const bool hubs = g->max_deg > kColHubDeg;
+  const double slots = (g->n + kColBS - 1) / kColBS;
+  const double block = 2.0 + 0.6 * slots + nnz * ((g->weighted ? 1.0e-4 : 6.0e-5) + (hubs ? 2.0e-5 : 0.0));
+  const double pass = g->n_comp > 1 ? 25.0 + 1.0e-3 * n : 13.0 + 0.5 * nnz / n + (hubs ? 10.0 : 0.0);
+  double tiles = 0.0;
+  for (int left = k; left > 0;) {
+    int T = 64;
+    while (T > left) T >>= 1;
+    tiles += pass + (T >= 16 ? 3.0e-6 : 2.0e-6) * nnz * T;
+    left -= T;
+  }
+  return block * ((k + kColChunk - 1) / kColChunk) <= tiles;
+}
+
+bool use_column(const DevGraph* g, int k, const SolveParams& sp) {
+  if (sp.tree || sp.achol || sp.warm) return false;
+  if (!column_fits(g->n, sp.precision == NVD_MIXED)) return false;
+  // the switches of the other single-launch path ask for it, or for none
+  const char* e = std::getenv("NVD_SMALL");
+  if (e && e[0] == '0') return false;
+  if (std::getenv("NVD_MID_BLOCKS")) return false;
+  if (const char* c = std::getenv("NVD_COLUMN")) return c[0] != '0';   // 0 never, 1 wherever it fits
+  return column_is_faster(g, k);
+}
+
+template <bool MIXED, bool UNIT, int EPT>
+static nvd_status launch_column_k(const ColArgs& a, int blocks, size_t bytes, hipStream_t s) {
+  const void* f = reinterpret_cast<const void*>(&k_column<MIXED, UNIT, EPT>);
+  NVD_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kColLds));
+  k_column<MIXED, UNIT, EPT><<<blocks, kColBS, bytes, s>>>(a);
+  NVD_HIP(hipGetLastError());
+  return NVD_OK;
+}
+
+template <bool MIXED, bool UNIT>
+static nvd_status launch_column_n(const ColArgs& a, int n, int blocks, size_t bytes, hipStream_t s) {
+  const int ept = (n + kColBS - 1) / kColBS;
+  if (ept <= 1) return launch_column_k<MIXED, UNIT, 1>(a, blocks, bytes, s);
+  if (ept <= 2) return launch_column_k<MIXED, UNIT, 2>(a, blocks, bytes, s);
+  if (ept <= 4) return launch_column_k<MIXED, UNIT, 4>(a, blocks, bytes, s);
+  if (ept <= 8) return launch_column_k<MIXED, UNIT, 8>(a, blocks, bytes, s);
+  if constexpr (MIXED) {
+    if (ept <= 10) return launch_column_k<MIXED, UNIT, 10>(a, blocks, bytes, s);
+    if (ept <= 14) return launch_column_k<MIXED, UNIT, 14>(a, blocks, bytes, s);
+    if (ept <= 18) return launch_column_k<MIXED, UNIT, 18>(a, blocks, bytes, s);
+    if (ept <= 24) return launch_column_k<MIXED, UNIT, 24>(a, blocks, bytes, s);
+    return launch_column_k<MIXED, UNIT, 32>(a, blocks, bytes, s);
+  } else {
+    // (arrays of 9 to 16 doubles are kept as one register tuple each and
+    // spill as a whole: 8 us an iteration at n = 10^4 with 10)
+    return launch_column_k<MIXED, UNIT, 17>(a, blocks, bytes, s);
+  }
+}
+
+// A pair that FP32 cannot finish on a graph whose FP64 vector does not fit:
+// the multi-kernel FP64 solver, from the pair's x.
+static nvd_status finish_multi_kernel(DevGraph* g, int col, int block, const double* P, const double* Q,
+                                      int64_t ld, const SolveParams& sp, const ColArgs& a,
+                                      nvd_pair_info* info, hipStream_t s) {
+  const int n = g->n;
+  const double* x = a.vec + ((size_t)block * 4 + 1) * a.stride;
+  double* X = const_cast<double*>(x) + a.stride;   // r's place
+  k_column_nodes<<<(n + 255) / 256, 256, 0, s>>>(n, g->col->d.perm, x, X);
+  NVD_HIP(hipGetLastError());
+  SolveParams f = sp;
+  f.precision = NVD_FP64;
+  f.warm = true;
+  NVD_TRY(ensure_workspace(g, 1, false));
+  NVD_TRY(solve_tile(g, 1, P + col, Q + col, ld, f, a.d_out + col, X, 1, g->ws->info, s));
+  if (a.X) k_column_put<<<(n + 255) / 256, 256, 0, s>>>(n, X, a.X + col, a.ldx);
+  NVD_HIP(hipGetLastError());
+  nvd_pair_info got;
+  NVD_HIP(hipMemcpyAsync(&got, g->ws->info, sizeof(got), hipMemcpyDeviceToHost, s));
+  NVD_HIP(hipStreamSynchronize(s));
+  got.iters += info->iters;
+  got.refine_steps = info->refine_steps;
+  got.flags |= NVD_INFO_FP64_FALLBACK;
+  *info = got;
+  return NVD_OK;
+}
+
+// The k pairs (P[:, j], Q[:, j]) of one graph.
+nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, int64_t ld,
+                        const SolveParams& sp, double* d_out, double* X, int64_t ldx,
+                        nvd_pair_info* info, hipStream_t s) {
+  const bool mixed = sp.precision == NVD_MIXED;
+  NVD_TRY(ensure_column(g, s));
+  const ColPlan* cp = g->col;
+  const long stride = (long)cp->d.slots * kColBS;
+  const long cstride = g->n_comp > 1 ? g->n_comp : 0;
+  const int chunk = std::min(k, kColChunk);
+  NVD_TRY(ensure_column_ws(&g->col_ws, stride, cstride, chunk, &g->bytes));
+  ColArgs a{};
+  a.g = cp->d;
+  a.P = P;
+  a.Q = Q;
+  a.ld = ld;
+  a.rtol2 = sp.rtol * sp.rtol;
+  a.irtol2 = sp.inner_rtol * sp.inner_rtol;
+  a.stall_ratio2 = kStallRatio2;
+  if (const char* e = std::getenv("NVD_REFINE_STALL_RATIO2")) {
+    const double v = std::strtod(e, nullptr);
+    if (v >= 0.0 && v <= 1.0) a.stall_ratio2 = v;
+  }
+  a.max_iter = sp.max_iter;
+  a.max_refine = sp.max_refine;
+  a.out_dsq = sp.out_dsq ? 1 : 0;
+  const size_t hb = parts_bytes(cp->d.nv);
+  const size_t most = ((size_t)kColLds - hb) / (sizeof(double) * kColBS) * kColBS;
+  a.lds_n = (int)std::min<size_t>(stride, most);
+  const size_t bytes = hb + sizeof(double) * (size_t)a.lds_n;
+  a.d_out = d_out;
+  a.X = X;
+  a.ldx = ldx;
+  a.info = g->col_ws.info;
+  a.vec = g->col_ws.vec;
+  a.stride = stride;
+  a.cmean = g->col_ws.vec + g->col_ws.cap_vec;
+  a.cstride = cstride;
+  a.handover = mixed ? 1 : 0;
+  auto launch = [&](bool in_fp64, size_t lds, int cols) -> nvd_status {
+    if (!in_fp64)
+      return g->weighted ? launch_column_n<true, false>(a, g->n, cols, lds, s)
+                         : launch_column_n<true, true>(a, g->n, cols, lds, s);
+    return g->weighted ? launch_column_n<false, false>(a, g->n, cols, lds, s)
+                       : launch_column_n<false, true>(a, g->n, cols, lds, s);
+  };
+  for (int c0 = 0; c0 < k; c0 += chunk) {
+    const int cols = std::min(chunk, k - c0);
+    a.col0 = c0;
+    a.resume = 0;
+    NVD_TRY(launch(!mixed, bytes, cols));
+    NVD_HIP(hipStreamSynchronize(s));
+    const nvd_pair_info* got = g->col_ws.info;
+    auto left = [&](int j) { return got[j].status == kColResume; };
+    bool any = false;
+    for (int j = 0; j < cols; ++j) any = any || left(j);
+    if (any && column_fits(g->n, false)) {
+      a.resume = 1;
+      NVD_TRY(launch(true, hb + sizeof(double) * (size_t)stride, cols));
+      NVD_HIP(hipStreamSynchronize(s));
+    }
+    std::copy(got, got + cols, info + c0);
+    for (int j = 0; any && j < cols; ++j)
+      if (left(j)) NVD_TRY(finish_multi_kernel(g, c0 + j, j, P, Q, ld, sp, a, &info[c0 + j], s));
+  }
+  return NVD_OK;
+}
+
+}  // namespace nvd

@@ -528,6 +528,7 @@ nvd_status graph_destroy(DevGraph* g) {
   free_tree(g->tree);
   free_achol(g->achol);
   free_slices(g);
+  free_column(g);
   if (g->heavy) (void)hipFree(g->heavy);
   free_graph_arrays(g);
   delete g;

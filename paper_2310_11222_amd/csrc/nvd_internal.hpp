@@ -73,6 +73,15 @@ struct AcholPre {
 };
 
 struct SliceGraph;   // column slices of the one-column apply (slice.hip)
+struct ColPlan;      // the graph as the one-block-per-column solver walks it (column.hip)
+
+// Scratch vectors and host result words of the one-block-per-column solver.
+struct ColWs {
+  double* vec = nullptr;           // [columns][5][n], then the component means
+  size_t cap_vec = 0, cap_cm = 0;  // doubles
+  nvd_pair_info* info = nullptr;   // pinned
+  int cap_info = 0;
+};
 
 struct DevGraph {
   int n = 0;
@@ -115,6 +124,8 @@ struct DevGraph {
   SliceGraph* slices = nullptr; // built when the sliced apply is first needed
   int slice_state = 0;          // -1: build failed, use the row-wise apply
   int slice_pick[2] = {0, 0};   // [FP64, FP32]: 1 sliced, -1 row-wise (timed), 0 not yet
+  ColPlan* col = nullptr;       // built when the one-block-per-column solver is first used
+  ColWs col_ws;
 };
 
 struct Workspace {
@@ -213,6 +224,15 @@ int small_blocks(DevGraph* g, int T, const SolveParams& sp);
 nvd_status solve_small(DevGraph* g, int T, int nb, const double* P, const double* Q, int64_t ld,
                        const SolveParams& sp, double* d_out, double* X, int64_t ldx,
                        nvd_pair_info* info_dev, hipStream_t s);
+// One block per column on graphs whose vector fits one CU's LDS (column.hip):
+// all k pairs in one launch, info on the host on return.
+bool use_column(const DevGraph* g, int k, const SolveParams& sp);
+nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, int64_t ld,
+                        const SolveParams& sp, double* d_out, double* X, int64_t ldx,
+                        nvd_pair_info* info, hipStream_t s);
+void column_weights_changed(DevGraph* g);
+void free_column(DevGraph* g);
+void free_column_ws(ColWs* w);
 // Tile for k pairs without timing anything: the autotuner's cached choice,
 // else the fixed heuristic.
 int untimed_tile(const DevGraph* g, int k, int precision);

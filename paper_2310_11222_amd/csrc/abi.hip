@@ -360,7 +360,12 @@ nvd_status nvd_distances(nvd_graph* h, int32_t k, const double* P, const double*
   if (tile == 0 && !column) tile = choose_tile(g, k, o.precision, s);
   for (int c0 = column ? k : 0; c0 < k && st == NVD_OK;) {
     int T = tile;
-    while (T > k - c0) T >>= 1;
+    if (o.tile_k == 0)
+      T = next_tile(g, k, k - c0, tile, sp);
+    else
+      while (T > k - c0) T >>= 1;
+    const int cols = std::min(T, k - c0);
+    sp.cols = cols;
     sp.nl = tuned_nl(g, o.precision, T);
     st = ensure_workspace(g, T, o.precision == NVD_MIXED);
     const int nb = st == NVD_OK ? small_blocks(g, T, sp) : 0;
@@ -378,7 +383,7 @@ nvd_status nvd_distances(nvd_graph* h, int32_t k, const double* P, const double*
       st = solve_tile(g, T, P + c0, Q + c0, ld, sp, d_out + c0, X ? X + c0 : nullptr, ldx,
                       g->ws->info, s);
     if (st == NVD_OK) {
-      hipError_t e = hipMemcpyAsync(hinfo.data() + c0, g->ws->info, sizeof(nvd_pair_info) * T,
+      hipError_t e = hipMemcpyAsync(hinfo.data() + c0, g->ws->info, sizeof(nvd_pair_info) * cols,
                                     hipMemcpyDeviceToHost, s);
       if (e == hipSuccess) e = hipStreamSynchronize(s);
       if (e != hipSuccess) {
@@ -386,7 +391,7 @@ nvd_status nvd_distances(nvd_graph* h, int32_t k, const double* P, const double*
         st = NVD_E_DEVICE;
       }
     }
-    c0 += T;
+    c0 += cols;
   }
   if (st != NVD_OK) return st;
   for (int j = 0; j < k; ++j) {

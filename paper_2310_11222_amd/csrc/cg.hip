@@ -39,7 +39,16 @@ struct ProjSrc {
   long lda;
   const double* b;   // optional second operand subtracted (ldb), may be null
   long ldb;
+  int cols;          // columns there are (0: the whole tile); the rest of a
+                     // ragged tile reads as zero
 };
+
+__device__ __forceinline__ double proj_value(const ProjSrc& src, long i, int c) {
+  if (src.cols > 0 && c >= src.cols) return 0.0;
+  double v = src.a[i * src.lda + c];
+  if (src.b) v -= src.b[i * src.ldb + c];
+  return v;
+}
 
 // Column sums of (a - b) over all rows; the grid's last block stores
 // mean[c] = sum / n (single-component graphs).
@@ -52,9 +61,7 @@ __global__ __launch_bounds__(kBS) void k_colsum(int n, ProjSrc src, ColState* cs
   constexpr int RPB = kBS / T;
   double acc[1][1] = {{0.0}};
   for (long i = (long)blockIdx.x * RPB + t / T; i < n; i += (long)gridDim.x * RPB) {
-    double v = src.a[i * src.lda + c];
-    if (src.b) v -= src.b[i * src.ldb + c];
-    acc[0][0] += v;
+    acc[0][0] += proj_value(src, i, c);
   }
   block_reduce_cols<kBS, 1, 1>(acc, T, sh);
   if (t < T) vals[t] = sh[t];
@@ -76,9 +83,7 @@ __global__ __launch_bounds__(kBS) void k_comp_mean(int ncomp, const int* perm, c
     double acc[1][1] = {{0.0}};
     for (int p = lo + t / T; p < hi; p += RPB) {
       const long i = perm[p];
-      double v = src.a[i * src.lda + c];
-      if (src.b) v -= src.b[i * src.ldb + c];
-      acc[0][0] += v;
+      acc[0][0] += proj_value(src, i, c);
     }
     block_reduce_cols<kBS, 1, 1>(acc, T, sh);
     if (t < T) cmean[(long)k * kMaxTile + t] = sh[t] / (double)(hi - lo);
@@ -119,7 +124,7 @@ __global__ __launch_bounds__(kBS) void k_proj_init(int n, long cap, ProjSrc src,
     const int c = (int)(e % T);
     double v = 0.0;
     if (i < n) {
-      v = src.a[i * src.lda + c] - (src.b ? src.b[i * src.ldb + c] : 0.0) - mean_of(m, i, c);
+      v = proj_value(src, i, c) - mean_of(m, i, c);
       acc[0][0] += v * v;
       acc[1][0] += v * v * invd[i];
     }
@@ -561,7 +566,7 @@ __global__ __launch_bounds__(kBS) void k_accum(long cap, double* x64, const floa
 // x -= mean (per component), optionally copied to the caller's X.
 template <int T>
 __global__ __launch_bounds__(kBS) void k_xfinal(int n, double* x64, MeanSrc m, double* X,
-                                                long ldx) {
+                                                long ldx, int cols) {
   const int t = threadIdx.x;
   const long tot = (long)n * T;
   for (long e = (long)blockIdx.x * kBS + t; e < tot; e += (long)gridDim.x * kBS) {
@@ -569,19 +574,19 @@ __global__ __launch_bounds__(kBS) void k_xfinal(int n, double* x64, MeanSrc m, d
     const int c = (int)(e % T);
     const double v = x64[e] - mean_of(m, i, c);
     x64[e] = v;
-    if (X) X[i * ldx + c] = v;
+    if (X && c < cols) X[i * ldx + c] = v;
   }
 }
 
 // Warm start: x64 = X - mean is copied in (the caller's guess), b is kept.
 template <int T>
-__global__ __launch_bounds__(kBS) void k_xload(int n, double* x64, const double* X, long ldx) {
+__global__ __launch_bounds__(kBS) void k_xload(int n, double* x64, const double* X, long ldx, int cols) {
   const int t = threadIdx.x;
   const long tot = (long)n * T;
   for (long e = (long)blockIdx.x * kBS + t; e < tot; e += (long)gridDim.x * kBS) {
     const long i = e / T;
     const int c = (int)(e % T);
-    x64[e] = X[i * ldx + c];
+    x64[e] = c < cols ? X[i * ldx + c] : 0.0;
   }
 }
 
@@ -1067,12 +1072,15 @@ nvd_status solve_tile_ws(DevGraph* g, Workspace* ws, int T, const double* P, con
   const long cap = (long)padded_cap(n, T);
   const int grid = stream_grid(cap);
   const double rtol2 = sp.rtol * sp.rtol;
+  // a ragged tile: its last columns are zero, so they are never active and
+  // nothing is read or written for them
+  const int cols = sp.cols > 0 ? sp.cols : T;
 
   // (a2) delta_bar = (P - Q) minus its per-component mean
   MeanSrc m{};
-  NVD_TRY(mean_into(g, ws, T, ProjSrc{P, ld, Q, ld}, &m, s));
+  NVD_TRY(mean_into(g, ws, T, ProjSrc{P, ld, Q, ld, cols}, &m, s));
   NVD_TILE_SWITCH(T, (k_proj_init<TT><<<grid, kBS, 0, s>>>(
-                         n, cap, ProjSrc{P, ld, Q, ld}, m, g->invd64, ws->b64, ws->x64, ws->r64,
+                         n, cap, ProjSrc{P, ld, Q, ld, cols}, m, g->invd64, ws->b64, ws->x64, ws->r64,
                          ws->p64, ws->q64, mixed ? 0 : 1, ws->cs, ws->red)));
   NVD_HIP(hipGetLastError());
   if (sp.tree && !mixed) NVD_TRY(tree_start<double>(g, ws, T, ws->r64, ws->p64, sp, s));
@@ -1094,7 +1102,7 @@ nvd_status solve_tile_ws(DevGraph* g, Workspace* ws, int T, const double* P, con
 
   bool have_x = false;
   if (sp.warm && X) {
-    NVD_TILE_SWITCH(T, (k_xload<TT><<<grid, kBS, 0, s>>>(n, ws->x64, X, ldx)));
+    NVD_TILE_SWITCH(T, (k_xload<TT><<<grid, kBS, 0, s>>>(n, ws->x64, X, ldx, cols)));
     NVD_HIP(hipGetLastError());
     have_x = true;
   }
@@ -1110,7 +1118,7 @@ nvd_status solve_tile_ws(DevGraph* g, Workspace* ws, int T, const double* P, con
       // x mean-zero, true residual, restart if needed
       MeanSrc mx{};
       NVD_TRY(mean_into(g, ws, T, ProjSrc{ws->x64, T, nullptr, 0}, &mx, s));
-      NVD_TILE_SWITCH(T, (k_xfinal<TT><<<grid, kBS, 0, s>>>(n, ws->x64, mx, nullptr, 0)));
+      NVD_TILE_SWITCH(T, (k_xfinal<TT><<<grid, kBS, 0, s>>>(n, ws->x64, mx, nullptr, 0, T)));
       NVD_TRY(launch_apply(resid, ws->red, s));
       k_check<<<1, 64, 0, s>>>(T, rtol2, ws->cs);
       NVD_HIP(hipGetLastError());
@@ -1218,7 +1226,7 @@ nvd_status solve_tile_ws(DevGraph* g, Workspace* ws, int T, const double* P, con
     } else {
       MeanSrc mx{};
       NVD_TRY(mean_into(g, ws, T, ProjSrc{ws->x64, T, nullptr, 0}, &mx, s));
-      NVD_TILE_SWITCH(T, (k_xfinal<TT><<<grid, kBS, 0, s>>>(n, ws->x64, mx, nullptr, 0)));
+      NVD_TILE_SWITCH(T, (k_xfinal<TT><<<grid, kBS, 0, s>>>(n, ws->x64, mx, nullptr, 0, T)));
       NVD_TRY(launch_apply(resid, ws->red, s));
     }
   }
@@ -1227,9 +1235,9 @@ nvd_status solve_tile_ws(DevGraph* g, Workspace* ws, int T, const double* P, con
     MeanSrc xm{};
     xm.n = n;
     if (shift_n > 0) xm.dots_sum = ws->cs->dots[4];
-    NVD_TILE_SWITCH(T, (k_xfinal<TT><<<grid, kBS, 0, s>>>(n, ws->x64, xm, X, ldx)));
+    NVD_TILE_SWITCH(T, (k_xfinal<TT><<<grid, kBS, 0, s>>>(n, ws->x64, xm, X, ldx, cols)));
   }
-  k_finish<<<1, 64, 0, s>>>(T, fp64_finish ? 1 : 0, ws->cs, d_out, info_dev, shift_n,
+  k_finish<<<1, 64, 0, s>>>(cols, fp64_finish ? 1 : 0, ws->cs, d_out, info_dev, shift_n,
                             sp.out_dsq ? 1 : 0);
   NVD_HIP(hipGetLastError());
   return NVD_OK;

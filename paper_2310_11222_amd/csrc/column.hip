@@ -260,14 +260,17 @@ __global__ __launch_bounds__(kColBS) void k_column(ColArgs a) {
     dots[0] += b[e] * xe;
     dots[1] += xe * re;
     dots[2] += re * re;
-    if (a.X) a.X[job.xoff + (long)g.perm[e] * job.ldx] = xe;
+    const long at = job.xoff + (long)g.perm[e] * job.ldx;
+    if (a.X) a.X[at] = xe;
+    if (a.B) a.B[at] = b[e];
+    if (a.R) a.R[at] = re;
   }
   col_sum<3>(dots, S, turn);
   if (t == 0) {
     const double dsq = bb > 0.0 ? dots[0] + dots[1] : 0.0;
     if (fp64_done && status == kStOk && open) status = kStNoconv;
     const double d0 = dsq > 0.0 ? dsq : 0.0;
-    a.d_out[a.col0 + job.out] = a.out_dsq ? d0 : sqrt(d0);
+    if (a.d_out) a.d_out[a.col0 + job.out] = a.out_dsq ? d0 : sqrt(d0);
     nvd_pair_info pi;
     pi.status = status;
     pi.iters = iters;
@@ -640,9 +643,15 @@ static nvd_status finish_multi_kernel(DevGraph* g, int col, int block, const dou
   SolveParams f = sp;
   f.precision = NVD_FP64;
   f.warm = true;
+  f.cols = 1;
   NVD_TRY(ensure_workspace(g, 1, false));
-  NVD_TRY(solve_tile(g, 1, P + col, Q + col, ld, f, a.d_out + col, X, 1, g->ws->info, s));
-  if (a.X) k_column_put<<<(n + 255) / 256, 256, 0, s>>>(n, X, a.X + col, a.ldx);
+  // (without a place for d: past the pair's x)
+  double* d = a.d_out ? a.d_out + col : X + a.stride;
+  NVD_TRY(solve_tile(g, 1, P + col, Q ? Q + col : nullptr, ld, f, d, X, 1, g->ws->info, s));
+  const int grid = (n + 255) / 256;
+  if (a.X) k_column_put<<<grid, 256, 0, s>>>(n, X, a.X + col, a.ldx);
+  if (a.B) k_column_put<<<grid, 256, 0, s>>>(n, g->ws->b64, a.B + col, a.ldx);
+  if (a.R) k_column_put<<<grid, 256, 0, s>>>(n, g->ws->r64, a.R + col, a.ldx);
   NVD_HIP(hipGetLastError());
   nvd_pair_info got;
   NVD_HIP(hipMemcpyAsync(&got, g->ws->info, sizeof(got), hipMemcpyDeviceToHost, s));
@@ -657,7 +666,7 @@ static nvd_status finish_multi_kernel(DevGraph* g, int col, int block, const dou
 // The k pairs (P[:, j], Q[:, j]) of one graph.
 nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, int64_t ld,
                         const SolveParams& sp, double* d_out, double* X, int64_t ldx,
-                        nvd_pair_info* info, hipStream_t s) {
+                        nvd_pair_info* info, hipStream_t s, double* B, double* R) {
   const bool mixed = sp.precision == NVD_MIXED;
   NVD_TRY(ensure_column(g, s));
   const ColPlan* cp = g->col;
@@ -686,6 +695,8 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
   const size_t bytes = hb + sizeof(double) * (size_t)a.lds_n;
   a.d_out = d_out;
   a.X = X;
+  a.B = B;
+  a.R = R;
   a.ldx = ldx;
   a.info = g->col_ws.info;
   a.vec = g->col_ws.vec;

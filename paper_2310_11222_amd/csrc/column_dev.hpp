@@ -97,7 +97,9 @@ struct ColArgs {
   int handover;              // mixed: pairs that FP32 cannot finish are left to an FP64 launch
   int resume;                // FP64: only those pairs, from their x in vec
   double* d_out;
-  double* X;
+  double* X;                 // null, or n x k (ldx) for the solutions; the same
+  double* B;                 // for delta_bar
+  double* R;                 // and for the final residuals
   long ldx;
   nvd_pair_info* info;       // pinned host memory, one per block from info0
   double* vec;               // [blocks][4][stride] b, x, r, FP32 x

@@ -209,7 +209,12 @@ struct SolveParams {
                             // Jacobi: the spanning forest, or (achol) the factor
   bool achol;               // the approximate-Cholesky factor
   bool out_dsq;             // d_out receives d^2 instead of d
+  int cols;                 // pairs of this tile where it is ragged (0: as many as it is wide)
 };
+// Tile of the next pass over the `left` remaining of k pairs: `tile` while
+// plenty are left, then what covers the rest in the least estimated time, a
+// tile wider than the rest included (tune.hip).
+int next_tile(const DevGraph* g, int k, int left, int tile, const SolveParams& sp);
 nvd_status solve_tile(DevGraph* g, int T, const double* P, const double* Q, int64_t ld,
                       const SolveParams& sp, double* d_out, double* X, int64_t ldx,
                       nvd_pair_info* info_dev, hipStream_t s);
@@ -225,11 +230,12 @@ nvd_status solve_small(DevGraph* g, int T, int nb, const double* P, const double
                        const SolveParams& sp, double* d_out, double* X, int64_t ldx,
                        nvd_pair_info* info_dev, hipStream_t s);
 // One block per column on graphs whose vector fits one CU's LDS (column.hip):
-// all k pairs in one launch, info on the host on return.
+// all k pairs in one launch, info on the host on return.  Q may be null (P
+// alone); B, R: null, or n x k (ldx) for delta_bar and the final residual.
 bool use_column(const DevGraph* g, int k, const SolveParams& sp);
 nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, int64_t ld,
                         const SolveParams& sp, double* d_out, double* X, int64_t ldx,
-                        nvd_pair_info* info, hipStream_t s);
+                        nvd_pair_info* info, hipStream_t s, double* B = nullptr, double* R = nullptr);
 void column_weights_changed(DevGraph* g);
 void free_column(DevGraph* g);
 void free_column_ws(ColWs* w);

@@ -29,12 +29,12 @@ constexpr int kGramRows = 16;   // rows staged in LDS per step
 constexpr int kGramBlocks = 2048;
 constexpr int kPairwiseMax = 4096;
 
-// Columns c0 .. c0+T-1 of an n x m row-major matrix from an n x T tile.
-__global__ void k_tile_put(int n, int T, const double* __restrict__ src, double* __restrict__ dst,
-                           long ld) {
+// Columns c0 .. c0+cols-1 of an n x m row-major matrix from an n x T tile.
+__global__ void k_tile_put(int n, int T, int cols, const double* __restrict__ src,
+                           double* __restrict__ dst, long ld) {
   const long tot = (long)n * T;
   for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < tot; e += (long)gridDim.x * blockDim.x)
-    dst[(e / T) * ld + e % T] = src[e];
+    if (e % T < cols) dst[(e / T) * ld + e % T] = src[e];
 }
 
 // Partial Gt tile of rows [i0, i1): part[s][a][b] = sum_i Vb[i][a] X[i][b] + X[i][a] R[i][b]
@@ -269,13 +269,20 @@ extern "C" nvd_status nvd_pairwise(nvd_graph* h, int32_t m, const double* V, int
   sp.warm = false;
   sp.achol = (o.flags & NVD_PRECOND_ACHOL) != 0;
   sp.tree = sp.achol || use_tree(g, o.flags);
-  int tile = o.tile_k;
-  if (tile == 0) tile = choose_tile(g, m, o.precision, s);
   std::vector<nvd_pair_info> hinfo(m);
   nvd_status st = NVD_OK;
-  for (int c0 = 0; c0 < m && st == NVD_OK;) {
+  const bool column = o.tile_k == 0 && use_column(g, m, sp);
+  if (column) st = solve_column(g, m, V, nullptr, ld, sp, nullptr, X, m, hinfo.data(), s, Vb, R);
+  int tile = o.tile_k;
+  if (tile == 0 && !column) tile = choose_tile(g, m, o.precision, s);
+  for (int c0 = column ? m : 0; c0 < m && st == NVD_OK;) {
     int T = tile;
-    while (T > m - c0) T >>= 1;
+    if (o.tile_k == 0)
+      T = next_tile(g, m, m - c0, tile, sp);
+    else
+      while (T > m - c0) T >>= 1;
+    const int cols = std::min(T, m - c0);
+    sp.cols = cols;
     sp.nl = tuned_nl(g, o.precision, T);
     st = ensure_workspace(g, T, o.precision == NVD_MIXED);
     // x of the tile's columns into X; delta_bar and the final residual stay
@@ -284,11 +291,11 @@ extern "C" nvd_status nvd_pairwise(nvd_graph* h, int32_t m, const double* V, int
       st = solve_tile(g, T, V + c0, nullptr, ld, sp, dscratch, X + c0, m, g->ws->info, s);
     if (st == NVD_OK) {
       const int grid = (int)std::min<long>(2048, ((long)n * T + 255) / 256);
-      k_tile_put<<<std::max(grid, 1), 256, 0, s>>>(n, T, g->ws->b64, Vb + c0, m);
-      k_tile_put<<<std::max(grid, 1), 256, 0, s>>>(n, T, g->ws->r64, R + c0, m);
+      k_tile_put<<<std::max(grid, 1), 256, 0, s>>>(n, T, cols, g->ws->b64, Vb + c0, m);
+      k_tile_put<<<std::max(grid, 1), 256, 0, s>>>(n, T, cols, g->ws->r64, R + c0, m);
       hipError_t e = hipGetLastError();
       if (e == hipSuccess)
-        e = hipMemcpyAsync(hinfo.data() + c0, g->ws->info, sizeof(nvd_pair_info) * T,
+        e = hipMemcpyAsync(hinfo.data() + c0, g->ws->info, sizeof(nvd_pair_info) * cols,
                            hipMemcpyDeviceToHost, s);
       if (e == hipSuccess) e = hipStreamSynchronize(s);
       if (e != hipSuccess) {
@@ -296,7 +303,7 @@ extern "C" nvd_status nvd_pairwise(nvd_graph* h, int32_t m, const double* V, int
         st = NVD_E_DEVICE;
       }
     }
-    c0 += T;
+    c0 += cols;
   }
   if (st == NVD_OK) {
     k_gram<<<dim3(ntiles, S), 256, 0, s>>>(n, m, Vb, X, R, rows_per_slice, tiles_1d, part);

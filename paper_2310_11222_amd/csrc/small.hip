@@ -63,6 +63,7 @@ struct SmallArgs {
   const double* P;
   const double* Q;
   long ld;
+  int cols;            // pairs of a ragged tile (its other columns are zero)
   double *b64, *x64, *r64, *p64, *q64;
   float *x32, *r32, *p32, *q32;
   double rtol2, irtol2, stall_ratio2;
@@ -527,7 +528,7 @@ __global__ __launch_bounds__(kSmallBS) void k_small_solve(SmallArgs a) {
     double acc[1] = {0.0};
     for (long e = elem0(); e < nT; e += elem_step()) {
       const long i = e / T;
-      acc[0] += a.P[i * a.ld + c] - a.Q[i * a.ld + c];
+      if (c < a.cols) acc[0] += a.P[i * a.ld + c] - a.Q[i * a.ld + c];
     }
     small_reduce<1, T>(acc, a, S, sh, red);
     if (t < T) S.mean[t] = red[t] / (double)n;
@@ -538,7 +539,7 @@ __global__ __launch_bounds__(kSmallBS) void k_small_solve(SmallArgs a) {
     double acc[2] = {0.0, 0.0};
     for (long e = elem0(); e < nT; e += elem_step()) {
       const long i = e / T;
-      const double v = a.P[i * a.ld + c] - a.Q[i * a.ld + c] - m;
+      const double v = c < a.cols ? a.P[i * a.ld + c] - a.Q[i * a.ld + c] - m : 0.0;
       a.b64[e] = v;
       a.x64[e] = 0.0;
       acc[0] += v * v;
@@ -687,9 +688,10 @@ __global__ __launch_bounds__(kSmallBS) void k_small_solve(SmallArgs a) {
   }
   // (a8) quadratic form, distances, per-pair info; x out
   if (a.X) {
-    for (long e = elem0(); e < nT; e += elem_step()) a.X[(e / T) * a.ldx + (e % T)] = a.x64[e];
+    for (long e = elem0(); e < nT; e += elem_step())
+      if (c < a.cols) a.X[(e / T) * a.ldx + c] = a.x64[e];
   }
-  if (blockIdx.x == 0 && t < T) {
+  if (blockIdx.x == 0 && t < a.cols) {
     const double bx = S.dots[0][t], xr = S.dots[1][t], rr = S.dots[2][t];
     const double bb = S.obnorm2[t];
     double dsq = bx + xr;
@@ -862,6 +864,7 @@ nvd_status solve_small(DevGraph* g, int T, int nb, const double* P, const double
   a.P = P;
   a.Q = Q;
   a.ld = ld;
+  a.cols = sp.cols > 0 ? sp.cols : T;
   a.b64 = ws->b64;
   a.x64 = ws->x64;
   a.r64 = ws->r64;

@@ -8,7 +8,7 @@
 // apply.  Which wins depends on the graph, so the candidates are timed on the
 // graph itself: for each T the apply alone picks NL, then one whole CG
 // iteration (apply, update, direction) with that NL is timed, and the T
-// minimising the time for all k columns, ceil(k / T) * t_iter(T), is cached in
+// minimising the time for all k columns (full tiles and the rest) is cached in
 // the graph handle per (precision, k bucket).
 #include <algorithm>
 #include <cstdlib>
@@ -78,6 +78,47 @@ int untimed_tile(const DevGraph* g, int k, int precision) {
   return t > 0 ? t : heuristic_tile(k);
 }
 
+// Estimated time (us) of one CG iteration of a tile, for the choice between
+// covers of a ragged rest only: launch and reduction latency, one line
+// request per gather up to 64 bytes of row (a wider row costs by its size),
+// and ten vector passes at streaming rate.  On the 10^7-node power-law graph
+// (FP32) it gives 2.7 ms at T = 16 (measured 2.4) and 1.6 at T = 1 (row-wise
+// 1.3); at 10^5 nodes 18 + 23 + 14 us at T = 32.
+static double iteration_estimate(const DevGraph* g, int T, const SolveParams& sp) {
+  const double es = sp.precision == NVD_MIXED ? 4.0 : 8.0;
+  const double row = T * es;
+  const double n = g->n;
+  if (g->n_comp == 1 && !sp.tree && !sp.warm && n * T <= 262144.0) return 22.0 + 8.0e-5 * n * T;   // one launch
+  // (an explicit preconditioner's solve costs some twenty passes in FP64)
+  const double passes = sp.tree ? 10.0 + 160.0 / es : 10.0;
+  return (sp.tree ? 60.0 : 18.0) + 2.0e-5 * g->nnz * std::max(1.0, row / 84.0) + n * row * passes / 5.5e6;
+}
+
+int next_tile(const DevGraph* g, int k, int left, int tile, const SolveParams& sp) {
+  // a tile that was picked over wider ones is not exceeded
+  const int most = 2 * tile > k ? std::min(2 * tile, kMaxTile) : tile;
+  if (left >= 2 * tile || left >= most) return tile;
+  int wide = 1;                                  // one tile over all that is left
+  while (wide < left && wide < most) wide *= 2;
+  if (wide == left) return wide;
+  // best[r]: least time for r columns; the tile that it starts with
+  double best[kMaxTile + 1];
+  int take[kMaxTile + 1];
+  best[0] = 0.0;
+  for (int r = 1; r <= left; ++r) {
+    best[r] = 1e300;
+    for (int T = 1; T <= wide; T *= 2) {
+      const double t = iteration_estimate(g, T, sp) + best[std::max(0, r - T)];
+      if (t < best[r]) {
+        best[r] = t;
+        take[r] = T;
+      }
+      if (T >= r) break;                         // one tile holds all r
+    }
+  }
+  return take[left];
+}
+
 int choose_tile(DevGraph* g, int k, int precision, hipStream_t s) {
   if (k <= 8 || g->n < 4096 || tuning_disabled()) return heuristic_tile(k);
   const int p = precision == NVD_MIXED ? 1 : 0;
@@ -104,7 +145,16 @@ int choose_tile(DevGraph* g, int k, int precision, hipStream_t s) {
     g->tuned_nl[p][log2i(T)] = nlT;
     float it_ms = 0.0f;
     if (time_cg_iteration(g, prec, T, nlT, s, &it_ms) != NVD_OK) return heuristic_tile(k);
-    const double total = (double)((k + T - 1) / T) * it_ms;
+    // full tiles, then the rest in the cover that next_tile takes for it
+    SolveParams sp{};
+    sp.precision = precision;
+    double rest = 0.0;
+    for (int left = k % T; left > 0;) {
+      const int Tr = next_tile(g, k, left, T, sp);
+      rest += iteration_estimate(g, Tr, sp) / iteration_estimate(g, T, sp);
+      left -= Tr;
+    }
+    const double total = ((double)(k / T) + rest) * it_ms;
     if (total < best) {
       best = total;
       bestT = T;

@@ -354,8 +354,13 @@ nvd_status nvd_distances(nvd_graph* h, int32_t k, const double* P, const double*
   nvd_status st = NVD_OK;
   // small graphs: every pair by a block of its own (a tile asked for by the
   // caller keeps the paths that solve tiles)
-  const bool column = o.tile_k == 0 && use_column(g, k, sp);
+  bool column = o.tile_k == 0 && use_column(g, k, sp);
   if (column) st = solve_column(g, k, P, Q, ld, sp, d_out, X, ldx, hinfo.data(), s);
+  if (st == NVD_E_UNSUPPORTED) {   // (more augmenting edges than a block takes)
+    column = false;
+    st = NVD_OK;
+    set_error("");
+  }
   int tile = o.tile_k;
   if (tile == 0 && !column) tile = choose_tile(g, k, o.precision, s);
   for (int c0 = column ? k : 0; c0 < k && st == NVD_OK;) {

@@ -467,6 +467,7 @@ void free_achol(AcholPre* ap) {
                   ap->part};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
+  free_column_pre(ap->col);
   delete ap;
 }
 

@@ -29,13 +29,10 @@
 #include <numeric>
 #include <vector>
 
-#include "column_dev.hpp"
+#include "column_kernel.hpp"
 
 namespace nvd {
 
-// LDS for the gathered vector and the heavy rows' sums (a CU has 160 KB;
-// the block's partial sums are static).
-constexpr int kColLds = 152 * 1024;
 // Rows with more neighbours than this (and more than twice the mean) are
 // heavy, and cut into parts of at least kColPart neighbours, so many that at
 // most kColMaxParts are needed.
@@ -47,242 +44,6 @@ constexpr int kColHubDeg = 64;
 constexpr int kColMaxEPT = 32;   // FP64: 17, what LDS holds
 // Columns of one launch (one CU each).
 constexpr int kColChunk = 256;
-// Status of a pair between the mixed launch and the FP64 one (never returned).
-constexpr int kColResume = -1;
-
-template <bool MIXED, bool UNIT, int EPT>
-__global__ __launch_bounds__(kColBS) void k_column(ColArgs a) {
-  extern __shared__ double lds[];
-  __shared__ ColShared S;
-  int t = thread_here();
-  int turn = 0;
-  ColGraph g;
-  ColJob job;
-  if (a.jobs) {
-    job = a.jobs[blockIdx.x];
-    g = a.graphs[job.graph];
-  } else {
-    g = a.g;
-    job.out = blockIdx.x;
-    job.voff = a.col0 + blockIdx.x;
-    job.ld = a.ld;
-    job.xoff = job.voff;
-    job.ldx = a.ldx;
-  }
-  make_scalar(g);
-  const int n = g.n;
-  double* const hq = lds;                       // [nv], ahead of the vector
-  double* const buf = lds + ((g.nv + 1) & ~1);
-  double* const b = a.vec + (size_t)blockIdx.x * 4 * a.stride;
-  double* const x = b + a.stride;
-  double* const r = x + a.stride;
-  double* const cm = a.cmean + (size_t)blockIdx.x * a.cstride;
-
-  int status = kStOk, iters = 0, refine = 0, fb = 0;
-  if (!MIXED && a.resume) {
-    if (a.info[job.out].status != kColResume) return;
-    iters = a.info[job.out].iters;
-    refine = a.info[job.out].refine_steps;
-    fb = 1;
-  }
-  double init[2] = {0.0, 0.0};
-  double rv[MIXED ? 1 : EPT];
-  if (!MIXED && a.resume) {
-    // b and x are those of the mixed launch; r is the residual of x
-    col_resid<UNIT>(g, x, b, r, buf, a.lds_n, hq);
-    t = thread_here();
-#pragma unroll
-    for (int j = 0; j < EPT; ++j) {
-      const int e = t + j * kColBS;
-      if constexpr (!MIXED) rv[j] = 0.0;
-      if (e < n) {
-        const double v = r[e];
-        init[0] += b[e] * b[e];
-        init[1] += v * v * g.inv64[e];
-        if constexpr (!MIXED) rv[j] = v;
-      }
-      four_at_a_time<EPT>(j);
-    }
-    col_sum<2>(init, S, turn);
-  } else {
-    // (a2) delta_bar = (P - Q) minus its mean on every component
-    for (int e = t; e < g.slots * kColBS; e += kColBS) {
-      double v = 0.0;
-      if (e < n) {
-        const long at = job.voff + (long)g.perm[e] * job.ld;
-        v = a.P[at] - (a.Q ? a.Q[at] : 0.0);
-      }
-      b[e] = v;
-      x[e] = 0.0;
-      r[e] = 0.0;
-    }
-    __syncthreads();
-    const double mean0 = col_means(g, b, cm, S, turn);
-#pragma unroll
-    for (int j = 0; j < EPT; ++j) {
-      const int e = t + j * kColBS;
-      if constexpr (!MIXED) rv[j] = 0.0;
-      if (e < n) {
-        const double v = b[e] - col_mean(g, cm, mean0, e);
-        b[e] = v;
-        r[e] = v;
-        init[0] += v * v;
-        init[1] += v * v * g.inv64[e];
-        if constexpr (!MIXED) rv[j] = v;
-      }
-      four_at_a_time<EPT>(j);
-    }
-    col_sum<2>(init, S, turn);
-  }
-  const double bb = init[0];
-  double rho = init[1];
-  int open = bb > 0.0;
-  bool fp64_done = false;
-
-  if constexpr (MIXED) {
-    float* const x32 = reinterpret_cast<float*>(r + a.stride);
-    float* const p32 = reinterpret_cast<float*>(buf);
-    int stall = 0;
-    double orr = bb;
-    for (int step = 0; uniform(open != 0) && step <= a.max_refine; ++step) {
-      double m = 0.0;
-      if (step > 0) {
-        // (a7) FP64 outer residual, projected
-        col_resid<UNIT>(g, x, b, r, buf, a.lds_n, hq);
-        m = col_means(g, r, cm, S, turn);
-      }
-      float f[EPT];
-      t = thread_here();
-      double s3[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-      for (int j = 0; j < EPT; ++j) {
-        const int e = t + j * kColBS;
-        f[j] = 0.0f;
-        if (j < g.slots) x32[e] = 0.0f;
-        if (e < n) {
-          const double v = r[e] - (step > 0 ? col_mean(g, cm, m, e) : 0.0);
-          f[j] = (float)v;
-          const float z = f[j] * g.inv32[e];
-          s3[0] += v * v;
-          s3[1] += (double)f[j] * (double)z;
-          s3[2] += (double)f[j] * (double)f[j];
-        }
-        four_at_a_time<EPT>(j);
-      }
-      col_sum<3>(s3, S, turn);
-      const double rr = s3[0];
-      if (step > 0 && a.handover) stall = refine_stall_count(orr, rr, stall, a.stall_ratio2);
-      orr = rr;
-      if (uniform(step > 0 && rr <= a.rtol2 * bb)) {
-        open = 0;
-        break;
-      }
-      if (uniform(refine_hand_to_fp64(stall))) {
-        open = 0;
-        fb = 1;
-        break;
-      }
-      if (refine >= a.max_refine) {
-        open = 0;
-        status = kStNoconv;
-        break;
-      }
-      if (!uniform(s3[2] > 0.0)) {
-        open = 0;               // the residual rounds to zero in FP32
-        break;
-      }
-      refine += 1;
-      const double need2 = rr > 0.0 ? 0.09 * a.rtol2 * bb / rr : 0.0;
-      const double it2 = need2 > a.irtol2 ? (need2 < 0.25 ? need2 : 0.25) : a.irtol2;
-      const ColRun run = col_cg<float, UNIT, EPT>(g, p32, hq, f, x32, s3[1], s3[2], it2, a.max_iter, S, turn);
-      iters += run.iters;
-      if (run.status == kStOk) {
-        for (int e = t; e < n; e += kColBS) x[e] += (double)x32[e];
-      } else {
-        open = 0;
-        if (run.status == kStNoconv && a.handover)
-          fb = 1;               // FP64 finishes from the last good x
-        else
-          status = run.status;
-      }
-    }
-    if (fb) {
-      // left to the FP64 launch, which takes b and x from vec
-      if (t == 0) {
-        nvd_pair_info pi{};
-        pi.status = kColResume;
-        pi.iters = iters;
-        pi.refine_steps = refine;
-        a.info[job.out] = pi;
-      }
-      return;
-    }
-    // the last residual is that of the final x, whose shift to mean zero
-    // leaves L x as it is
-    __syncthreads();
-    const double mx = col_means(g, x, cm, S, turn);
-    for (int e = t; e < n; e += kColBS) x[e] -= col_mean(g, cm, mx, e);
-  } else {
-    fp64_done = true;
-    for (int restarts = 0; open; ++restarts) {
-      if (uniform(rho > 0.0)) {
-        const ColRun run =
-            col_cg<double, UNIT, EPT>(g, buf, hq, rv, x, rho, bb, a.rtol2, a.max_iter, S, turn);
-        iters += run.iters;
-        status = run.status;
-      }
-      const double mx = col_means(g, x, cm, S, turn);
-      for (int e = t; e < n; e += kColBS) x[e] -= col_mean(g, cm, mx, e);
-      col_resid<UNIT>(g, x, b, r, buf, a.lds_n, hq);
-      double s2[2] = {0.0, 0.0};
-      t = thread_here();
-#pragma unroll
-      for (int j = 0; j < EPT; ++j) {
-        const int e = t + j * kColBS;
-        if (e < n) {
-          rv[j] = r[e];
-          s2[0] += rv[j] * rv[j];
-          s2[1] += rv[j] * rv[j] * g.inv64[e];
-        }
-        four_at_a_time<EPT>(j);
-      }
-      col_sum<2>(s2, S, turn);
-      rho = s2[1];
-      open = status == kStOk && uniform(s2[0] > a.rtol2 * bb);
-      if (restarts >= 2) break;
-    }
-  }
-
-  // (a8) quadratic form, distance, per-pair info; x out
-  double dots[3] = {0.0, 0.0, 0.0};
-  for (int e = t; e < n; e += kColBS) {
-    const double xe = x[e], re = r[e];
-    dots[0] += b[e] * xe;
-    dots[1] += xe * re;
-    dots[2] += re * re;
-    const long at = job.xoff + (long)g.perm[e] * job.ldx;
-    if (a.X) a.X[at] = xe;
-    if (a.B) a.B[at] = b[e];
-    if (a.R) a.R[at] = re;
-  }
-  col_sum<3>(dots, S, turn);
-  if (t == 0) {
-    const double dsq = bb > 0.0 ? dots[0] + dots[1] : 0.0;
-    if (fp64_done && status == kStOk && open) status = kStNoconv;
-    const double d0 = dsq > 0.0 ? dsq : 0.0;
-    if (a.d_out) a.d_out[a.col0 + job.out] = a.out_dsq ? d0 : sqrt(d0);
-    nvd_pair_info pi;
-    pi.status = status;
-    pi.iters = iters;
-    pi.refine_steps = refine;
-    pi.flags = fb ? NVD_INFO_FP64_FALLBACK : 0;
-    pi.rel_res = bb > 0.0 ? sqrt(dots[2] / bb) : 0.0;
-    pi.dsq_plain = bb > 0.0 ? dots[0] : 0.0;
-    pi.dsq = dsq;
-    a.info[job.out] = pi;
-  }
-}
-
 // Weights and 1 / degree in the block's order, from the graph's.
 __global__ void k_column_weights(int entries, const int* src, int n, int npad, const int* perm,
                                  const double* w64, const double* invd64, const float* invd32, double* sw64,
@@ -327,8 +88,8 @@ struct ColPlan {
 };
 
 // Scratch and result words of a call, kept with the graph (or the batch).
-nvd_status ensure_column_ws(ColWs* w, long stride, long cstride, int cols, int64_t* bytes) {
-  const size_t vec = (size_t)stride * 4 * cols, cm = (size_t)cstride * cols;
+nvd_status ensure_column_ws(ColWs* w, long stride, int vecs, long cstride, int cols, int64_t* bytes) {
+  const size_t vec = (size_t)stride * vecs * cols, cm = (size_t)cstride * cols;
   if (w->cap_vec < vec || w->cap_cm < cm) {
     (void)hipFree(w->vec);
     w->vec = nullptr;
@@ -553,6 +314,35 @@ static nvd_status ensure_column(DevGraph* g, hipStream_t s) {
   return NVD_OK;
 }
 
+template <bool MIXED, bool UNIT>
+static nvd_status launch_column_n(const ColArgs& a, int n, int blocks, size_t bytes, hipStream_t s) {
+  const int ept = (n + kColBS - 1) / kColBS;
+  if (ept <= 1) return launch_column_k<MIXED, UNIT, 1, false>(a, blocks, bytes, s);
+  if (ept <= 2) return launch_column_k<MIXED, UNIT, 2, false>(a, blocks, bytes, s);
+  if (ept <= 4) return launch_column_k<MIXED, UNIT, 4, false>(a, blocks, bytes, s);
+  if (ept <= 8) return launch_column_k<MIXED, UNIT, 8, false>(a, blocks, bytes, s);
+  if constexpr (MIXED) {
+    if (ept <= 10) return launch_column_k<MIXED, UNIT, 10, false>(a, blocks, bytes, s);
+    if (ept <= 14) return launch_column_k<MIXED, UNIT, 14, false>(a, blocks, bytes, s);
+    if (ept <= 18) return launch_column_k<MIXED, UNIT, 18, false>(a, blocks, bytes, s);
+    if (ept <= 24) return launch_column_k<MIXED, UNIT, 24, false>(a, blocks, bytes, s);
+    return launch_column_k<MIXED, UNIT, 32, false>(a, blocks, bytes, s);
+  } else {
+    // (arrays of 9 to 16 doubles are kept as one register tuple each and
+    // spill as a whole)
+    return launch_column_k<MIXED, UNIT, 17, false>(a, blocks, bytes, s);
+  }
+}
+
+nvd_status launch_column_jacobi(const ColArgs& a, bool mixed, bool unit, int n, int blocks, size_t bytes,
+                                hipStream_t s) {
+  if (mixed)
+    return unit ? launch_column_n<true, true>(a, n, blocks, bytes, s)
+                : launch_column_n<true, false>(a, n, blocks, bytes, s);
+  return unit ? launch_column_n<false, true>(a, n, blocks, bytes, s)
+              : launch_column_n<false, false>(a, n, blocks, bytes, s);
+}
+
 static size_t parts_bytes(int nv) { return sizeof(double) * (size_t)((nv + 1) & ~1); }
 
 // Whether a column of n nodes fits one block: its elements in registers, its
@@ -591,43 +381,24 @@ static bool column_is_faster(const DevGraph* g, int k) {
 }
 
 bool use_column(const DevGraph* g, int k, const SolveParams& sp) {
-  if (sp.tree || sp.achol || sp.warm) return false;
-  if (!column_fits(g->n, sp.precision == NVD_MIXED)) return false;
+  if (sp.warm) return false;
+  if (sp.achol && g->n > kColBS * kColMaxPreEPT) return false;
+  // (the forest's sums are FP64 in either precision)
+  const bool fp64_vector = sp.precision != NVD_MIXED || (sp.tree && !sp.achol);
+  if (!column_fits(g->n, !fp64_vector)) return false;
   // the switches of the other single-launch path ask for it, or for none
   const char* e = std::getenv("NVD_SMALL");
   if (e && e[0] == '0') return false;
   if (std::getenv("NVD_MID_BLOCKS")) return false;
   if (const char* c = std::getenv("NVD_COLUMN")) return c[0] != '0';   // 0 never, 1 wherever it fits
+  // An explicit preconditioner costs the tiled path ten to hundreds of launches
+  // an iteration (the factor two for every round: BA n = 10^4, 8 pairs, 16.5
+  // ms; in blocks 2.0), so the block is taken wherever it fits, except for a
+  // few pairs with the augmented forest on its largest graphs (us an
+  // iteration, block / tiled: 5 slots 48 / 86, 17 slots and 7 pairs 115 / 113).
+  if (sp.achol) return true;
+  if (sp.tree) return g->n <= 14 * kColBS || k > 8;
   return column_is_faster(g, k);
-}
-
-template <bool MIXED, bool UNIT, int EPT>
-static nvd_status launch_column_k(const ColArgs& a, int blocks, size_t bytes, hipStream_t s) {
-  const void* f = reinterpret_cast<const void*>(&k_column<MIXED, UNIT, EPT>);
-  NVD_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kColLds));
-  k_column<MIXED, UNIT, EPT><<<blocks, kColBS, bytes, s>>>(a);
-  NVD_HIP(hipGetLastError());
-  return NVD_OK;
-}
-
-template <bool MIXED, bool UNIT>
-static nvd_status launch_column_n(const ColArgs& a, int n, int blocks, size_t bytes, hipStream_t s) {
-  const int ept = (n + kColBS - 1) / kColBS;
-  if (ept <= 1) return launch_column_k<MIXED, UNIT, 1>(a, blocks, bytes, s);
-  if (ept <= 2) return launch_column_k<MIXED, UNIT, 2>(a, blocks, bytes, s);
-  if (ept <= 4) return launch_column_k<MIXED, UNIT, 4>(a, blocks, bytes, s);
-  if (ept <= 8) return launch_column_k<MIXED, UNIT, 8>(a, blocks, bytes, s);
-  if constexpr (MIXED) {
-    if (ept <= 10) return launch_column_k<MIXED, UNIT, 10>(a, blocks, bytes, s);
-    if (ept <= 14) return launch_column_k<MIXED, UNIT, 14>(a, blocks, bytes, s);
-    if (ept <= 18) return launch_column_k<MIXED, UNIT, 18>(a, blocks, bytes, s);
-    if (ept <= 24) return launch_column_k<MIXED, UNIT, 24>(a, blocks, bytes, s);
-    return launch_column_k<MIXED, UNIT, 32>(a, blocks, bytes, s);
-  } else {
-    // (arrays of 9 to 16 doubles are kept as one register tuple each and
-    // spill as a whole: 8 us an iteration at n = 10^4 with 10)
-    return launch_column_k<MIXED, UNIT, 17>(a, blocks, bytes, s);
-  }
 }
 
 // A pair that FP32 cannot finish on a graph whose FP64 vector does not fit:
@@ -636,7 +407,7 @@ static nvd_status finish_multi_kernel(DevGraph* g, int col, int block, const dou
                                       int64_t ld, const SolveParams& sp, const ColArgs& a,
                                       nvd_pair_info* info, hipStream_t s) {
   const int n = g->n;
-  const double* x = a.vec + ((size_t)block * 4 + 1) * a.stride;
+  const double* x = a.vec + ((size_t)block * a.vecs + 1) * a.stride;
   double* X = const_cast<double*>(x) + a.stride;   // r's place
   k_column_nodes<<<(n + 255) / 256, 256, 0, s>>>(n, g->col->d.perm, x, X);
   NVD_HIP(hipGetLastError());
@@ -673,8 +444,11 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
   const long stride = (long)cp->d.slots * kColBS;
   const long cstride = g->n_comp > 1 ? g->n_comp : 0;
   const int chunk = std::min(k, kColChunk);
-  NVD_TRY(ensure_column_ws(&g->col_ws, stride, cstride, chunk, &g->bytes));
+  const int vecs = sp.tree ? 8 : 4;
+  NVD_TRY(ensure_column_ws(&g->col_ws, stride, vecs, cstride, chunk, &g->bytes));
   ColArgs a{};
+  a.vecs = vecs;
+  if (sp.tree) NVD_TRY(ensure_column_pre(g, sp.achol, cp->d.perm, cp->d.slots, &a.pre));
   a.g = cp->d;
   a.P = P;
   a.Q = Q;
@@ -692,7 +466,9 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
   const size_t hb = parts_bytes(cp->d.nv);
   const size_t most = ((size_t)kColLds - hb) / (sizeof(double) * kColBS) * kColBS;
   a.lds_n = (int)std::min<size_t>(stride, most);
-  const size_t bytes = hb + sizeof(double) * (size_t)a.lds_n;
+  // (the forest's augmentation takes kColAugLds values of it, whatever n)
+  const size_t least = sp.tree ? (size_t)kColAugLds : 0;
+  const size_t bytes = hb + sizeof(double) * std::max<size_t>(a.lds_n, least);
   a.d_out = d_out;
   a.X = X;
   a.B = B;
@@ -705,11 +481,7 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
   a.cstride = cstride;
   a.handover = mixed ? 1 : 0;
   auto launch = [&](bool in_fp64, size_t lds, int cols) -> nvd_status {
-    if (!in_fp64)
-      return g->weighted ? launch_column_n<true, false>(a, g->n, cols, lds, s)
-                         : launch_column_n<true, true>(a, g->n, cols, lds, s);
-    return g->weighted ? launch_column_n<false, false>(a, g->n, cols, lds, s)
-                       : launch_column_n<false, true>(a, g->n, cols, lds, s);
+    return (sp.tree ? launch_column_pre : launch_column_jacobi)(a, !in_fp64, !g->weighted, g->n, cols, lds, s);
   };
   for (int c0 = 0; c0 < k; c0 += chunk) {
     const int cols = std::min(chunk, k - c0);
@@ -723,7 +495,7 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
     for (int j = 0; j < cols; ++j) any = any || left(j);
     if (any && column_fits(g->n, false)) {
       a.resume = 1;
-      NVD_TRY(launch(true, hb + sizeof(double) * (size_t)stride, cols));
+      NVD_TRY(launch(true, hb + sizeof(double) * std::max<size_t>(stride, least), cols));
       NVD_HIP(hipStreamSynchronize(s));
     }
     std::copy(got, got + cols, info + c0);

@@ -73,6 +73,34 @@ __device__ __forceinline__ void make_scalar(ColGraph& g) {
   make_scalar(g.ccomp);
 }
 
+constexpr int kColNoEvent = 0x7fff;
+enum { kColPreTree = 1, kColPreAchol = 2 };
+
+// An explicit preconditioner in the block's order (column_pre.hip).
+struct ColPre {
+  int kind;
+  // approximate Cholesky: forward (0) and backward (1) solve
+  const unsigned short* apos;    // [n] elimination position of each position
+  const int4* steps[2];          // nsteps + 2 (empty ones last)
+  int nsteps[2];
+  const unsigned short* idx[2];
+  const double* c64[2];
+  const float* c32[2];
+  const double* ip64;            // [n] 1 / pivot by elimination position
+  const float* ip32;
+  // spanning forest, by position: preorder place, subtree size, the
+  // component's first and last preorder place, 1 / weight to the parent
+  const unsigned short *tpre, *tsize, *tlo, *thi;
+  const double* twinv;
+  const unsigned short* tour;    // [2 slots][1024] events: preorder place, 0x8000: left
+  int k, nend;                   // augmenting edges, nodes they touch
+  const unsigned short* auv;     // [2k] preorder places of their ends
+  const double* Cinv;            // [k][k]
+  const int* aoff;               // [nend + 1]
+  const unsigned short* aend;    // [nend] preorder place
+  const unsigned short* aedge;   // edge, 0x8000: its second end
+};
+
 // One column to solve: pair data at P[voff + i * ld], results at `out`.
 struct ColJob {
   int graph;
@@ -85,6 +113,8 @@ struct ColJob {
 
 struct ColArgs {
   ColGraph g;                // the graph, unless `graphs` is set
+  ColPre pre;                // its preconditioner (one graph only)
+  int vecs;                  // vectors of a block in vec: 4, with a preconditioner 8
   const ColGraph* graphs;    // several graphs: jobs[block] names the one
   const ColJob* jobs;        // null: block b takes column col0 + b of g
   const double* P;
@@ -102,7 +132,7 @@ struct ColArgs {
   double* R;                 // and for the final residuals
   long ldx;
   nvd_pair_info* info;       // pinned host memory, one per block from info0
-  double* vec;               // [blocks][4][stride] b, x, r, FP32 x
+  double* vec;               // [blocks][vecs][stride] b, x, r, FP32 x, scratch
   long stride;
   double* cmean;             // [blocks][cstride] component means (nc > 1)
   long cstride;

@@ -19,6 +19,9 @@ namespace nvd {
 // ---------------------------------------------------------------------------
 struct Workspace;
 
+struct ColPreDev;   // a preconditioner in the one-block solver's order (column_pre.hip)
+void free_column_pre(ColPreDev* p);
+
 // Spanning forest for the tree preconditioner (built on first use): Euler
 // tour positions, inverse edge weights to the parent, and scan buffers.
 struct TreePre {
@@ -42,6 +45,7 @@ struct TreePre {
   double* aug_Y = nullptr;        // [n][k] L_T^+ U (built with the first tile)
   double* aug_Cinv = nullptr;     // [k][k] C^-1
   double* aug_st = nullptr;       // [2][k][kMaxTile] U^T z, then C^-1 U^T z
+  ColPreDev* col = nullptr;       // the forest as the one-block solver walks it
 };
 
 // Approximate-Cholesky factor for its preconditioner (built on first use):
@@ -62,6 +66,7 @@ struct AcholPre {
   float* ip32 = nullptr;
   double* mean = nullptr;      // [n_comp][kMaxTile]
   double* part = nullptr;      // [blocks][kMaxTile]
+  ColPreDev* col = nullptr;    // the factor as the one-block solver walks it
   std::vector<int> round_off;  // host: positions of each round, last range = remainder
   std::vector<int> fwd_max;    // host: longest forward pull list of each round
   std::vector<int> bwd_max;    // host: longest backward pull list of each round

@@ -271,8 +271,13 @@ extern "C" nvd_status nvd_pairwise(nvd_graph* h, int32_t m, const double* V, int
   sp.tree = sp.achol || use_tree(g, o.flags);
   std::vector<nvd_pair_info> hinfo(m);
   nvd_status st = NVD_OK;
-  const bool column = o.tile_k == 0 && use_column(g, m, sp);
+  bool column = o.tile_k == 0 && use_column(g, m, sp);
   if (column) st = solve_column(g, m, V, nullptr, ld, sp, nullptr, X, m, hinfo.data(), s, Vb, R);
+  if (st == NVD_E_UNSUPPORTED) {   // (more augmenting edges than a block takes)
+    column = false;
+    st = NVD_OK;
+    set_error("");
+  }
   int tile = o.tile_k;
   if (tile == 0 && !column) tile = choose_tile(g, m, o.precision, s);
   for (int c0 = column ? m : 0; c0 < m && st == NVD_OK;) {

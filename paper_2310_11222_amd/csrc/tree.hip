@@ -349,6 +349,7 @@ void free_tree(TreePre* tp) {
                   tp->aug_Cinv};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
+  free_column_pre(tp->col);
   delete tp;
 }
 

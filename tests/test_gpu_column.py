@@ -109,3 +109,45 @@ def test_column_hand_over_new_weights_and_strides(monkeypatch, n):
     np.testing.assert_allclose(X.cpu().numpy(), ref["x"], rtol=0, atol=1e-7 * np.abs(ref["x"]).max())
     d2, _, _ = dg.distances(Pw[:, 2:6], Qw[:, 4:8], precision="fp64", out="dsq")
     assert rel_err(np.sqrt(d2.cpu().numpy()), ref["d"]).max() <= TOL["fp64"]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("precond,model,n,k,weighted", [
+    ("achol", "star", 2, 1, True), ("achol", "many", 4000, 3, True), ("achol", "er", 1025, 2, False),
+    ("achol", "ba", 6000, 3, True), ("achol", "ws", 17408, 2, False), ("achol", "ba", 24576, 1, False),
+    ("tree", "star", 64, 2, True), ("tree", "ring", 1024, 3, True), ("tree", "many", 4000, 2, True),
+    ("tree", "ba1", 9000, 3, False), ("tree", "ring", 17408, 2, True), ("tree", "er", 700, 2, True)])
+def test_column_preconditioners(monkeypatch, precision, precond, model, n, k, weighted):
+    """The factor's rounds and the augmented forest in one block (a forest
+    alone, one or a few hundred edges off it; one component, many)."""
+    rng = np.random.default_rng(n + k)
+    if model == "ring":                                # a cycle with ten chords
+        u = np.arange(n)
+        a = rng.choice(n // 2 - 2, 10, replace=False)
+        g = HostGraph(n, np.concatenate([u[:-1], [0], a]), np.concatenate([u[1:], [n - 1], a + n // 2]))
+        g = g.with_weights(rng.lognormal(0, 1, g.num_edges)) if weighted else g
+    elif model == "ba1":
+        g = barabasi_albert(n, 1, rng)
+    else:
+        g = _graph(model, n, rng, weighted)
+    P, Q = _pairs(g.n, k, rng)
+    say("column", precond, precision, model, n, k, weighted)
+    dg = dev_graph(g)
+    rtol = 1e-10 if precision == "fp64" else 1e-8
+    runs = []
+    for column in ("1", "0"):
+        monkeypatch.setenv("NVD_COLUMN", column)
+        runs.append(dg.distances(P, Q, precision=precision, rtol=rtol, return_x=True, precond=precond))
+    (d1, X1, i1), (d2, X2, i2) = runs
+    d1, d2, X1, X2 = (v.cpu().numpy() for v in (d1, d2, X1, X2))
+    assert all(i["status"] == 0 and i["rel_res"] <= rtol * 1.01 for i in i1), i1
+    assert rel_err(d1, d2).max() <= TOL[precision]
+    # another order of the sums: the counts stay close (a tenth covers FP32
+    # recurrences of many iterations)
+    assert all(abs(a["iters"] - b["iters"]) <= 2 + b["iters"] // 10 for a, b in zip(i1, i2)), (i1, i2)
+    if model in ("star", "er", "ba", "many", "ws"):    # the rest is too long for plain CG on the CPU
+        ref = oracle.ge_pcg(g.n, g.row_ptr, g.col_idx, g.w, P, Q)["d"]
+        assert rel_err(d1, ref).max() <= TOL[precision]
+    monkeypatch.setenv("NVD_COLUMN", "1")
+    d3, X3, _ = dg.distances(P, Q, precision=precision, rtol=rtol, return_x=True, precond=precond)
+    assert np.array_equal(d3.cpu().numpy(), d1) and np.array_equal(X3.cpu().numpy(), X1)

@@ -215,6 +215,7 @@ __global__ void ks_reset(SArgs a) {
     a.s.g_oact[i] = 0;
     a.s.xseq[i] = 0;
     a.s.xdone[i] = 0;
+    a.s.tick[i] = 0u;   // (their place moves with the tile of the call)
   }
   if (i < 2) a.s.n_act[i] = 0;
 }

@@ -33,6 +33,14 @@ constexpr int SBS = 256;          // threads per block of the sweep kernels
 #define NVD_CHUNK_ROWS 1024
 #endif
 constexpr int kChunkRows = NVD_CHUNK_ROWS;   // rows per short chunk
+// Below this many rows in all, chunks of half the size: 64 graphs of 3,300 to
+// 10^5 nodes (2.1M rows) have some 260 full chunks to an XCD's 32 CUs, and the
+// apply, whose gathers want more waves in flight than that, took 21.4 ms a
+// call, 19.5 with half chunks (62 graphs up to 37,000 nodes, 14 pairs: 18.0 and
+// 13.8).  Quarter chunks gave 20.2 and 13.3; the 10^7 rows of 512 graphs are
+// fastest with full ones.  The rule depends on the batch alone, so results
+// repeat.
+constexpr long kHalfChunkRows = 4L << 20;
 // Blocks per sweep kernel at most.  One block per chunk is best measured:
 // the dispatcher then balances the uneven chunk costs (long rows, skipped
 // graphs) better than a grid-stride loop.
@@ -827,6 +835,7 @@ __global__ __launch_bounds__(SBS) void ks_xout(SArgs a) {
 // their summation order are fixed by its rows alone.
 static nvd_status build_chunks(nvd_batch* b, hipStream_t s) {
   const int G = b->G;
+  const int rows = b->tot_n < kHalfChunkRows ? kChunkRows / 2 : kChunkRows;
   std::vector<int> order(G);
   for (int g = 0; g < G; ++g) order[g] = g;
   auto size_of = [&](int g) { return (double)b->nnz[g] + 3.0 * b->n[g]; };
@@ -854,10 +863,10 @@ static nvd_status build_chunks(nvd_batch* b, hipStream_t s) {
       if (xcd[g] != q) continue;
       b->ch_first[g] = (int)cg.size();
       const int n = b->n[g];
-      for (int lo = 0; lo < n; lo += kChunkRows) {
+      for (int lo = 0; lo < n; lo += rows) {
         cg.push_back(g);
         clo.push_back(lo);
-        chi.push_back(std::min(n, lo + kChunkRows));
+        chi.push_back(std::min(n, lo + rows));
       }
       b->ch_nshort[g] = (int)cg.size() - b->ch_first[g];
       for (int r = 0; r < b->n_long[g]; ++r) {

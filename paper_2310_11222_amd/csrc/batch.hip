@@ -940,6 +940,11 @@ nvd_status nvd_batch_create(int32_t G, nvd_graph* const* graphs, void* stream, n
   if (st == NVD_OK && hipHostMalloc((void**)&b->h_err, sizeof(int), hipHostMallocDefault) != hipSuccess)
     st = NVD_E_NOMEM;
   if (st == NVD_OK && hipStreamSynchronize(s) != hipSuccess) st = NVD_E_DEVICE;
+  if (st == NVD_OK) {
+    std::vector<const DevGraph*> gs(G);
+    for (int i = 0; i < G; ++i) gs[i] = graphs[i]->g;
+    st = make_column_batch(G, gs.data(), s, &b->col, &b->bytes);
+  }
   if (st != NVD_OK) {
     batch_free(b);
     delete b;
@@ -1309,7 +1314,10 @@ extern "C" nvd_status nvd_batch_distances(nvd_batch* b, const int32_t* k_per_gra
   nvd_status st = NVD_E_UNSUPPORTED;
   const bool mixed = o.precision == NVD_MIXED;
   if (!(o.flags & NVD_BATCH_PERSISTENT)) {
-    st = run_sweep(b, ks, T, o, P, Q, d_out, X_out, hinfo.data(), s);
+    if (b->col && use_column_batch(b->col, mixed))
+      st = solve_column_batch(b->col, ks, o, P, Q, d_out, X_out, hinfo.data(), s);
+    else
+      st = run_sweep(b, ks, T, o, P, Q, d_out, X_out, hinfo.data(), s);
     T = 0;    // skip the persistent solver below
   }
 #define NVD_BT(TT)                                                                          \

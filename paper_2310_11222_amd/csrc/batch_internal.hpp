@@ -77,6 +77,7 @@ struct nvd_batch {
   hipGraphExec_t sw_exec = nullptr;
   std::vector<unsigned char> sw_key;
   bool sw_capture_failed = false;
+  nvd::ColBatch* col = nullptr;        // a batch of small graphs, for one block per pair (column.hip)
 };
 
 static void batch_drop_graph(nvd_batch* b) {
@@ -105,6 +106,7 @@ static inline void batch_free(nvd_batch* b) {
                   b->ch_buf, b->sg_dev, b->spart, b->sstate};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
+  nvd::free_column_batch(b->col);
   if (b->h_err) (void)hipHostFree(b->h_err);
   if (b->h_poll) (void)hipHostFree(b->h_poll);
 }

@@ -24,9 +24,11 @@
 // refinement rules, same edge-difference form of L x); sums have a fixed
 // order, so results repeat bit for bit.
 #include <algorithm>
+#include <atomic>
 #include <cstdlib>
 #include <cstring>
 #include <numeric>
+#include <thread>
 #include <vector>
 
 #include "column_kernel.hpp"
@@ -87,19 +89,18 @@ struct ColPlan {
   int64_t bytes = 0;
 };
 
-// Scratch and result words of a call, kept with the graph (or the batch).
-nvd_status ensure_column_ws(ColWs* w, long stride, int vecs, long cstride, int cols, int64_t* bytes) {
-  const size_t vec = (size_t)stride * vecs * cols, cm = (size_t)cstride * cols;
+// Scratch (`vec` doubles of vectors, then `cm` of component means) and result
+// words of a call, kept with the graph or the batch.
+nvd_status ensure_column_ws(ColWs* w, size_t vec, size_t cm, int cols, int64_t* bytes) {
   if (w->cap_vec < vec || w->cap_cm < cm) {
     (void)hipFree(w->vec);
     w->vec = nullptr;
     if (bytes) *bytes -= (int64_t)(sizeof(double) * (w->cap_vec + w->cap_cm));
     w->cap_vec = w->cap_cm = 0;
-    const size_t v = std::max(vec, w->cap_vec), c = std::max(cm, w->cap_cm);
-    NVD_HIP(hipMalloc((void**)&w->vec, sizeof(double) * (v + c)));
-    w->cap_vec = v;
-    w->cap_cm = c;
-    if (bytes) *bytes += (int64_t)(sizeof(double) * (v + c));
+    NVD_HIP(hipMalloc((void**)&w->vec, sizeof(double) * (vec + cm)));
+    w->cap_vec = vec;
+    w->cap_cm = cm;
+    if (bytes) *bytes += (int64_t)(sizeof(double) * (vec + cm));
   }
   if (w->cap_info < cols) {
     if (w->info) (void)hipHostFree(w->info);
@@ -149,12 +150,24 @@ struct Blob {
 
 }  // namespace
 
-static nvd_status build_column(DevGraph* g) {
+// The host's layout of a graph for the block (see ColGraph).
+struct ColLayout {
+  std::vector<int> perm, soff, src, voff, vown, coff, cnode, ccomp;
+  std::vector<unsigned short> idx;
+  ColGraph d{};                          // its counts
+  // Appends the arrays to a buffer; the pointers of `d` become offsets in it.
+  void put(Blob* bl);
+  size_t o_src = 0;
+};
+
+static void layout_column(const DevGraph* g, ColLayout* lay) {
   const int n = g->n;
   const int* rp = g->h_rp.data();
   const int* ci = g->h_ci.data();
   // positions: nodes by falling degree, ties by node (counting sort)
-  std::vector<int> first(g->max_deg + 2, 0), perm(n), pos(n);
+  std::vector<int> first(g->max_deg + 2, 0), pos(n);
+  std::vector<int>& perm = lay->perm;
+  perm.resize(n);
   for (int i = 0; i < n; ++i) ++first[g->max_deg - (rp[i + 1] - rp[i]) + 1];
   std::partial_sum(first.begin(), first.end(), first.begin());
   for (int i = 0; i < n; ++i) {
@@ -169,12 +182,14 @@ static nvd_status build_column(DevGraph* g) {
   while (nh < n && nh < kColBS && deg(nh) > heavy_at) hnnz += deg(nh++);
   int part = kColPart;
   while (hnnz / part + nh > kColMaxParts) part *= 2;
-  std::vector<int> voff(nh + 1, 0);
+  std::vector<int>& voff = lay->voff;
+  voff.assign(nh + 1, 0);
   for (int e = 0; e < nh; ++e) voff[e + 1] = voff[e] + (deg(e) + part - 1) / part;
   const int nv = voff[nh];
   const int slots = (n + kColBS - 1) / kColBS;
   const int vslots = (nv + kColBS - 1) / kColBS;
-  std::vector<int> vown(std::max(1, vslots * kColBS), 0);
+  std::vector<int>& vown = lay->vown;
+  vown.assign(std::max(1, vslots * kColBS), 0);
   for (int e = 0; e < nh; ++e)
     for (int v = voff[e]; v < voff[e + 1]; ++v) vown[v] = e;
   // the neighbours of a lane's row: first entry, count, own position
@@ -192,7 +207,8 @@ static nvd_status build_column(DevGraph* g) {
     return {lo, std::min(part, rp[perm[e] + 1] - lo), e};
   };
   const int all = slots + vslots;
-  std::vector<int> soff(kColWaves * all + 1, 0);
+  std::vector<int>& soff = lay->soff;
+  soff.assign(kColWaves * all + 1, 0);
   for (int w = 0; w < kColWaves; ++w)
     for (int j = 0; j < all; ++j) {
       int most = 0;
@@ -200,8 +216,10 @@ static nvd_status build_column(DevGraph* g) {
       soff[w * all + j + 1] = soff[w * all + j] + (most + 1) / 2;
     }
   const size_t entries = (size_t)(soff[kColWaves * all] + kColSpare) * 128;
-  std::vector<unsigned short> idx(entries, 0);
-  std::vector<int> src(entries, -1);
+  std::vector<unsigned short>& idx = lay->idx;
+  std::vector<int>& src = lay->src;
+  idx.assign(entries, 0);
+  src.assign(entries, -1);
   for (int w = 0; w < kColWaves; ++w)
     for (int j = 0; j < all; ++j) {
       const int at0 = soff[w * all + j], pairs = soff[w * all + j + 1] - at0;
@@ -216,7 +234,7 @@ static nvd_status build_column(DevGraph* g) {
     }
   // components, largest first
   const int nc = g->n_comp;
-  std::vector<int> coff, cnode, ccomp;
+  std::vector<int>&coff = lay->coff, &cnode = lay->cnode, &ccomp = lay->ccomp;
   int nc_block = 0, nc_wave = 0;
   if (nc > 1) {
     std::vector<int> size(nc, 0), order(nc), rank(nc);
@@ -239,16 +257,54 @@ static nvd_status build_column(DevGraph* g) {
       cnode[at[c]++] = e;
     }
   }
+  ColGraph& d = lay->d;
+  d.n = n;
+  d.nh = nh;
+  d.nc = nc;
+  d.slots = slots;
+  d.vslots = vslots;
+  d.nv = nv;
+  d.nc_block = nc_block;
+  d.nc_wave = std::max(nc_wave, nc_block);
+}
+
+void ColLayout::put(Blob* bl) {
+  auto at = [&](const auto& v) {
+    return bl->put(v.data(), sizeof(v[0]) * v.size());
+  };
+  // (offsets for now: `place` turns them into pointers)
+  d.perm = reinterpret_cast<const int*>(at(perm));
+  d.soff = reinterpret_cast<const int*>(at(soff));
+  d.idx = reinterpret_cast<const unsigned*>(at(idx));
+  o_src = at(src);
+  d.voff = reinterpret_cast<const int*>(at(voff));
+  d.vown = reinterpret_cast<const int*>(at(vown));
+  d.coff = reinterpret_cast<const int*>(at(coff));
+  d.cnode = reinterpret_cast<const int*>(at(cnode));
+  d.ccomp = reinterpret_cast<const int*>(at(ccomp));
+}
+
+// Offsets of ColLayout::put as pointers into the device copy.
+static ColGraph place(ColGraph d, const unsigned char* base) {
+  auto fix = [&](auto& p) {
+    p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(base + reinterpret_cast<size_t>(p));
+  };
+  fix(d.perm);
+  fix(d.soff);
+  fix(d.idx);
+  fix(d.voff);
+  fix(d.vown);
+  fix(d.coff);
+  fix(d.cnode);
+  fix(d.ccomp);
+  return d;
+}
+
+static nvd_status build_column(DevGraph* g) {
+  ColLayout lay;
+  layout_column(g, &lay);
   Blob bl;
-  const size_t o_perm = bl.put(perm.data(), sizeof(int) * n);
-  const size_t o_soff = bl.put(soff.data(), sizeof(int) * soff.size());
-  const size_t o_idx = bl.put(idx.data(), sizeof(unsigned short) * entries);
-  const size_t o_src = bl.put(src.data(), sizeof(int) * src.size());
-  const size_t o_voff = bl.put(voff.data(), sizeof(int) * (nh + 1));
-  const size_t o_vown = bl.put(vown.data(), sizeof(int) * vown.size());
-  const size_t o_coff = bl.put(coff.data(), sizeof(int) * coff.size());
-  const size_t o_cnode = bl.put(cnode.data(), sizeof(int) * cnode.size());
-  const size_t o_ccomp = bl.put(ccomp.data(), sizeof(int) * ccomp.size());
+  lay.put(&bl);
   ColPlan* cp = new ColPlan();
   hipError_t e = hipMalloc((void**)&cp->blob, bl.h.size());
   if (e == hipSuccess) e = hipMemcpy(cp->blob, bl.h.data(), bl.h.size(), hipMemcpyHostToDevice);
@@ -259,27 +315,32 @@ static nvd_status build_column(DevGraph* g) {
     return e == hipErrorOutOfMemory ? NVD_E_NOMEM : NVD_E_DEVICE;
   }
   cp->bytes = (int64_t)bl.h.size();
-  auto ip = [&](size_t o) { return reinterpret_cast<const int*>(cp->blob + o); };
-  cp->src = ip(o_src);
-  cp->entries = (int)entries;
-  cp->d.n = n;
-  cp->d.nh = nh;
-  cp->d.nc = nc;
-  cp->d.slots = slots;
-  cp->d.vslots = vslots;
-  cp->d.nv = nv;
-  cp->d.nc_block = nc_block;
-  cp->d.nc_wave = std::max(nc_wave, nc_block);
-  cp->d.perm = ip(o_perm);
-  cp->d.soff = ip(o_soff);
-  cp->d.idx = reinterpret_cast<const unsigned*>(cp->blob + o_idx);
-  cp->d.voff = ip(o_voff);
-  cp->d.vown = ip(o_vown);
-  cp->d.coff = ip(o_coff);
-  cp->d.cnode = ip(o_cnode);
-  cp->d.ccomp = ip(o_ccomp);
+  cp->d = place(lay.d, cp->blob);
+  cp->src = reinterpret_cast<const int*>(cp->blob + lay.o_src);
+  cp->entries = (int)lay.src.size();
   g->col = cp;
   g->bytes += cp->bytes;
+  return NVD_OK;
+}
+
+// Doubles that the weights and 1 / degrees of a layout take (FP64 and FP32).
+static size_t weight_doubles(size_t entries, int npad) { return (12 * (entries + (size_t)npad) + 7) / 8; }
+
+// Where they go: at `at` (weight_doubles of it), and filled from the graph's.
+static nvd_status put_weights(const DevGraph* g, ColGraph* d, size_t entries, const int* src, double* at,
+                              hipStream_t s) {
+  const int npad = d->slots * kColBS;
+  const size_t sw = g->weighted ? entries : 0;
+  float* f = reinterpret_cast<float*>(at + sw + npad);
+  d->w64 = g->weighted ? reinterpret_cast<const double2*>(at) : nullptr;
+  d->inv64 = at + sw;
+  d->w32 = g->weighted ? reinterpret_cast<const float2*>(f) : nullptr;
+  d->inv32 = f + sw;
+  const int work = std::max((int)entries, npad);
+  k_column_weights<<<std::min(1024, (work + 255) / 256), 256, 0, s>>>(
+      (int)entries, src, g->n, npad, d->perm, g->weighted ? g->w64 : nullptr, g->invd64, g->invd32, at, f,
+      at + sw, f + sw);
+  NVD_HIP(hipGetLastError());
   return NVD_OK;
 }
 
@@ -288,28 +349,16 @@ static nvd_status ensure_column(DevGraph* g, hipStream_t s) {
   if (!g->col) NVD_TRY(build_column(g));
   ColPlan* cp = g->col;
   if (!cp->stale) return NVD_OK;
-  const int n = g->n;
   if (!cp->weights || cp->weighted != g->weighted) {
     (void)hipFree(cp->weights);
     cp->weights = nullptr;
-    const size_t sw = g->weighted ? (size_t)cp->entries : 0, n2 = (size_t)cp->d.slots * kColBS;
-    NVD_HIP(hipMalloc((void**)&cp->weights, 12 * (sw + n2)));
+    const size_t want = weight_doubles(g->weighted ? cp->entries : 0, cp->d.slots * kColBS);
+    NVD_HIP(hipMalloc((void**)&cp->weights, sizeof(double) * want));
     cp->weighted = g->weighted;
-    cp->bytes += (int64_t)(12 * (sw + n2));
-    g->bytes += (int64_t)(12 * (sw + n2));
-    double* d = cp->weights;
-    float* f = reinterpret_cast<float*>(d + sw + n2);
-    cp->d.w64 = g->weighted ? reinterpret_cast<const double2*>(d) : nullptr;
-    cp->d.inv64 = d + sw;
-    cp->d.w32 = g->weighted ? reinterpret_cast<const float2*>(f) : nullptr;
-    cp->d.inv32 = f + sw;
+    cp->bytes += (int64_t)(sizeof(double) * want);
+    g->bytes += (int64_t)(sizeof(double) * want);
   }
-  const int npad = cp->d.slots * kColBS;
-  const int work = std::max(cp->entries, npad);
-  k_column_weights<<<std::min(1024, (work + 255) / 256), 256, 0, s>>>(
-      cp->entries, cp->src, n, npad, cp->d.perm, g->weighted ? g->w64 : nullptr, g->invd64, g->invd32,
-      (double*)cp->d.w64, (float*)cp->d.w32, (double*)cp->d.inv64, (float*)cp->d.inv32);
-  NVD_HIP(hipGetLastError());
+  NVD_TRY(put_weights(g, &cp->d, cp->entries, cp->src, cp->weights, s));
   cp->stale = false;
   return NVD_OK;
 }
@@ -445,7 +494,7 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
   const long cstride = g->n_comp > 1 ? g->n_comp : 0;
   const int chunk = std::min(k, kColChunk);
   const int vecs = sp.tree ? 8 : 4;
-  NVD_TRY(ensure_column_ws(&g->col_ws, stride, vecs, cstride, chunk, &g->bytes));
+  NVD_TRY(ensure_column_ws(&g->col_ws, (size_t)stride * vecs * chunk, (size_t)cstride * chunk, chunk, &g->bytes));
   ColArgs a{};
   a.vecs = vecs;
   if (sp.tree) NVD_TRY(ensure_column_pre(g, sp.achol, cp->d.perm, cp->d.slots, &a.pre));
@@ -502,6 +551,185 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
     for (int j = 0; any && j < cols; ++j)
       if (left(j)) NVD_TRY(finish_multi_kernel(g, c0 + j, j, P, Q, ld, sp, a, &info[c0 + j], s));
   }
+  return NVD_OK;
+}
+
+// ---------------------------------------------------------------------------
+// batches of small graphs
+// ---------------------------------------------------------------------------
+// Every (graph, pair) is a block, the longest first.  Taken where every graph
+// of the batch fits (ms a call, block / sweep: 12 graphs of up to 6,600 nodes,
+// 7 pairs mixed 0.65 / 4.8; 47 up to 9,900, 5 pairs 1.2 / 6.4; 64 up to 17,000,
+// 16 pairs 4.5 / 13.0).
+// Beside a sweep over larger graphs the blocks took from it what they saved
+// (62 graphs up to 37,000 nodes, 14 pairs: 18.6 / 18.0): such batches are
+// swept whole.  Beyond 24 slots a block's iteration takes longer than the
+// sweep's (n = 32,000, weighted: 32 us / 26).
+constexpr int kColBatchNodes = 24 * kColBS;
+
+struct ColBatch {
+  std::vector<ColGraph> h;         // the graphs' layouts (on the host)
+  std::vector<int> weighted;
+  int most = 0;                    // nodes of the largest
+  unsigned char* blob = nullptr;
+  double* weights = nullptr;
+  ColGraph* dev = nullptr;
+  // jobs of the last call, kept while the pair counts stay the same
+  std::vector<int> ks;
+  std::vector<ColJob> jobs[2];     // [unit, weighted]
+  ColJob* jobs_dev = nullptr;
+  size_t cap_jobs = 0, work = 0;
+  ColWs ws;
+};
+
+void free_column_batch(ColBatch* c) {
+  if (!c) return;
+  void* ptrs[] = {c->blob, c->weights, c->dev, c->jobs_dev};
+  for (void* p : ptrs) (void)hipFree(p);
+  free_column_ws(&c->ws);
+  delete c;
+}
+
+nvd_status make_column_batch(int G, const DevGraph* const* graphs, hipStream_t s, ColBatch** out,
+                             int64_t* bytes) {
+  *out = nullptr;
+  int most = 0;
+  for (int i = 0; i < G; ++i) most = std::max(most, graphs[i]->n_comp == 1 ? graphs[i]->n : INT32_MAX);
+  if (most > kColBatchNodes) return NVD_OK;
+  std::vector<ColLayout> lay(G);
+  const int nt = (int)std::max(1u, std::min(std::min(16u, std::thread::hardware_concurrency()), (unsigned)G));
+  std::atomic<int> next{0};
+  auto run = [&]() {
+    for (int i = next++; i < G; i = next++) layout_column(graphs[i], &lay[i]);
+  };
+  std::vector<std::thread> th;
+  for (int t = 1; t < nt; ++t) th.emplace_back(run);
+  run();
+  for (auto& x : th) x.join();
+  Blob bl;
+  size_t nw = 0;
+  for (int i = 0; i < G; ++i) {
+    lay[i].put(&bl);
+    nw += weight_doubles(graphs[i]->weighted ? lay[i].src.size() : 0, lay[i].d.slots * kColBS);
+  }
+  ColBatch* c = new ColBatch();
+  c->most = most;
+  nvd_status st = NVD_OK;
+  hipError_t e = hipMalloc((void**)&c->blob, bl.h.size());
+  if (e == hipSuccess) e = hipMalloc((void**)&c->weights, sizeof(double) * nw);
+  if (e == hipSuccess) e = hipMalloc((void**)&c->dev, sizeof(ColGraph) * G);
+  if (e == hipSuccess) e = hipMemcpyAsync(c->blob, bl.h.data(), bl.h.size(), hipMemcpyHostToDevice, s);
+  size_t at = 0;
+  for (int i = 0; e == hipSuccess && st == NVD_OK && i < G; ++i) {
+    const DevGraph* g = graphs[i];
+    ColGraph d = place(lay[i].d, c->blob);
+    st = put_weights(g, &d, lay[i].src.size(), reinterpret_cast<const int*>(c->blob + lay[i].o_src),
+                     c->weights + at, s);
+    at += weight_doubles(g->weighted ? lay[i].src.size() : 0, d.slots * kColBS);
+    c->h.push_back(d);
+    c->weighted.push_back(g->weighted ? 1 : 0);
+  }
+  if (e == hipSuccess && st == NVD_OK)
+    e = hipMemcpyAsync(c->dev, c->h.data(), sizeof(ColGraph) * G, hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess && st == NVD_OK) {
+    set_error(std::string("nvd_batch_create: ") + hipGetErrorString(e));
+    st = e == hipErrorOutOfMemory ? NVD_E_NOMEM : NVD_E_DEVICE;
+  }
+  if (st != NVD_OK) {
+    free_column_batch(c);
+    return st;
+  }
+  *bytes += (int64_t)(bl.h.size() + sizeof(double) * nw + sizeof(ColGraph) * G);
+  *out = c;
+  return NVD_OK;
+}
+
+bool use_column_batch(const ColBatch* c, bool mixed) {
+  const char* e = std::getenv("NVD_COLUMN");
+  return !(e && e[0] == '0') && column_fits(c->most, mixed);
+}
+
+nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd_opts& o, const double* P,
+                              const double* Q, double* d_out, double* X, nvd_pair_info* info, hipStream_t s) {
+  const int G = (int)c->h.size();
+  int K = 0;
+  for (const int k : ks) K += k;
+  if (c->ks != ks) {
+    // (every call waits for its launches: the jobs may change)
+    c->ks.clear();
+    std::vector<long> voff(G);
+    std::vector<int> out(G), order(G);
+    long v = 0;
+    int first = 0;
+    for (int g = 0; g < G; ++g) {
+      voff[g] = v;
+      out[g] = first;
+      first += ks[g];
+      v += (long)c->h[g].n * ks[g];
+    }
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return c->h[x].n > c->h[y].n; });
+    c->work = 0;
+    for (auto& j : c->jobs) j.clear();
+    for (const int g : order)
+      for (int j = 0; j < ks[g]; ++j) {
+        ColJob job{};
+        job.graph = g;
+        job.out = out[g] + j;
+        job.voff = job.xoff = voff[g] + j;
+        job.ld = job.ldx = ks[g];
+        job.work = (long)c->work;
+        c->work += (size_t)4 * c->h[g].slots * kColBS;
+        c->jobs[c->weighted[g]].push_back(job);
+      }
+    std::vector<ColJob> all(c->jobs[0]);
+    all.insert(all.end(), c->jobs[1].begin(), c->jobs[1].end());
+    if (c->cap_jobs < all.size()) {
+      (void)hipFree(c->jobs_dev);
+      c->jobs_dev = nullptr;
+      c->cap_jobs = 0;
+      NVD_HIP(hipMalloc((void**)&c->jobs_dev, sizeof(ColJob) * all.size()));
+      c->cap_jobs = all.size();
+    }
+    NVD_HIP(hipMemcpy(c->jobs_dev, all.data(), sizeof(ColJob) * all.size(), hipMemcpyHostToDevice));
+    c->ks = ks;
+  }
+  NVD_TRY(ensure_column_ws(&c->ws, c->work, 0, K, nullptr));
+  ColArgs a{};
+  a.graphs = c->dev;
+  a.vecs = 4;
+  a.P = P;
+  a.Q = Q;
+  a.rtol2 = o.rtol * o.rtol;
+  a.irtol2 = o.inner_rtol * o.inner_rtol;
+  a.stall_ratio2 = kStallRatio2;
+  a.max_iter = o.max_iter;
+  a.max_refine = o.max_refine;
+  a.out_dsq = 0;
+  a.handover = 0;                  // batches leave a pair that FP32 cannot finish as it is
+  a.d_out = d_out;
+  a.X = X;
+  a.info = c->ws.info;
+  a.vec = c->ws.vec;
+  size_t first = 0;
+  for (int w = 0; w < 2; ++w) {
+    const std::vector<ColJob>& jobs = c->jobs[w];
+    if (jobs.empty()) continue;
+    int slots = 0, nv = 0;
+    for (const ColJob& j : jobs) {
+      slots = std::max(slots, c->h[j.graph].slots);
+      nv = std::max(nv, c->h[j.graph].nv);
+    }
+    const size_t fit = ((size_t)kColLds - parts_bytes(nv)) / (sizeof(double) * kColBS);
+    a.lds_n = (int)std::min<size_t>(slots, fit) * kColBS;
+    a.jobs = c->jobs_dev + first;
+    first += jobs.size();
+    NVD_TRY(launch_column_jacobi(a, o.precision == NVD_MIXED, w == 0, slots * kColBS, (int)jobs.size(),
+                                 parts_bytes(nv) + sizeof(double) * (size_t)a.lds_n, s));
+  }
+  NVD_HIP(hipStreamSynchronize(s));
+  std::copy(c->ws.info, c->ws.info + K, info);
   return NVD_OK;
 }
 

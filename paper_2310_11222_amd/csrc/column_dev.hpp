@@ -109,6 +109,7 @@ struct ColJob {
   long ld;
   long xoff;     // X[xoff + i * ldx]
   long ldx;
+  long work;     // its vectors in vec
 };
 
 struct ColArgs {

@@ -40,10 +40,11 @@ __global__ __launch_bounds__(kColBS) void k_column(ColArgs a) {
   const int n = g.n;
   double* const hq = lds;                       // [nv], ahead of the vector
   double* const buf = lds + ((g.nv + 1) & ~1);
-  double* const b = a.vec + (size_t)blockIdx.x * a.vecs * a.stride;
-  double* const x = b + a.stride;
-  double* const r = x + a.stride;
-  double* const work = r + 2 * a.stride;       // scratch of an explicit preconditioner
+  const long stride = a.jobs ? (long)g.slots * kColBS : a.stride;
+  double* const b = a.vec + (a.jobs ? job.work : (long)blockIdx.x * a.vecs * stride);
+  double* const x = b + stride;
+  double* const r = x + stride;
+  double* const work = r + 2 * stride;       // scratch of an explicit preconditioner
   double* const cm = a.cmean + (size_t)blockIdx.x * a.cstride;
 
   int status = kStOk, iters = 0, refine = 0, fb = 0;
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(kColBS) void k_column(ColArgs a) {
   bool fp64_done = false;
 
   if constexpr (MIXED) {
-    float* const x32 = reinterpret_cast<float*>(r + a.stride);
+    float* const x32 = reinterpret_cast<float*>(r + stride);
     float* const p32 = reinterpret_cast<float*>(buf);
     int stall = 0;
     double orr = bb;
@@ -164,7 +165,7 @@ __global__ __launch_bounds__(kColBS) void k_column(ColArgs a) {
       const double it2 = need2 > a.irtol2 ? (need2 < 0.25 ? need2 : 0.25) : a.irtol2;
       ColRun run;
       if constexpr (PRE)
-        run = col_cg_pre<float, UNIT, EPT>(g, a.pre, p32, buf, hq, f, x32, work, a.stride, cm, s3[2], it2,
+        run = col_cg_pre<float, UNIT, EPT>(g, a.pre, p32, buf, hq, f, x32, work, stride, cm, s3[2], it2,
                                            a.max_iter,
                                            S, turn);
       else
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(kColBS) void k_column(ColArgs a) {
       if (uniform(rho > 0.0)) {
         ColRun run;
         if constexpr (PRE)
-          run = col_cg_pre<double, UNIT, EPT>(g, a.pre, buf, buf, hq, rv, x, work, a.stride, cm, bb, a.rtol2,
+          run = col_cg_pre<double, UNIT, EPT>(g, a.pre, buf, buf, hq, rv, x, work, stride, cm, bb, a.rtol2,
                                               a.max_iter,
                                               S, turn);
         else

@@ -241,6 +241,15 @@ bool use_column(const DevGraph* g, int k, const SolveParams& sp);
 nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, int64_t ld,
                         const SolveParams& sp, double* d_out, double* X, int64_t ldx,
                         nvd_pair_info* info, hipStream_t s, double* B = nullptr, double* R = nullptr);
+// A batch of small graphs in the same way (column.hip); *out is null where it
+// has larger ones.
+struct ColBatch;
+nvd_status make_column_batch(int G, const DevGraph* const* graphs, hipStream_t s, ColBatch** out,
+                             int64_t* bytes);
+bool use_column_batch(const ColBatch* c, bool mixed);
+nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd_opts& o, const double* P,
+                              const double* Q, double* d_out, double* X, nvd_pair_info* info, hipStream_t s);
+void free_column_batch(ColBatch* c);
 void column_weights_changed(DevGraph* g);
 void free_column(DevGraph* g);
 void free_column_ws(ColWs* w);

@@ -151,3 +151,39 @@ def test_column_preconditioners(monkeypatch, precision, precond, model, n, k, we
     monkeypatch.setenv("NVD_COLUMN", "1")
     d3, X3, _ = dg.distances(P, Q, precision=precision, rtol=rtol, return_x=True, precond=precond)
     assert np.array_equal(d3.cpu().numpy(), d1) and np.array_equal(X3.cpu().numpy(), X1)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("sizes,ks", [((2, 64, 1025, 5000, 16384), (1, 3, 64, 2, 5)),
+                                      ((17408, 700, 24576), (2, 1, 3)), ((300,) * 40, (7,) * 40)])
+def test_column_batch(monkeypatch, precision, sizes, ks):
+    """Batches of small graphs, unit and weighted together: a block per
+    (graph, pair), against the sweep and against every graph on its own; a
+    second call with other pair counts, the first again."""
+    import torch
+    import paper_2310_11222_amd as nvd
+    rng = np.random.default_rng(len(sizes))
+    graphs = [star_graph(1) if n == 2 else _graph("ba" if i % 2 else "ws", n, rng, i % 3 != 1)
+              for i, n in enumerate(sizes)]
+    Ps, Qs = zip(*[_pairs(g.n, k, rng) for g, k in zip(graphs, ks)])
+    say("column batch", precision, sizes, ks)
+    dgs = [dev_graph(g) for g in graphs]
+    batch = nvd.Batch(dgs)
+    rtol = 1e-10 if precision == "fp64" else 1e-8
+    d1, X1, i1 = batch.distances(Ps, Qs, precision=precision, rtol=rtol, return_x=True)
+    assert all(i["status"] == 0 and i["rel_res"] <= rtol * 1.01 for i in i1), i1
+    d3, _, _ = batch.distances([p[:, :1] for p in Ps], [q[:, :1] for q in Qs], precision=precision, rtol=rtol)
+    d4, X4, _ = batch.distances(Ps, Qs, precision=precision, rtol=rtol, return_x=True)
+    assert torch.equal(d1, d4) and torch.equal(X1, X4)
+    first = np.cumsum([0] + list(ks))[:-1]
+    assert rel_err(d3.cpu().numpy(), d1.cpu().numpy()[first]).max() <= 1e-14
+    monkeypatch.setenv("NVD_COLUMN", "0")
+    d2, X2, _ = batch.distances(Ps, Qs, precision=precision, rtol=rtol, return_x=True)
+    assert rel_err(d1.cpu().numpy(), d2.cpu().numpy()).max() <= TOL[precision]
+    tol = (1e-7 if precision == "fp64" else 1e-5) * float(X2.abs().max())
+    np.testing.assert_allclose(X1.cpu().numpy(), X2.cpu().numpy(), rtol=0, atol=tol)
+    at = 0
+    for g, dg, P, Q, k in zip(graphs, dgs, Ps, Qs, ks):
+        one, _, _ = dg.distances(P, Q, precision="fp64")
+        assert rel_err(d1.cpu().numpy()[at:at + k], one.cpu().numpy()).max() <= TOL[precision]
+        at += k

@@ -271,6 +271,18 @@ nvd_status nvd_graph_query(const nvd_graph* h, int32_t* labels, double* degree) 
   return NVD_OK;
 }
 
+// Whether `left` columns go into one pass L = 2 T lanes wide rather than a pass
+// for the widest power of two and others for the rest.  One lane an element
+// is no loss up to 16 lanes.  Wider, two passes with 16-byte vectors are as
+// fast or faster (us, one / two passes, FP32 on a 3 10^5-node power-law graph:
+// 24 columns 135 / 108, 48 columns 245 / 126), three are not (28 columns 139 /
+// 175).  A small graph's passes cost their launches alone (3,000 nodes, 48
+// columns: 16 / 28).
+static bool one_ragged_pass(const DevGraph* g, int left, int L) {
+  if ((long)g->nnz * L <= 2L << 20) return true;
+  return L <= 16 || (L == 32 && __builtin_popcount(left) >= 3);
+}
+
 nvd_status nvd_laplacian_apply(nvd_graph* h, int32_t dtype, int32_t k, const void* X,
                                int64_t ldx, void* Y, int64_t ldy, void* stream) {
   set_error("");
@@ -297,6 +309,12 @@ nvd_status nvd_laplacian_apply(nvd_graph* h, int32_t dtype, int32_t k, const voi
     sc.y = static_cast<char*>(Y) + c0 * es;
     sc.ldy = ldy;
     sc.epi = EPI_PLAIN;
+    const int left = k - c0;
+    if (left > T && left < 64 && one_ragged_pass(g, left, 2 * T)) {
+      sc.T = 2 * T;
+      NVD_TRY(launch_ragged(sc, left, as_stream(stream)));
+      return NVD_OK;
+    }
     NVD_TRY(launch_apply(sc, g->ws->red, as_stream(stream)));
     c0 += T;
   }

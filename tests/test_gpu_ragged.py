@@ -74,3 +74,39 @@ def test_ragged_matrix(monkeypatch, n, m, column):
     D, _, info = dg.pairwise(P, precision="mixed", rtol=1e-9, inner_rtol=1e-2)
     assert rel_err(D.cpu().numpy()[iu], ref).max() <= 1e-8
     assert all(i["flags"] & 1 and i["status"] == 0 for i in info)
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("model,n,k,pad", [("ba", 500, 3, 0), ("ba", 500, 63, 2), ("star", 9000, 5, 1),
+                                           ("ba", 60000, 7, 0), ("ba", 60000, 13, 3), ("ba", 60000, 28, 0),
+                                           ("ba", 60000, 33, 1), ("er", 20000, 100, 0)])
+def test_ragged_apply(model, n, k, pad, weighted):
+    """Y = L X on k columns of wider arrays whose other entries are NaN (X)
+    and have to stay as they are (Y): rows within a lane group, long rows in
+    one and in several segments, isolated nodes."""
+    import torch
+    from nvdgen.graphs import star_graph
+    rng = np.random.default_rng(n + k)
+    g = {"ba": lambda: barabasi_albert(n, 3, rng), "er": lambda: erdos_renyi(n, n, rng),
+         "star": lambda: star_graph(n - 1)}[model]()
+    if weighted:
+        g = g.with_weights(rng.uniform(0.5, 2.0, g.num_edges))
+    say("ragged apply", model, n, k, pad, weighted)
+    dg = dev_graph(g)
+    X = rng.standard_normal((n, k))
+    rows = np.repeat(np.arange(n), np.diff(g.row_ptr))
+    w = np.ones(g.nnz) if g.w is None else g.w
+    for dtype, eps in ((torch.float64, 2.0 ** -53), (torch.float32, 2.0 ** -24)):
+        Xd = _wide(X, pad, pad).to(dtype)
+        Y = torch.full((n, k + 2 * pad), 7.0, dtype=dtype, device="cuda")
+        dg.laplacian_apply(Xd[:, :k] if pad == 0 else Xd, out=Y[:, pad:pad + k])
+        Xr = Xd.double().cpu().numpy()
+        diff = w[:, None] * (Xr[rows] - Xr[g.col_idx])
+        ref, size = np.zeros((n, k)), np.zeros((n, k))
+        np.add.at(ref, rows, diff)
+        np.add.at(size, rows, np.abs(diff) + w[:, None] * np.abs(Xr[rows]))
+        # every term is rounded a few times and a row's sum once per entry
+        deg = np.diff(g.row_ptr)[:, None]
+        err = np.abs(Y[:, pad:pad + k].double().cpu().numpy() - ref)
+        assert (err <= (deg + 8) * eps * size + 1e-300).all()
+        assert bool((Y[:, :pad] == 7.0).all()) and bool((Y[:, pad + k:] == 7.0).all())

@@ -13,38 +13,6 @@ nvd_status graph_create(int64_t n, int64_t nnz, const int64_t* row_ptr, const in
                         const double* w, hipStream_t s, DevGraph** out);
 nvd_status graph_destroy(DevGraph* g);
 
-// Edge-weight adjoint: one thread per (row, column) pair of a tile is too
-// fine for short rows, so a group of T lanes takes one row and walks its
-// neighbours; each CSR entry's value is the sum over the tile's columns,
-// reduced across the T lanes by shuffles.
-template <int T>
-__global__ __launch_bounds__(kBS) void k_grad_w(int n, const int* rp, const int* ci,
-                                                const int* in_pos, const double* X, long ldx,
-                                                const double* gs, double* gw, int accumulate) {
-  constexpr int RW = 64 / T;
-  const int t = threadIdx.x;
-  const int lane = t & 63;
-  const int c = lane % T;
-  const int g = lane / T;
-  const double gc = gs[c];
-  const long rows_per_step = (long)gridDim.x * (kBS / 64) * RW;
-  for (long row = (long)blockIdx.x * (kBS / 64) * RW + (t >> 6) * RW + g; row < n;
-       row += rows_per_step) {
-    const double xi = X[row * ldx + c];
-    const int lo = rp[row], hi = rp[row + 1];
-    for (int e = lo; e < hi; ++e) {
-      const double df = xi - X[(long)ci[e] * ldx + c];
-      double v = -0.5 * gc * df * df;
-#pragma unroll
-      for (int off = 1; off < T; off <<= 1) v += __shfl_xor(v, off, 64);
-      if (c == 0) {
-        const long pos = in_pos ? in_pos[e] : e;
-        gw[pos] = accumulate ? gw[pos] + v : v;
-      }
-    }
-  }
-}
-
 // Adjoint with respect to the node vectors: d(sum_j g_j d_j^2)/dP = 2 X
 // diag(g) and d/dQ its negative (x_j = L^+ delta_j is the saved solution;
 // L^+ is symmetric, so no second solve is needed).  Either output may be null.
@@ -73,29 +41,6 @@ __global__ void k_grad_scale_d(int k, const double* __restrict__ g, const double
   gs[j] = dj > 0.0 ? g[j] / (2.0 * dj) : 0.0;
 }
 
-// New edge weights from a device array in the input CSR order, checked
-// before anything is replaced: every value finite and > 0 and equal to its
-// mirror entry's.  flag bit 1: bad value, bit 2: asymmetric.
-__global__ void k_check_weights(int n, const int* rp, const int* ci, const int* in_pos,
-                                const double* w_in, int* flag) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  for (int e = rp[i]; e < rp[i + 1]; ++e) {
-    const double v = w_in[in_pos ? in_pos[e] : e];
-    if (!(v > 0.0) || !isfinite(v)) atomicOr(flag, 1);
-    const int j = ci[e];
-    int lo = rp[j], hi = rp[j + 1];
-    while (lo < hi) {                  // mirror entry (j, i)
-      const int mid = (lo + hi) >> 1;
-      if (ci[mid] < i)
-        lo = mid + 1;
-      else
-        hi = mid;
-    }
-    if (lo >= rp[j + 1] || ci[lo] != i || w_in[in_pos ? in_pos[lo] : lo] != v) atomicOr(flag, 2);
-  }
-}
-
 // Commit checked weights: every internal entry takes its input value.
 __global__ void k_set_weights(int nnz, const int* in_pos, const double* w_in, double* w64,
                               float* w32) {
@@ -104,19 +49,6 @@ __global__ void k_set_weights(int nnz, const int* in_pos, const double* w_in, do
   const double v = w_in[in_pos ? in_pos[e] : e];
   w64[e] = v;
   w32[e] = (float)v;
-}
-
-__global__ void k_degree_refresh(int n, const int* rp, const double* w64, double* deg64,
-                                 float* deg32, double* invd64, float* invd32) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double d = 0.0;
-  for (int e = rp[i]; e < rp[i + 1]; ++e) d += w64[e];
-  deg64[i] = d;
-  deg32[i] = (float)d;
-  const double inv = d > 0.0 ? 1.0 / d : 0.0;
-  invd64[i] = inv;
-  invd32[i] = (float)inv;
 }
 
 // Solver options: precision, tolerances, limits and tile.
@@ -440,22 +372,8 @@ nvd_status nvd_graph_set_weights(nvd_graph* h, const double* w, void* stream) {
   DevGraph* g = h->g;
   hipStream_t s = as_stream(stream);
   // 1. check the new values; the graph is left untouched if they are rejected
-  int* flag = nullptr;
-  NVD_HIP(hipMalloc((void**)&flag, sizeof(int)));
   int hflag = 0;
-  hipError_t e = hipMemcpyAsync(flag, &hflag, sizeof(int), hipMemcpyHostToDevice, s);
-  const int grid = (g->n + 255) / 256;
-  if (e == hipSuccess) {
-    k_check_weights<<<grid, 256, 0, s>>>(g->n, g->rp, g->ci, g->in_pos, w, flag);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) e = hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)hipFree(flag);
-  if (e != hipSuccess) {
-    set_error(std::string("nvd_graph_set_weights: ") + hipGetErrorString(e));
-    return NVD_E_DEVICE;
-  }
+  NVD_TRY(check_weights(g, w, &hflag, s));
   if (hflag) {
     set_error(std::string("nvd_graph_set_weights: ") +
               ((hflag & 1) ? "a weight is not a finite positive number" : "") +
@@ -471,9 +389,8 @@ nvd_status nvd_graph_set_weights(nvd_graph* h, const double* w, void* stream) {
   }
   if (g->nnz > 0)
     k_set_weights<<<(g->nnz + 255) / 256, 256, 0, s>>>(g->nnz, g->in_pos, w, g->w64, g->w32);
-  k_degree_refresh<<<grid, 256, 0, s>>>(g->n, g->rp, g->w64, g->deg64, g->deg32, g->invd64,
-                                        g->invd32);
-  e = hipGetLastError();
+  launch_row_degree(g->n, g->rp, g->w64, nullptr, g->deg64, g->deg32, g->invd64, g->invd32, s);
+  hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) {
     set_error(std::string("nvd_graph_set_weights: ") + hipGetErrorString(e));
@@ -481,7 +398,7 @@ nvd_status nvd_graph_set_weights(nvd_graph* h, const double* w, void* stream) {
   }
   g->weighted = true;
   // the spanning forest (tree preconditioner) holds 1/w of its edges and is
-  // built from the host copy of the weights: refresh the copy, drop the forest
+  // built from the host copy of the weights: drop the forest
   free_tree(g->tree);
   g->tree = nullptr;
   if (g->achol) g->bytes -= g->achol->bytes;
@@ -491,12 +408,7 @@ nvd_status nvd_graph_set_weights(nvd_graph* h, const double* w, void* stream) {
   // the one-block-per-column solver's layout (refreshed on its next use)
   free_slices(g);
   column_weights_changed(g);
-  g->h_w.resize(std::max(g->nnz, 1));
-  if (hipMemcpy(g->h_w.data(), g->w64, sizeof(double) * g->nnz, hipMemcpyDeviceToHost) != hipSuccess) {
-    set_error("nvd_graph_set_weights: copying the weights back failed");
-    return NVD_E_DEVICE;
-  }
-  g->h_w.resize(g->nnz);
+  g->h_w_stale = true;   // (copied back when a forest, factor or slices are built)
   return NVD_OK;
 }
 
@@ -538,24 +450,7 @@ nvd_status nvd_grad_weights(nvd_graph* h, int32_t k, const double* X, int64_t ld
   DevGraph* g = h->g;
   hipStream_t s = as_stream(stream);
   if (g->in_pos) NVD_HIP(hipMemsetAsync(grad_w, 0, sizeof(double) * g->nnz_in, s));
-  for (int c0 = 0; c0 < k;) {
-    int T = 64;
-    while (T > k - c0) T >>= 1;
-    const int rows_per_block = (kBS / 64) * (64 / T);
-    long grid = (g->n + rows_per_block - 1) / rows_per_block;
-    grid = std::min<long>(std::max<long>(grid, 1), 8192);
-    const int acc = c0 > 0 ? 1 : 0;
-    switch (T) {
-#define NVD_G(TT) \
-  case TT: k_grad_w<TT><<<grid, kBS, 0, s>>>(g->n, g->rp, g->ci, g->in_pos, X + c0, ldx, gscale + c0, grad_w, acc); break;
-      NVD_G(1) NVD_G(2) NVD_G(4) NVD_G(8) NVD_G(16) NVD_G(32) NVD_G(64)
-#undef NVD_G
-      default: break;
-    }
-    NVD_HIP(hipGetLastError());
-    c0 += T;
-  }
-  return NVD_OK;
+  return grad_entries(g, k, X, ldx, gscale, grad_w, s);
 }
 
 }  // extern "C"

@@ -481,6 +481,7 @@ static int achol_max_rounds() {
 
 nvd_status ensure_achol(DevGraph* g) {
   if (g->achol) return NVD_OK;
+  NVD_TRY(ensure_host_weights(g));
   const int n = g->n;
   HostFactor f = factor_graph(g, achol_max_rounds());
   // forward pull lists: for position q (vertex order[q]) the entries (v, c)

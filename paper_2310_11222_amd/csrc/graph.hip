@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 #include <climits>
+#include <cstdlib>
 #include <cstring>
 #include <numeric>
 #include <thread>
@@ -29,31 +30,10 @@ static nvd_status dalloc(T** p, size_t count, int64_t* bytes) {
   return NVD_OK;
 }
 
-__global__ void k_degree(int n, const int* rp, const double* w64, float* w32, double* deg64,
-                         float* deg32, double* invd64, float* invd32) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int lo = rp[i], hi = rp[i + 1];
-  double d = 0.0;
-  if (w64) {
-    for (int e = lo; e < hi; ++e) {
-      d += w64[e];
-      w32[e] = (float)w64[e];
-    }
-  } else {
-    d = (double)(hi - lo);
-  }
-  deg64[i] = d;
-  deg32[i] = (float)d;
-  const double inv = d > 0.0 ? 1.0 / d : 0.0;
-  invd64[i] = inv;
-  invd32[i] = (float)inv;
-}
-
 static void free_graph_arrays(DevGraph* g) {
   void* ptrs[] = {g->rp,     g->ci,     g->w64,  g->w32,      g->deg64,    g->deg32,
                   g->invd64, g->invd32, g->comp, g->comp_perm, g->comp_off, g->in_pos,
-                  g->long_buf, g->lr.seg_part, g->lr.row_tick};
+                  g->long_buf, g->lr.seg_part, g->lr.row_tick, g->erow};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
 }
@@ -75,6 +55,8 @@ nvd_status free_workspace(Workspace* ws) {
 static size_t padded(size_t n, int tile) { return ((n * (size_t)tile + 15) / 16) * 16; }
 
 nvd_status ensure_workspace(DevGraph* g, int tile, bool need32) {
+  // column slices (2^20 nodes, or by order) are built from the host's weights
+  if (g->h_w_stale && (g->n >= 1 << 20 || std::getenv("NVD_SLICE"))) NVD_TRY(ensure_host_weights(g));
   Workspace* ws = g->ws;
   const size_t need = padded((size_t)g->n, tile);
   if (ws && ws->cap_rows >= need && (!need32 || ws->x32)) return NVD_OK;
@@ -494,8 +476,7 @@ static nvd_status build_graph(int64_t n64, int64_t nnz64, const int64_t* row_ptr
       st = NVD_E_DEVICE;
   }
   if (st == NVD_OK) {
-    k_degree<<<(n + 255) / 256, 256, 0, stream>>>(n, g->rp, g->w64, g->w32, g->deg64, g->deg32,
-                                                  g->invd64, g->invd32);
+    launch_row_degree(n, g->rp, g->w64, g->w32, g->deg64, g->deg32, g->invd64, g->invd32, stream);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) {

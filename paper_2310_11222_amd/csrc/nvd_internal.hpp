@@ -116,6 +116,9 @@ struct DevGraph {
   // host copies kept for queries and batching
   std::vector<int> h_rp, h_ci, h_comp;
   std::vector<double> h_w;     // empty if unit
+  bool h_w_stale = false;      // the weights were replaced since (ensure_host_weights)
+  int* erow = nullptr;         // [nnz] row of each entry, built when first needed (entries.hip)
+  int* mirror = nullptr;       // [nnz] its mirror entry (one allocation with erow)
   int64_t bytes = 0;
   Workspace* ws = nullptr;
   int tuned_tile[2][8] = {};   // [precision][log2 k bucket] -> tile (0 = not tuned)
@@ -252,6 +255,15 @@ bool use_column_batch(const ColBatch* c, bool mixed);
 nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd_opts& o, const double* P,
                               const double* Q, double* d_out, double* X, nvd_pair_info* info, hipStream_t s);
 void free_column_batch(ColBatch* c);
+// By CSR entry (entries.hip): weighted degrees, the check of new weights (bit 1:
+// one not finite and positive, bit 2: one differs from its mirror's), the
+// adjoint for the weights, the host's copy of replaced weights.
+void launch_row_degree(int n, const int* rp, const double* w64, float* w32, double* deg64, float* deg32,
+                       double* invd64, float* invd32, hipStream_t s);
+nvd_status check_weights(DevGraph* g, const double* w, int* bits, hipStream_t s);
+nvd_status grad_entries(DevGraph* g, int k, const double* X, int64_t ldx, const double* gs, double* gw,
+                        hipStream_t s);
+nvd_status ensure_host_weights(DevGraph* g);
 void column_weights_changed(DevGraph* g);
 void free_column(DevGraph* g);
 void free_column_ws(ColWs* w);

@@ -366,7 +366,10 @@ bool use_tree(const DevGraph* g, uint32_t flags) {
 static nvd_status build_aug(DevGraph* g);
 
 nvd_status ensure_tree(DevGraph* g, int T) {
-  if (!g->tree) NVD_TRY(build_tree(g));
+  if (!g->tree) {
+    NVD_TRY(ensure_host_weights(g));
+    NVD_TRY(build_tree(g));
+  }
   TreePre* tp = g->tree;
   if (tp->cap_tile >= T) {
     if (tp->k_aug > 0 && !tp->aug_Y) NVD_TRY(build_aug(g));

@@ -326,8 +326,8 @@ def slice_source_sha():
 
 
 def load_slice_traffic():
-    """Counter bytes per k = 1 FP32 apply by column slices (slice pass plus
-    combine) on the 10^7-node graph, from the committed profile, if taken on
+    """Counter bytes per k = 1 FP32 apply by column slices (gather plus rows
+    kernel) on the 10^7-node graph, from the committed profile, if taken on
     the current source."""
     p = os.path.join(ROOT, "profiles", "k_slice_f32_configmodel1e7_k1_traffic.md")
     if not os.path.exists(p):

@@ -219,15 +219,14 @@ nvd_status nvd_graph_query(const nvd_graph* g, int32_t* labels_host,
  * returns once enqueued.
  * One column (k = 1, here and in the solvers' tiles of one pair) on a graph
  * of at least 2^20 nodes may be applied by column slices: the nodes are cut
- * into slices whose part of X fits one XCD's L2, each XCD gathers from its
- * own slice, and per-row partial sums are added slice by slice in a fixed
- * order.  The first such call of each precision builds the slice structure
+ * into slices whose part of X fits in LDS, the entries' values of X are
+ * gathered there and written in slice order, and the rows are then summed
+ * from them in CSR order.  The first such call of each precision builds the slice structure
  * on the host, times both forms of the apply on its X and keeps the faster
  * for the graph (that call waits for the device and then enqueues).  The
  * structure is kept with the graph while one precision uses it (device
- * memory: about 4 bytes per CSR entry, plus 11 bytes per row and slice with
- * neighbours there; weighted graphs 12 more per entry and 8 per row) and
- * dropped by nvd_graph_set_weights and nvd_graph_destroy.  nvd_distances_noalloc never
+ * memory: about 12 bytes per CSR entry), across nvd_graph_set_weights, and
+ * dropped by nvd_graph_destroy.  nvd_distances_noalloc never
  * uses it.  Environment: NVD_SLICE=0 never uses it, NVD_SLICE=1 uses it at
  * any size without timing. */
 nvd_status nvd_laplacian_apply(nvd_graph* g, int32_t dtype, int32_t k,

@@ -404,11 +404,10 @@ nvd_status nvd_graph_set_weights(nvd_graph* h, const double* w, void* stream) {
   if (g->achol) g->bytes -= g->achol->bytes;
   free_achol(g->achol);
   g->achol = nullptr;
-  // the slices of the one-column apply hold copies of the weights, as does
-  // the one-block-per-column solver's layout (refreshed on its next use)
-  free_slices(g);
+  // the one-block-per-column solver's layout holds copies of the weights
+  // (refreshed on its next use)
   column_weights_changed(g);
-  g->h_w_stale = true;   // (copied back when a forest, factor or slices are built)
+  g->h_w_stale = true;   // (copied back when a forest or factor is built)
   return NVD_OK;
 }
 

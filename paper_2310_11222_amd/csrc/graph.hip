@@ -8,7 +8,6 @@
 #include <algorithm>
 #include <cmath>
 #include <climits>
-#include <cstdlib>
 #include <cstring>
 #include <numeric>
 #include <thread>
@@ -55,8 +54,6 @@ nvd_status free_workspace(Workspace* ws) {
 static size_t padded(size_t n, int tile) { return ((n * (size_t)tile + 15) / 16) * 16; }
 
 nvd_status ensure_workspace(DevGraph* g, int tile, bool need32) {
-  // column slices (2^20 nodes, or by order) are built from the host's weights
-  if (g->h_w_stale && (g->n >= 1 << 20 || std::getenv("NVD_SLICE"))) NVD_TRY(ensure_host_weights(g));
   Workspace* ws = g->ws;
   const size_t need = padded((size_t)g->n, tile);
   if (ws && ws->cap_rows >= need && (!need32 || ws->x32)) return NVD_OK;

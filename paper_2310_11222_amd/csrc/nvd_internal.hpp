@@ -202,7 +202,7 @@ struct SpmmCall {
 };
 nvd_status launch_spmm(const SpmmCall& c, const GridRed& red, hipStream_t s);
 // The apply the solvers and nvd_laplacian_apply use: one column (T = 1) on a
-// large graph by XCD-pinned column slices (slice.hip), else launch_spmm.
+// large graph by column slices in LDS (slice.hip), else launch_spmm.
 nvd_status launch_apply(const SpmmCall& c, const GridRed& red, hipStream_t s);
 // The plain apply on cols < c.T columns, c.T the next power of two (ragged.hip).
 nvd_status launch_ragged(const SpmmCall& c, int cols, hipStream_t s);

@@ -1,42 +1,50 @@
 // Laplacian apply of one right-hand-side column (T = 1) on large graphs, by
-// column slices pinned to XCDs.  Same operator as k_spmm (the paper's
+// column slices held in LDS.  Same operator as k_spmm (the paper's
 // section 3.1 L = D - A):
 //   (L x)_v = sum_u w_vu (x_v - x_u).
 //
 // On a large random graph a one-column apply is bound by its neighbour
-// gathers: each reads 4 or 8 bytes of x and brings a 128-byte line, and the
-// lines of x do not stay in an XCD's 4 MB L2.  Here the columns (nodes) are
-// cut into S = 8m slices of at most kSlNodes nodes, so that one slice of x
-// fits in one XCD's L2, and the rows into chunks of kSlRows rows:
-//  * slice pass: block b works on slice s = 8r + (b mod 8) of a group of
-//    consecutive chunks, with the blocks of round r first.  The hardware
-//    deals consecutive blocks to the 8 XCDs round-robin, so every gather of a
-//    block hits the slice its XCD holds.  For every row of a chunk with
-//    neighbours in the slice (an
-//    "item") it writes one partial sum: in FP64, sum_{u in slice} w_vu (x_v - x_u)
-//    (the edge-difference form); in FP32, sum_{u in slice} w_vu x_u
-//    accumulated in FP64 (x_v is then not read by every slice: at 32 slices
-//    those reads were three quarters of the pass's traffic).  Items of at
-//    most kSlLongItem neighbours take one lane each (4 items per thread,
-//    their neighbour lists contiguous, offsets from a block scan); longer
-//    items take one wave each.
-//  * combine: block per chunk; the partials of each slice are added into an
-//    LDS row accumulator, slice after slice (a row has at most one item per
-//    slice), then (FP32) y_v = d_v x_v - sum in FP64, d_v the FP64 sum of
-//    the row's FP32 weights, rounded once to FP32 -- at least as accurate
-//    as the FP32 edge-difference sum -- and the epilogue of the apply
+// gathers: each reads 4 or 8 bytes of x and brings a 128-byte line from
+// beyond the XCD's 4 MB L2, and even gathers that hit the L2 are bound by its
+// rate of requests (the form that held slices of x in the L2s and wrote one
+// partial sum per row and slice ran at 0.69 ms per FP32 apply, about 1.3 TB/s
+// of its traffic, on the 10^7-node graph below).  LDS answers random reads an
+// order of magnitude faster, so here the gathers are made there and everything
+// else is a stream.  The columns (nodes) are cut into slices of kSlNodes, and
+// the rows into chunks of consecutive rows with at most kSlChunk CSR entries:
+//  * gather: the entries, ordered by (slice, chunk, CSR position), are split
+//    evenly over the blocks.  A block loads the slice of x that its entries
+//    lie in into LDS, reads the entries' 2-byte columns within the slice and
+//    writes the neighbours' values x_u in the same order.  An even split of
+//    the entries needs no balance between slices: a block that crosses into
+//    the next slice loads that one too.
+//  * rows: a block per chunk at a time.  The chunk's values lie in one run per
+//    slice; L lanes take a run, and put its values at their 2-byte positions,
+//    the entries' CSR order within the chunk, in LDS.  Then a thread per
+//    row sums w_vu (x_v - x_u) in FP64 in CSR order, with the weights read
+//    from the graph's own CSR (rows of more than kSlGroupRow entries
+//    are summed by 16 lanes, of more than kSlWaveRow by the wave), rounds once, and does the epilogue of the apply
 //    (store, CG dot p^T q, or the FP64 residual r = b - L x and its dots) as
-//    in k_spmm.
+//    in k_spmm.  Neighbouring chunks, whose runs share lines, go to blocks of
+//    one XCD.
+// A row of more than kSlChunk entries is a chunk of its own; its pieces of
+// kSlChunk entries are summed by the gather's blocks straight from x.
+// Per entry the streams are 2 bytes of column, 2 of position, and the value
+// written and read back.  The gather is bound by them; the rows kernel waits
+// on the chain run start -> value -> LDS -> sum of each chunk.
+// Configuration model, n = 10^7, 75.7 M entries, unit weights: FP32 0.35 ms
+// per apply (gather 0.12, 4.9 TB/s; rows 0.23, 2.7 TB/s) against 0.69 for the
+// L2 slices and 1.26 row by row; FP64 0.59 ms (0.22 and 0.37) against 1.09
+// and 1.37.
 // Every sum is taken in a fixed order, so results repeat bit for bit.  The
-// slice structure is built on the host from the graph's CSR the first time
-// it is needed and kept with the graph.
+// order of the entries is built on the host from the graph's CSR the first
+// time it is needed and kept with the graph; it does not depend on the
+// weights.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
-#include <cstring>
 #include <string>
 #include <thread>
-#include <type_traits>
 #include <vector>
 
 #include "device_common.hpp"
@@ -44,58 +52,52 @@
 
 namespace nvd {
 
-constexpr int kSlRows = 2048;        // rows per chunk (LDS accumulator)
-constexpr int kSlLongItem = 32;      // neighbours above which an item takes a wave
-// Chunks of one slice per block of the slice pass: 8 for the FP32 pass; the
-// FP64 pass (which also reads each row's own x) measured faster with one.
-constexpr int slice_group(bool diff) { return diff ? 1 : 8; }
-constexpr int kSlNodes = 327680;     // nodes per slice: 2.5 MB of FP64 x
+constexpr int kSlBS = 1024;
+// Nodes per slice: two FP32 slices (two blocks) or one FP64 slice fill a CU's
+// 160 KB of LDS.
+constexpr int kSlNodes = 20352;
+// CSR entries per chunk (the LDS values of the rows kernel: two FP32 blocks or
+// one FP64 block per CU, beside the reductions' scratch).
+constexpr int kSlChunk = 16384;
+// Entries above which a row is summed by a group of 16 lanes, and by its wave.
+constexpr int kSlGroupRow = 16;
+constexpr int kSlWaveRow = 256;
 constexpr int kSlMinN = 1 << 20;     // graphs this large try the slices by default
+// Blocks of both kernels: what 256 CUs hold at once.
+template <typename V>
+constexpr int kSlBlocks = sizeof(V) == 8 ? 256 : 512;
 
 struct SliceGraph {
-  int S = 0, nch = 0, sn = 0;
-  long n_items = 0, n_long = 0;
-  // short items, per (slice, chunk) k = s*nch + c: [it_off[k], it_off[k+1]),
-  // a multiple of 4 (padding items: lrow = kSlRows, cnt = 0); their
-  // neighbours [es_off[k], es_off[k+1]) in item order
-  long* it_off = nullptr;
-  long* es_off = nullptr;
-  uint16_t* it_lrow = nullptr;
-  uint8_t* it_cnt = nullptr;
-  int* col_s = nullptr;
-  float* w32_s = nullptr;
-  double* w64_s = nullptr;
-  // long items [lg_off[k], lg_off[k+1]), neighbours at lg_ent
-  long* lg_off = nullptr;
-  uint16_t* lg_lrow = nullptr;
-  int* lg_cnt = nullptr;
-  long* lg_ent = nullptr;
-  int* col_l = nullptr;
-  float* w32_l = nullptr;
-  double* w64_l = nullptr;
-  double* part_s = nullptr;   // one FP64 partial per item
-  double* part_l = nullptr;
-  double* dw32 = nullptr;     // weighted graphs: FP64 sum of each row's FP32 weights
+  int S = 0, nch = 0, sn = 0, lsh = 0;
+  unsigned quads = 0;              // entries / 4 (every slice padded to a multiple of 4)
+  unsigned* off4 = nullptr;        // [S+1] first entry of slice s, / 4
+  uint16_t* lcol = nullptr;        // [4 quads] column within the slice
+  uint16_t* pos = nullptr;         // [4 quads] CSR position within the chunk
+  unsigned* run = nullptr;         // [nch+1][S] first entry of chunk c in slice s
+  int* row0 = nullptr;             // [nch+1] first row of chunk c
+  int* piece0 = nullptr;           // [nch+1] first piece of a chunk that is one long row
+  int n_piece = 0;
+  int* piece = nullptr;            // [n_piece][3] row, CSR range
+  double* val = nullptr;           // [4 quads] neighbours' values, FP32 or FP64
+  double* psum = nullptr;          // [n_piece]
   int64_t bytes = 0;
 };
 
 struct SliceArgs {
-  int n, S, nch;
-  const long* it_off;
-  const long* es_off;
-  const uint16_t* it_lrow;
-  const uint8_t* it_cnt;
-  const int* col_s;
-  const void* w_s;
-  const long* lg_off;
-  const uint16_t* lg_lrow;
-  const int* lg_cnt;
-  const long* lg_ent;
-  const int* col_l;
-  const void* w_l;
-  double* part_s;
-  double* part_l;
-  const double* dw;  // FP32 apply: d_v (sum of the row's FP32 weights, in FP64)
+  int n, S, nch, sn, lsh, n_piece;
+  unsigned quads;
+  const unsigned* off4;
+  const uint16_t* lcol;
+  const uint16_t* pos;
+  const unsigned* run;
+  const int* row0;
+  const int* piece0;
+  const int* piece;
+  void* val;
+  double* psum;
+  const int* rp;
+  const int* ci;
+  const void* w;     // CSR weights in the call's precision
   const int* gate;   // EPI_CG: the tile's active count; nothing to do when 0
 };
 
@@ -110,225 +112,268 @@ struct SliceOut {
   ColState* cs;
 };
 
-// DIFF: the edge-difference partial (FP64); else sum w x_u in FP64 (FP32).
-template <typename V, bool UNIT, bool DIFF>
-__global__ __launch_bounds__(kBS) void k_slice_pass(SliceArgs a, const V* __restrict__ x, long ldx) {
-  using A = typename std::conditional<DIFF, V, double>::type;
-  __shared__ int wsum[kBS / 64];
-  constexpr int G = slice_group(DIFF);
-  __shared__ long bnd[G + 1];
-  __shared__ long bndl[G + 1];
+__device__ __forceinline__ double wave_total(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// Sum over the 16 lanes of a DPP row, in every lane of it.
+template <int CTRL>
+__device__ __forceinline__ double row_turned(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double group_total(double v) {
+  v += row_turned<0x128>(v);   // row_ror:8, 4, 2, 1
+  v += row_turned<0x124>(v);
+  v += row_turned<0x122>(v);
+  v += row_turned<0x121>(v);
+  return v;
+}
+
+template <typename V, bool UNIT>
+__global__ __launch_bounds__(kSlBS, sizeof(V) == 8 ? 4 : 8) void k_slice_gather(SliceArgs a, const V* __restrict__ x,
+                                                                               long ldx) {
+  extern __shared__ double lds[];
+  V* xs = reinterpret_cast<V*>(lds);
   if (a.gate && *a.gate == 0) return;
-  // block -> (slice s, chunks c0 .. c0+cn-1); consecutive blocks go to the
-  // 8 XCDs in turn, and the blocks of one round cover slices 8r .. 8r+7
-  const int ngrp = (a.nch + G - 1) / G;
-  const int per_round = 8 * ngrp;
-  const int r = (int)blockIdx.x / per_round;
-  const int idx = (int)blockIdx.x - r * per_round;
-  const int s = r * 8 + (idx & 7);
-  const int c0 = (idx >> 3) * G;
-  const int cn = min(G, a.nch - c0);
-  const long k = (long)s * a.nch + c0;
-  // the items (and neighbours) of consecutive chunks of one slice are
-  // contiguous: the block walks them as one range
-  if ((int)threadIdx.x <= cn) {
-    bnd[threadIdx.x] = a.it_off[k + threadIdx.x];
-    bndl[threadIdx.x] = a.lg_off[k + threadIdx.x];
+  const int t = threadIdx.x;
+  const unsigned per = (a.quads + gridDim.x - 1) / gridDim.x;
+  unsigned q = min(a.quads, blockIdx.x * per);
+  const unsigned qend = min(a.quads, q + per);
+  int s = 0;
+  for (int lo = 0, hi = a.S; lo < hi;) {   // last slice that starts at or before q
+    const int mid = (lo + hi) >> 1;
+    if (a.off4[mid + 1] <= q) {
+      lo = mid + 1;
+    } else {
+      hi = mid;
+    }
+    s = lo;
   }
-  __syncthreads();
-  const V* ws = static_cast<const V*>(a.w_s);
-  const V* wl = static_cast<const V*>(a.w_l);
-  A* part_s = reinterpret_cast<A*>(a.part_s);
-  A* part_l = reinterpret_cast<A*>(a.part_l);
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const long i0 = bnd[0], i1 = bnd[cn];
-  long ebase = a.es_off[k];
-  for (long tile = i0; tile < i1; tile += 4 * kBS) {
-    const long my = tile + 4 * t;
-    const bool has = my < i1;
-    // a thread's 4 items lie in one chunk (every chunk's range is a
-    // multiple of 4 items)
-    long base_row = 0;
-    if constexpr (DIFF) {
-      int g = 0;
-      while (g + 1 < cn && bnd[g + 1] <= my) ++g;
-      base_row = (long)(c0 + g) * kSlRows;
-    }
-    // 4 items per thread: lrow and count as one 8- and one 4-byte load
-    const uint32_t cw = has ? *reinterpret_cast<const uint32_t*>(a.it_cnt + my) : 0u;
-    const uint2 lw = has ? *reinterpret_cast<const uint2*>(a.it_lrow + my) : make_uint2(0u, 0u);
-    const int cnt[4] = {(int)(cw & 255u), (int)((cw >> 8) & 255u), (int)((cw >> 16) & 255u),
-                        (int)(cw >> 24)};
-    const int lr[4] = {(int)(lw.x & 0xffffu), (int)(lw.x >> 16), (int)(lw.y & 0xffffu), (int)(lw.y >> 16)};
-    const int tot = cnt[0] + cnt[1] + cnt[2] + cnt[3];
-    // offset of this thread's neighbours: exclusive scan of tot over the block
-    int incl = tot;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += v;
-    }
-    if (lane == 63) wsum[wave] = incl;
+  const uint2* lc = reinterpret_cast<const uint2*>(a.lcol);
+  using V4 = typename VecOf<V, 4>::type;
+  V4* out = static_cast<V4*>(a.val);
+  for (; q < qend; ++s) {
+    const unsigned qs = min(qend, a.off4[s + 1]);
+    if (qs == q) continue;
+    const long j0 = (long)s * a.sn;
+    const int m = (int)min((long)a.sn, a.n - j0);
+#pragma unroll 4
+    for (int j = t; j < m; j += kSlBS) xs[j] = x[(j0 + j) * ldx];
     __syncthreads();
-    int wpre = 0, btot = 0;
+    unsigned i = q + t;
+    constexpr int U = 4;
+    for (; i + (U - 1) * kSlBS < qs; i += U * kSlBS) {
+      uint2 c[U];
 #pragma unroll
-    for (int w = 0; w < kBS / 64; ++w) {
-      if (w < wave) wpre += wsum[w];
-      btot += wsum[w];
-    }
-    __syncthreads();
-    const long e0 = ebase + wpre + incl - tot;
-    ebase += btot;
-    V xi[4] = {(V)0, (V)0, (V)0, (V)0};
-    if constexpr (DIFF) {
+      for (int u = 0; u < U; ++u) c[u] = lc[i + u * kSlBS];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) xi[j] = cnt[j] > 0 ? x[(base_row + lr[j]) * ldx] : (V)0;
-    }
-    const int c1 = cnt[0], c2 = c1 + cnt[1], c3 = c2 + cnt[2];
-    A acc[4] = {(A)0, (A)0, (A)0, (A)0};
-    // neighbours in flight per thread (FP64 keeps 4: its registers bound occupancy)
-    constexpr int EU = sizeof(V) == 8 ? 4 : 8;
-    for (int q0 = 0; q0 < tot; q0 += EU) {
-      int cc[EU];
-      V wt[EU];
-#pragma unroll
-      for (int u = 0; u < EU; ++u) {
-        cc[u] = 0;
-        wt[u] = (V)1;
-        if (q0 + u < tot) {
-          cc[u] = a.col_s[e0 + q0 + u];
-          if constexpr (!UNIT) wt[u] = ws[e0 + q0 + u];
-        }
-      }
-      V xv[EU];
-#pragma unroll
-      for (int u = 0; u < EU; ++u) xv[u] = q0 + u < tot ? x[(long)cc[u] * ldx] : (V)0;
-#pragma unroll
-      for (int u = 0; u < EU; ++u) {
-        const int q = q0 + u;
-        if (q < tot) {
-          // item j of neighbour q: the counts' running sums c1 <= c2 <= c3
-          const int j = q < c1 ? 0 : (q < c2 ? 1 : (q < c3 ? 2 : 3));
-          A d;
-          if constexpr (DIFF) {
-            const V xo = j == 0 ? xi[0] : (j == 1 ? xi[1] : (j == 2 ? xi[2] : xi[3]));
-            d = wt[u] * (xo - xv[u]);
-          } else {
-            d = (A)wt[u] * (A)xv[u];
-          }
-          if (j == 0)
-            acc[0] += d;
-          else if (j == 1)
-            acc[1] += d;
-          else if (j == 2)
-            acc[2] += d;
-          else
-            acc[3] += d;
-        }
+      for (int u = 0; u < U; ++u) {
+        V4 v;
+        v[0] = xs[c[u].x & 0xffffu];
+        v[1] = xs[c[u].x >> 16];
+        v[2] = xs[c[u].y & 0xffffu];
+        v[3] = xs[c[u].y >> 16];
+        out[i + u * kSlBS] = v;
       }
     }
-    if (has) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) part_s[my + j] = acc[j];
+    for (; i < qs; i += kSlBS) {
+      const uint2 c = lc[i];
+      V4 v;
+      v[0] = xs[c.x & 0xffffu];
+      v[1] = xs[c.x >> 16];
+      v[2] = xs[c.y & 0xffffu];
+      v[3] = xs[c.y >> 16];
+      out[i] = v;
     }
+    __syncthreads();
+    q = qs;
   }
-  // long items: one wave each, lanes over the neighbours, fixed-order sum
-  const long l0 = bndl[0], l1 = bndl[cn];
-  for (long q = l0 + wave; q < l1; q += kBS / 64) {
-    long row = 0;
-    if constexpr (DIFF) {
-      int g = 0;
-      while (g + 1 < cn && bndl[g + 1] <= q) ++g;
-      row = (long)(c0 + g) * kSlRows + a.lg_lrow[q];
+  // pieces of long rows
+  const V* w = static_cast<const V*>(a.w);
+  for (int p = blockIdx.x; p < a.n_piece; p += gridDim.x) {
+    const int row = a.piece[3 * p], lo = a.piece[3 * p + 1], hi = a.piece[3 * p + 2];
+    const double xv = (double)x[row * ldx];
+    double sum = 0.0;
+#pragma unroll 4
+    for (int e = lo + t; e < hi; e += kSlBS)
+      sum += (UNIT ? 1.0 : (double)w[e]) * (xv - (double)x[a.ci[e] * ldx]);
+    sum = wave_total(sum);
+    if ((t & 63) == 0) lds[t >> 6] = sum;
+    __syncthreads();
+    if (t == 0) {
+      double tot = 0.0;
+      for (int k = 0; k < kSlBS / 64; ++k) tot += lds[k];
+      a.psum[p] = tot;
     }
-    const int cnt = a.lg_cnt[q];
-    const long e = a.lg_ent[q];
-    const V xr = DIFF ? x[row * ldx] : (V)0;
-    A sum = (A)0;
-    for (int j = lane; j < cnt; j += 64) {
-      const V wt = UNIT ? (V)1 : wl[e + j];
-      const V xu = x[(long)a.col_l[e + j] * ldx];
-      if constexpr (DIFF)
-        sum += wt * (xr - xu);
-      else
-        sum += (A)wt * (A)xu;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
-    if (lane == 0) part_l[q] = sum;
+    __syncthreads();
   }
 }
 
-template <typename V, int EPI, bool DIFF>
-__global__ __launch_bounds__(kBS) void k_slice_combine(SliceArgs a, SliceOut<V> o, GridRed red) {
-  using A = typename std::conditional<DIFF, V, double>::type;
+template <typename V, bool UNIT, int EPI>
+__global__ __launch_bounds__(kSlBS, sizeof(V) == 8 ? 4 : 8) void k_slice_rows(SliceArgs a, SliceOut<V> o, GridRed red) {
   constexpr int ND = EPI == EPI_CG ? 1 : (EPI == EPI_RESID ? 5 : 0);
   constexpr int NDA = ND > 0 ? ND : 1;
-  __shared__ A acc[kSlRows + 1];
-  __shared__ double sh_red[ND > 0 ? ND * kBS : 1];
+  extern __shared__ double lds[];
   __shared__ double vals[NDA];
+  V* xe = reinterpret_cast<V*>(lds);
   if constexpr (EPI == EPI_CG) {
     if (o.cs->n_active == 0) return;
   }
-  const int t = threadIdx.x;
-  const A* part_s = reinterpret_cast<const A*>(a.part_s);
-  const A* part_l = reinterpret_cast<const A*>(a.part_l);
+  const int t = threadIdx.x, lane = t & 63;
+  const V* w = static_cast<const V*>(a.w);
+  const V* val = static_cast<const V*>(a.val);
   double dacc[NDA][1];
 #pragma unroll
   for (int d = 0; d < NDA; ++d) dacc[d][0] = 0.0;
-  for (int c = blockIdx.x; c < a.nch; c += gridDim.x) {
-    for (int i = t; i <= kSlRows; i += kBS) acc[i] = (A)0;
-    __syncthreads();
-    for (int s = 0; s < a.S; ++s) {
-      const long k = (long)s * a.nch + c;
-      const long i0 = a.it_off[k], i1 = a.it_off[k + 1];
-      for (long it = i0 + 4 * t; it < i1; it += 4 * kBS) {
-        const uint2 lw = *reinterpret_cast<const uint2*>(a.it_lrow + it);
-        // padding items add 0 into the spare slot kSlRows
-        acc[lw.x & 0xffffu] += part_s[it];
-        acc[lw.x >> 16] += part_s[it + 1];
-        acc[lw.y & 0xffffu] += part_s[it + 2];
-        acc[lw.y >> 16] += part_s[it + 3];
-      }
-      const long l0 = a.lg_off[k], l1 = a.lg_off[k + 1];
-      for (long q = l0 + t; q < l1; q += kBS) acc[a.lg_lrow[q]] += part_l[q];
-      __syncthreads();
+  auto finish = [&](unsigned row, double xv, double sum) {
+    const V yv = (V)sum;
+    if constexpr (EPI == EPI_PLAIN) {
+      o.y[row * o.ldy] = yv;
+    } else if constexpr (EPI == EPI_CG) {
+      o.y[row * o.ldy] = yv;
+      dacc[0][0] += xv * (double)yv;
+    } else {
+      const double bb = o.b[row * o.ldb];
+      const double rr = bb - (double)yv;
+      o.y[row * o.ldy] = (V)rr;
+      dacc[0][0] += bb * xv;
+      dacc[1][0] += xv * rr;
+      dacc[2][0] += rr * rr;
+      dacc[3][0] += rr;
+      dacc[4][0] += xv;
     }
-    for (int i = t; i < kSlRows; i += kBS) {
-      const long row = (long)c * kSlRows + i;
-      if (row >= a.n) break;
-      V yv;
-      if constexpr (DIFF)
-        yv = acc[i];
-      else
-        yv = (V)((double)o.x[row * o.ldx] * a.dw[row] - acc[i]);
-      if constexpr (EPI == EPI_PLAIN) {
-        o.y[row * o.ldy] = yv;
-      } else if constexpr (EPI == EPI_CG) {
-        o.y[row * o.ldy] = yv;
-        dacc[0][0] += (double)o.x[row * o.ldx] * (double)yv;
-      } else {
-        const double own = (double)o.x[row * o.ldx];
-        const double bb = o.b[row * o.ldb];
-        const double rr = bb - (double)yv;
-        o.y[row * o.ldy] = (V)rr;
-        dacc[0][0] += bb * own;
-        dacc[1][0] += own * rr;
-        dacc[2][0] += rr * rr;
-        dacc[3][0] += rr;
-        dacc[4][0] += own;
+  };
+  // block b runs on XCD b mod 8 (the grid is a multiple of 8): the chunks of
+  // an XCD are consecutive, and its blocks walk them side by side
+  const int xcd = blockIdx.x & 7;
+  const int c1 = (int)((long)(xcd + 1) * a.nch / 8);
+  const int nsub = kSlBS >> a.lsh, sub = t >> a.lsh, l = t & ((1 << a.lsh) - 1);
+  for (int c = (int)((long)xcd * a.nch / 8) + (blockIdx.x >> 3); c < c1; c += gridDim.x >> 3) {
+    const unsigned r0 = a.row0[c], r1 = a.row0[c + 1];
+    const int pc = a.piece0[c], pn = a.piece0[c + 1];
+    if (pn > pc) {   // one long row
+      if (t < 64) {
+        double sum = 0.0;
+        for (int p = pc + lane; p < pn; p += 64) sum += a.psum[p];
+        sum = wave_total(sum);
+        if (t == 0) finish(r0, (double)o.x[r0 * o.ldx], sum);
       }
+      continue;
+    }
+    // the thread's first row, in flight while the values arrive
+    unsigned row = (unsigned)r0 + t;
+    int e0 = 0, e1 = 0;
+    V xv = (V)0;
+    if (row < r1) {
+      e0 = a.rp[row];
+      e1 = a.rp[row + 1];
+      xv = o.x[row * o.ldx];
+    }
+    const int ebase = a.rp[r0];
+    const unsigned* run = a.run + (long)c * a.S;
+    constexpr int U = 4;   // runs in flight; 8 spill in FP32: 415 us per apply against 350
+    for (int s = sub; s < a.S; s += U * nsub) {
+      unsigned p[U], e[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int su = s + u * nsub;
+        const bool in = su < a.S;
+        p[u] = in ? run[su] + l : 0u;
+        e[u] = in ? run[su + a.S] : 0u;
+      }
+      bool more = true;
+      while (more) {
+        V v[U];
+        unsigned at[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (p[u] < e[u]) {
+            v[u] = val[p[u]];
+            at[u] = a.pos[p[u]];
+          }
+        more = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (p[u] < e[u]) xe[at[u]] = v[u];
+          p[u] += 1u << a.lsh;
+          more = more || p[u] < e[u];
+        }
+      }
+    }
+    __syncthreads();
+    const int rows = (int)(r1 - r0);
+    for (int base = 0; base < rows; base += kSlBS) {
+      const unsigned next = row + kSlBS;
+      int f0 = 0, f1 = 0;
+      V xn = (V)0;
+      if (next < r1) {
+        f0 = a.rp[next];
+        f1 = a.rp[next + 1];
+        xn = o.x[next * o.ldx];
+      }
+      const double xr = (double)xv;
+      const int len = e1 - e0;
+      double sum = 0.0;
+      if (len <= kSlGroupRow) {
+        for (int j = 0; j < len; j += 4) {
+          double term[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int e = min(e0 + j + u, e1 - 1);
+            term[u] = (UNIT ? 1.0 : (double)w[e]) * (xr - (double)xe[e - ebase]);
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) sum += j + u < len ? term[u] : 0.0;
+        }
+      }
+      // four rows at a time, 16 lanes each: group i takes the i-th of the mask
+      for (unsigned long long m = __ballot(len > kSlGroupRow && len <= kSlWaveRow); m != 0;) {
+        const int mine = __popcll(m & ((1ull << lane) - 1ull));
+        const bool out = (m >> lane & 1ull) != 0 && mine < 4;
+        const unsigned long long m1 = m & (m - 1), m2 = m1 & (m1 - 1), m3 = m2 & (m2 - 1);
+        const int grp = lane >> 4;
+        const unsigned long long mg = grp == 0 ? m : (grp == 1 ? m1 : (grp == 2 ? m2 : m3));
+        const int k = mg != 0 ? __builtin_ctzll(mg) : lane;
+        const int b0 = __shfl(e0, k, 64), b1 = __shfl(e1, k, 64);   // (in every lane: its source must be active)
+        const double xb = __shfl(xr, k, 64);
+        double part = 0.0;
+        for (int e = b0 + (lane & 15); e < (mg != 0 ? b1 : b0); e += 16)
+          part += (UNIT ? 1.0 : (double)w[e]) * (xb - (double)xe[e - ebase]);
+        part = __shfl(group_total(part), mine << 4 & 63, 64);
+        if (out) sum = part;
+        m = m3 & (m3 - 1);
+      }
+      for (unsigned long long m = __ballot(len > kSlWaveRow); m != 0; m &= m - 1) {
+        const int k = __builtin_ctzll(m);
+        const int b0 = __shfl(e0, k, 64), b1 = __shfl(e1, k, 64);
+        const double xb = __shfl(xr, k, 64);
+        double part = 0.0;
+        for (int e = b0 + lane; e < b1; e += 64)
+          part += (UNIT ? 1.0 : (double)w[e]) * (xb - (double)xe[e - ebase]);
+        part = wave_total(part);
+        if (lane == k) sum = part;
+      }
+      if (row < r1) finish(row, xr, sum);
+      row = next;
+      e0 = f0;
+      e1 = f1;
+      xv = xn;
     }
     __syncthreads();
   }
   if constexpr (ND > 0) {
-    block_reduce_cols<kBS, ND, 1>(dacc, 1, sh_red);
+    __syncthreads();
+    block_reduce_cols<kSlBS, ND, 1>(dacc, 1, lds);
     if (t == 0) {
 #pragma unroll
-      for (int d = 0; d < ND; ++d) vals[d] = sh_red[d * kBS];
+      for (int d = 0; d < ND; ++d) vals[d] = lds[d * kSlBS];
     }
     __syncthreads();
-    if (!grid_reduce<kBS>(vals, ND, red)) return;
+    if (!grid_reduce<kSlBS>(vals, ND, red)) return;
     if (t == 0) {
       ColState* cs = o.cs;
       if constexpr (EPI == EPI_CG) {
@@ -359,9 +404,7 @@ void free_slices(DevGraph* g) {
   SliceGraph* sg = g->slices;
   if (!sg) return;
   (void)hipDeviceSynchronize();
-  void* ps[] = {sg->it_off, sg->es_off, sg->it_lrow, sg->it_cnt, sg->col_s, sg->w32_s, sg->w64_s,
-                sg->lg_off, sg->lg_lrow, sg->lg_cnt, sg->lg_ent, sg->col_l, sg->w32_l, sg->w64_l,
-                sg->part_s, sg->part_l, sg->dw32};
+  void* ps[] = {sg->off4, sg->lcol, sg->pos, sg->run, sg->row0, sg->piece0, sg->piece, sg->val, sg->psum};
   for (void* p : ps)
     if (p) (void)hipFree(p);
   g->bytes -= sg->bytes;
@@ -371,7 +414,7 @@ void free_slices(DevGraph* g) {
 }
 
 // NVD_SLICE: "0" never, "1" for every graph, otherwise graphs of at least
-// kSlMinN nodes.  NVD_SLICE_NODES: nodes per slice (default kSlNodes).
+// kSlMinN nodes.  NVD_SLICE_NODES: nodes per slice (default and most kSlNodes).
 static int slice_mode() {
   const char* e = std::getenv("NVD_SLICE");
   if (e && e[0] == '0') return 0;
@@ -380,16 +423,20 @@ static int slice_mode() {
 }
 
 template <typename T>
-static bool up(T** dst, const std::vector<T>& v, int64_t& bytes) {
-  const size_t nb = std::max<size_t>(1, v.size()) * sizeof(T);
+static bool room(T** dst, size_t count, int64_t& bytes) {
+  const size_t nb = std::max<size_t>(1, count) * sizeof(T);
   if (hipMalloc(reinterpret_cast<void**>(dst), nb) != hipSuccess) {
     *dst = nullptr;
     return false;
   }
   bytes += (int64_t)nb;
-  if (!v.empty() && hipMemcpy(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess)
-    return false;
   return true;
+}
+
+template <typename T>
+static bool up(T** dst, const std::vector<T>& v, int64_t& bytes) {
+  return room(dst, v.size(), bytes) &&
+         (v.empty() || hipMemcpy(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice) == hipSuccess);
 }
 
 static nvd_status build_slices(DevGraph* g) {
@@ -397,176 +444,93 @@ static nvd_status build_slices(DevGraph* g) {
   long sn = kSlNodes;
   if (const char* e = std::getenv("NVD_SLICE_NODES")) {
     const long v = std::atol(e);
-    if (v >= 1) sn = v;
+    if (v >= 1 && v < sn) sn = v;
   }
-  if (sn > n) sn = n;
   const std::vector<int>& rp = g->h_rp;
-  // Slice boundaries: consecutive node ranges with about the same number of
-  // CSR entries (column j holds deg(j) of them: the graph is symmetric), so
-  // that the 8 XCDs of a round get about the same work even where degree
-  // follows the node id (preferential attachment puts the hubs first), and
-  // at most sn nodes each (one slice of x in an XCD's L2).  A multiple of 8.
-  const int S0 = (int)(((n + sn - 1) / sn + 7) / 8 * 8);
-  std::vector<int> slice_of(n);
-  int S = 0;
-  {
-    const double per = (double)g->nnz / S0;
-    long first = 0;
-    double acc = 0.0;
-    for (long j = 0; j < n; ++j) {
-      const double dj = (double)(rp[j + 1] - rp[j]);
-      if (j > first && (j - first >= sn || acc + 0.5 * dj > per * (S + 1))) {
-        ++S;
-        first = j;
+  const std::vector<int>& ci = g->h_ci;
+  const int S = (int)((n + sn - 1) / sn);
+  // chunks: as many rows as kSlChunk entries hold, and no more than kSlChunk
+  // rows (isolated nodes have no entries); a longer row by itself
+  std::vector<int> row0(1, 0), piece0(1, 0), piece;
+  for (long r = 0; r < n;) {
+    long e = r + 1;
+    if (rp[e] - rp[r] > kSlChunk) {
+      for (long lo = rp[r]; lo < rp[e]; lo += kSlChunk) {
+        piece.push_back((int)r);
+        piece.push_back((int)lo);
+        piece.push_back((int)std::min<long>(lo + kSlChunk, rp[e]));
       }
-      slice_of[j] = S;
-      acc += dj;
+    } else {
+      while (e < n && rp[e + 1] - rp[r] <= kSlChunk && e - r < kSlChunk) ++e;
     }
-    S = (S + 1 + 7) / 8 * 8;
+    row0.push_back((int)e);
+    piece0.push_back((int)(piece.size() / 3));
+    r = e;
   }
-  const int nch = (int)((n + kSlRows - 1) / kSlRows);
-  const long K = (long)S * nch;
-  if (K > (1L << 31) / 8 || (long)8 * nch > (1L << 30)) {
+  const int nch = (int)row0.size() - 1;
+  if ((long)S * (nch + 1) > (1L << 28)) {   // the runs would average less than a few entries
     set_error("slices: graph too large for the sliced apply");
     return NVD_E_UNSUPPORTED;
   }
-  const std::vector<int>& ci = g->h_ci;
-  const bool wtd = g->weighted;
-  const std::vector<double>& hw = g->h_w;
   const int nthr = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-  // pass 1: items and neighbours per (slice, chunk); rows are sorted by
-  // column, so a row's neighbours in one slice are one run
-  std::vector<long> ns(K + 1, 0), nl(K + 1, 0), es(K + 1, 0), el(K + 1, 0);
-  std::vector<char> bad(nthr, 0);
-  auto runs = [&](long i, auto&& f) {
-    long e = rp[i];
-    const long end = rp[i + 1];
-    int prev = -1;
-    while (e < end) {
-      const int s = slice_of[ci[e]];
-      if (s < prev) return false;
-      long f2 = e + 1;
-      while (f2 < end && slice_of[ci[f2]] == s) ++f2;
-      f(s, e, (int)(f2 - e));
-      prev = s;
-      e = f2;
-    }
-    return true;
-  };
-  {
+  auto chunks = [&](auto&& f) {
     std::vector<std::thread> th;
     for (int tt = 0; tt < nthr; ++tt)
       th.emplace_back([&, tt] {
         for (int c = tt; c < nch; c += nthr)
-          for (long i = (long)c * kSlRows; i < std::min(n, (long)(c + 1) * kSlRows); ++i) {
-            const bool ok = runs(i, [&](int s, long, int len) {
-              const long k = (long)s * nch + c;
-              if (len > kSlLongItem) {
-                nl[k + 1]++;
-                el[k + 1] += len;
-              } else {
-                ns[k + 1]++;
-                es[k + 1] += len;
-              }
-            });
-            if (!ok) bad[tt] = 1;
-          }
+          if (piece0[c + 1] == piece0[c]) f(c);
       });
     for (auto& x : th) x.join();
+  };
+  // entries of each (chunk, slice), then where each run starts
+  std::vector<unsigned> run((size_t)S * (nch + 1), 0u);
+  chunks([&](int c) {
+    unsigned* cnt = &run[(size_t)S * c];
+    for (long e = rp[row0[c]]; e < rp[row0[c + 1]]; ++e) cnt[ci[e] / sn]++;
+  });
+  std::vector<unsigned> at(S, 0u), off4(S + 1, 0u);
+  for (int c = 0; c < nch; ++c)
+    for (int s = 0; s < S; ++s) at[s] += run[(size_t)S * c + s];
+  unsigned total = 0;
+  for (int s = 0; s < S; ++s) {
+    const unsigned len = at[s];
+    at[s] = total;
+    off4[s] = total / 4;
+    total += (len + 3) / 4 * 4;
   }
-  if (std::any_of(bad.begin(), bad.end(), [](char b) { return b != 0; })) {
-    set_error("slices: rows are not sorted by column");
-    return NVD_E_UNSUPPORTED;
-  }
-  std::vector<long> it_off(K + 1, 0), lg_off(K + 1, 0);
-  for (long k = 0; k < K; ++k) {
-    it_off[k + 1] = it_off[k] + (ns[k + 1] + 3) / 4 * 4;
-    lg_off[k + 1] = lg_off[k] + nl[k + 1];
-    es[k + 1] += es[k];
-    el[k + 1] += el[k];
-  }
-  const long NI = it_off[K], NL = lg_off[K];
-  std::vector<uint16_t> it_lrow(NI, (uint16_t)kSlRows), lg_lrow(NL);
-  std::vector<uint8_t> it_cnt(NI, 0);
-  std::vector<int> col_s(es[K]), col_l(el[K]), lg_cnt(NL);
-  std::vector<long> lg_ent(NL);
-  std::vector<double> w_s(wtd ? es[K] : 0), w_l(wtd ? el[K] : 0);
-  {
-    std::vector<std::thread> th;
-    for (int tt = 0; tt < nthr; ++tt)
-      th.emplace_back([&, tt] {
-        std::vector<long> pi(S), pe(S), pl(S), pq(S);
-        for (int c = tt; c < nch; c += nthr) {
-          for (int s = 0; s < S; ++s) {
-            const long k = (long)s * nch + c;
-            pi[s] = it_off[k];
-            pe[s] = es[k];
-            pl[s] = lg_off[k];
-            pq[s] = el[k];
-          }
-          for (long i = (long)c * kSlRows; i < std::min(n, (long)(c + 1) * kSlRows); ++i) {
-            const uint16_t lrow = (uint16_t)(i - (long)c * kSlRows);
-            runs(i, [&](int s, long e, int len) {
-              if (len > kSlLongItem) {
-                const long q = pl[s]++;
-                lg_lrow[q] = lrow;
-                lg_cnt[q] = len;
-                lg_ent[q] = pq[s];
-                for (int j = 0; j < len; ++j) {
-                  col_l[pq[s] + j] = ci[e + j];
-                  if (wtd) w_l[pq[s] + j] = hw[e + j];
-                }
-                pq[s] += len;
-              } else {
-                const long q = pi[s]++;
-                it_lrow[q] = lrow;
-                it_cnt[q] = (uint8_t)len;
-                for (int j = 0; j < len; ++j) {
-                  col_s[pe[s] + j] = ci[e + j];
-                  if (wtd) w_s[pe[s] + j] = hw[e + j];
-                }
-                pe[s] += len;
-              }
-            });
-          }
-        }
-      });
-    for (auto& x : th) x.join();
-  }
+  off4[S] = total / 4;
+  for (int c = 0; c <= nch; ++c)
+    for (int s = 0; s < S; ++s) {
+      const unsigned len = run[(size_t)S * c + s];
+      run[(size_t)S * c + s] = at[s];
+      at[s] += len;
+    }
+  std::vector<uint16_t> lcol(total, 0), pos(total, 0);
+  chunks([&](int c) {
+    std::vector<unsigned> next(run.begin() + (size_t)S * c, run.begin() + (size_t)S * (c + 1));
+    const long e0 = rp[row0[c]];
+    for (long e = e0; e < rp[row0[c + 1]]; ++e) {
+      const int s = (int)(ci[e] / sn);
+      const unsigned p = next[s]++;
+      lcol[p] = (uint16_t)(ci[e] - s * sn);
+      pos[p] = (uint16_t)(e - e0);
+    }
+  });
   SliceGraph* sg = new SliceGraph();
   sg->S = S;
   sg->nch = nch;
   sg->sn = (int)sn;
-  sg->n_items = NI;
-  sg->n_long = NL;
-  bool ok = up(&sg->it_off, it_off, sg->bytes) && up(&sg->es_off, es, sg->bytes) &&
-            up(&sg->it_lrow, it_lrow, sg->bytes) && up(&sg->it_cnt, it_cnt, sg->bytes) &&
-            up(&sg->col_s, col_s, sg->bytes) && up(&sg->lg_off, lg_off, sg->bytes) &&
-            up(&sg->lg_lrow, lg_lrow, sg->bytes) && up(&sg->lg_cnt, lg_cnt, sg->bytes) &&
-            up(&sg->lg_ent, lg_ent, sg->bytes) && up(&sg->col_l, col_l, sg->bytes);
-  if (ok && wtd) {
-    std::vector<double> dw(n, 0.0);
-    for (long i = 0; i < n; ++i)
-      for (long e = rp[i]; e < rp[i + 1]; ++e) dw[i] += (double)(float)hw[e];
-    ok = up(&sg->dw32, dw, sg->bytes);
-  }
-  if (ok && wtd) {
-    std::vector<float> f_s(w_s.size()), f_l(w_l.size());
-    for (size_t j = 0; j < w_s.size(); ++j) f_s[j] = (float)w_s[j];
-    for (size_t j = 0; j < w_l.size(); ++j) f_l[j] = (float)w_l[j];
-    ok = up(&sg->w64_s, w_s, sg->bytes) && up(&sg->w64_l, w_l, sg->bytes) && up(&sg->w32_s, f_s, sg->bytes) &&
-         up(&sg->w32_l, f_l, sg->bytes);
-  }
-  if (ok) {
-    ok = hipMalloc(&sg->part_s, std::max<long>(4, NI) * sizeof(double)) == hipSuccess;
-    if (ok) sg->bytes += std::max<long>(4, NI) * sizeof(double);
-    else sg->part_s = nullptr;
-  }
-  if (ok) {
-    ok = hipMalloc(&sg->part_l, std::max<long>(1, NL) * sizeof(double)) == hipSuccess;
-    if (ok) sg->bytes += std::max<long>(1, NL) * sizeof(double);
-    else sg->part_l = nullptr;
-  }
+  sg->quads = total / 4;
+  sg->n_piece = (int)(piece.size() / 3);
+  // lanes per run: at most half its average, so that few of the last step's
+  // lanes are idle, and at most 16 (10^7 nodes, runs of 33: FP32 apply 350 us
+  // with 16 lanes, 394 with 8, whose loads are half as wide)
+  const double avg = (double)total / ((double)S * nch);
+  while (sg->lsh < 4 && (4 << sg->lsh) <= avg) sg->lsh++;
+  const bool ok = up(&sg->off4, off4, sg->bytes) && up(&sg->lcol, lcol, sg->bytes) && up(&sg->pos, pos, sg->bytes) &&
+                  up(&sg->run, run, sg->bytes) && up(&sg->row0, row0, sg->bytes) &&
+                  up(&sg->piece0, piece0, sg->bytes) && up(&sg->piece, piece, sg->bytes) &&
+                  room(&sg->val, total, sg->bytes) && room(&sg->psum, (size_t)sg->n_piece, sg->bytes);
   g->slices = sg;
   g->bytes += sg->bytes;
   if (!ok) {
@@ -578,6 +542,35 @@ static nvd_status build_slices(DevGraph* g) {
   return NVD_OK;
 }
 
+template <typename V, bool UNIT, int EPI>
+static nvd_status launch_forms(const SliceArgs& a, const SliceOut<V>& o, const GridRed& red, hipStream_t s) {
+  constexpr int lds_gather = kSlNodes * sizeof(V), lds_rows = kSlChunk * sizeof(V);
+  auto* gather = &k_slice_gather<V, UNIT>;
+  auto* rows = &k_slice_rows<V, UNIT, EPI>;
+  NVD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(gather), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              lds_gather));
+  NVD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(rows), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              lds_rows));
+  gather<<<kSlBlocks<V>, kSlBS, lds_gather, s>>>(a, o.x, o.ldx);
+  rows<<<std::min(kSlBlocks<V>, (a.nch + 7) / 8 * 8), kSlBS, lds_rows, s>>>(a, o, red);
+  NVD_HIP(hipGetLastError());
+  return NVD_OK;
+}
+
+template <typename V, bool UNIT>
+static nvd_status launch_epi(const SliceArgs& a, const SliceOut<V>& o, int epi, const GridRed& red, hipStream_t s) {
+  switch (epi) {
+    case EPI_PLAIN: return launch_forms<V, UNIT, EPI_PLAIN>(a, o, red, s);
+    case EPI_CG: return launch_forms<V, UNIT, EPI_CG>(a, o, red, s);
+    case EPI_RESID:
+      if constexpr (sizeof(V) == 8) return launch_forms<V, UNIT, EPI_RESID>(a, o, red, s);
+      break;
+    default: break;
+  }
+  set_error("slices: unsupported epilogue");
+  return NVD_E_UNSUPPORTED;
+}
+
 template <typename V>
 static nvd_status launch_sliced(const SpmmCall& c, const GridRed& red, hipStream_t s) {
   const DevGraph* g = c.g;
@@ -587,26 +580,25 @@ static nvd_status launch_sliced(const SpmmCall& c, const GridRed& red, hipStream
   a.n = g->n;
   a.S = sg->S;
   a.nch = sg->nch;
-  a.it_off = sg->it_off;
-  a.es_off = sg->es_off;
-  a.it_lrow = sg->it_lrow;
-  a.it_cnt = sg->it_cnt;
-  a.col_s = sg->col_s;
-  a.lg_off = sg->lg_off;
-  a.lg_lrow = sg->lg_lrow;
-  a.lg_cnt = sg->lg_cnt;
-  a.lg_ent = sg->lg_ent;
-  a.col_l = sg->col_l;
-  if constexpr (sizeof(V) == 8) {
-    a.w_s = sg->w64_s;
-    a.w_l = sg->w64_l;
-  } else {
-    a.w_s = sg->w32_s;
-    a.w_l = sg->w32_l;
-  }
-  a.part_s = sg->part_s;
-  a.part_l = sg->part_l;
-  a.dw = unit ? g->deg64 : sg->dw32;
+  a.sn = sg->sn;
+  a.lsh = sg->lsh;
+  a.n_piece = sg->n_piece;
+  a.quads = sg->quads;
+  a.off4 = sg->off4;
+  a.lcol = sg->lcol;
+  a.pos = sg->pos;
+  a.run = sg->run;
+  a.row0 = sg->row0;
+  a.piece0 = sg->piece0;
+  a.piece = sg->piece;
+  a.val = sg->val;
+  a.psum = sg->psum;
+  a.rp = g->rp;
+  a.ci = g->ci;
+  if constexpr (sizeof(V) == 8)
+    a.w = g->w64;
+  else
+    a.w = g->w32;
   a.gate = c.epi == EPI_CG ? &c.cs->n_active : nullptr;
   SliceOut<V> o{};
   o.x = static_cast<const V*>(c.x);
@@ -616,10 +608,6 @@ static nvd_status launch_sliced(const SpmmCall& c, const GridRed& red, hipStream
   o.b = c.b;
   o.ldb = c.ldb;
   o.cs = c.cs;
-  constexpr bool DIFF = sizeof(V) == 8;
-  constexpr int G = slice_group(DIFF);
-  const int pass_grid = sg->S * ((sg->nch + G - 1) / G);   // S/8 rounds x 8 slices x chunk groups
-  const int comb_grid = std::min(sg->nch, kMaxBlocks);
   int pid = -1;
   if (prof_enabled()) {
     const double sv = (double)sizeof(V);
@@ -629,29 +617,9 @@ static nvd_status launch_sliced(const SpmmCall& c, const GridRed& red, hipStream
     const double vecb = c.epi == EPI_RESID ? 3.0 * 8.0 * n : 2.0 * sv * n;
     pid = prof_begin(s, sizeof(V) == 8 ? PK_SPMM64 : PK_SPMM32, csr + vecb);
   }
-  if (unit)
-    k_slice_pass<V, true, DIFF><<<pass_grid, kBS, 0, s>>>(a, o.x, o.ldx);
-  else
-    k_slice_pass<V, false, DIFF><<<pass_grid, kBS, 0, s>>>(a, o.x, o.ldx);
-  bool ok = true;
-  switch (c.epi) {
-    case EPI_PLAIN: k_slice_combine<V, EPI_PLAIN, DIFF><<<comb_grid, kBS, 0, s>>>(a, o, red); break;
-    case EPI_CG: k_slice_combine<V, EPI_CG, DIFF><<<comb_grid, kBS, 0, s>>>(a, o, red); break;
-    case EPI_RESID:
-      if constexpr (sizeof(V) == 8)
-        k_slice_combine<V, EPI_RESID, DIFF><<<comb_grid, kBS, 0, s>>>(a, o, red);
-      else
-        ok = false;
-      break;
-    default: ok = false;
-  }
+  const nvd_status st = unit ? launch_epi<V, true>(a, o, c.epi, red, s) : launch_epi<V, false>(a, o, c.epi, red, s);
   prof_end(s, pid);
-  if (!ok) {
-    set_error("slices: unsupported epilogue");
-    return NVD_E_UNSUPPORTED;
-  }
-  NVD_HIP(hipGetLastError());
-  return NVD_OK;
+  return st;
 }
 
 // Time the row-wise and the sliced apply of this call's x (EPI_PLAIN into a

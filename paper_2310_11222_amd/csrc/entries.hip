@@ -10,6 +10,7 @@
 #include <algorithm>
 
 #include "column_pre_dev.hpp"
+#include "entry_walk.hpp"
 
 namespace nvd {
 
@@ -27,10 +28,10 @@ __device__ __forceinline__ int row_of(int n, const int* __restrict__ rp, int e) 
 }
 
 // Row of every entry, and the entry (j, i) of every entry (i, j).
-__global__ __launch_bounds__(256) void k_entries(int n, int nnz, const int* __restrict__ rp,
-                                                 const int* __restrict__ ci, int* __restrict__ erow,
-                                                 int* __restrict__ mirror) {
-  for (int e = blockIdx.x * 256 + threadIdx.x; e < nnz; e += gridDim.x * 256) {
+__global__ __launch_bounds__(kEntryBS) void k_entries(int n, int nnz, const int* __restrict__ rp,
+                                                      const int* __restrict__ ci, int* __restrict__ erow,
+                                                      int* __restrict__ mirror) {
+  for_entries(blockIdx.x, gridDim.x, threadIdx.x, nnz, [&](int e) {
     const int i = row_of(n, rp, e), j = ci[e];
     erow[e] = i;
     int a = rp[j], b = rp[j + 1];
@@ -42,21 +43,21 @@ __global__ __launch_bounds__(256) void k_entries(int n, int nnz, const int* __re
         b = mid;
     }
     mirror[e] = a;                     // (the graph was checked to be symmetric)
-  }
+  });
 }
 
 // New weights in input order: bit 1 where one is not finite and positive, bit 2
 // where an entry's and its mirror's differ.
-__global__ __launch_bounds__(256) void k_check_entries(int nnz, const int* __restrict__ in_pos,
-                                                       const int* __restrict__ mirror,
-                                                       const double* __restrict__ w, int* flag) {
+__global__ __launch_bounds__(kEntryBS) void k_check_entries(int nnz, const int* __restrict__ in_pos,
+                                                            const int* __restrict__ mirror,
+                                                            const double* __restrict__ w, int* flag) {
   int bad = 0;
-  for (int e = blockIdx.x * 256 + threadIdx.x; e < nnz; e += gridDim.x * 256) {
+  for_entries(blockIdx.x, gridDim.x, threadIdx.x, nnz, [&](int e) {
     const int m = mirror[e];
     const double v = w[in_pos ? in_pos[e] : e];
     if (!(v > 0.0) || !isfinite(v)) bad |= 1;
     if (w[in_pos ? in_pos[m] : m] != v) bad |= 2;
-  }
+  });
   if (bad) atomicOr(flag, bad);
 }
 
@@ -139,8 +140,6 @@ __global__ __launch_bounds__(256) void k_grad_entries(int n, int nnz, const int*
   }
 }
 
-static int entry_grid(long work) { return (int)std::max<long>(1, std::min<long>((work + 255) / 256, 65536)); }
-
 void launch_row_degree(int n, const int* rp, const double* w64, float* w32, double* deg64, float* deg32,
                        double* invd64, float* invd32, hipStream_t s) {
   k_row_degree<<<entry_grid(16L * n), 256, 0, s>>>(n, rp, w64, w32, deg64, deg32, invd64, invd32);
@@ -151,7 +150,7 @@ static nvd_status ensure_entries(DevGraph* g, hipStream_t s) {
   int* p = nullptr;
   const size_t count = 2 * (size_t)std::max(g->nnz, 1) + 1;
   NVD_HIP(hipMalloc((void**)&p, sizeof(int) * count));
-  if (g->nnz > 0) k_entries<<<entry_grid(g->nnz), 256, 0, s>>>(g->n, g->nnz, g->rp, g->ci, p, p + g->nnz);
+  if (g->nnz > 0) k_entries<<<entry_grid(g->nnz), kEntryBS, 0, s>>>(g->n, g->nnz, g->rp, g->ci, p, p + g->nnz);
   // (other streams may use them from the next call on)
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -173,7 +172,7 @@ nvd_status check_weights(DevGraph* g, const double* w, int* bits, hipStream_t s)
   *bits = 0;
   NVD_HIP(hipMemcpyAsync(flag, bits, sizeof(int), hipMemcpyHostToDevice, s));
   if (g->nnz > 0)
-    k_check_entries<<<std::min(entry_grid(g->nnz), 2048), 256, 0, s>>>(g->nnz, g->in_pos, g->mirror, w, flag);
+    k_check_entries<<<std::min(entry_grid(g->nnz), 2048), kEntryBS, 0, s>>>(g->nnz, g->in_pos, g->mirror, w, flag);
   NVD_HIP(hipGetLastError());
   NVD_HIP(hipMemcpyAsync(bits, flag, sizeof(int), hipMemcpyDeviceToHost, s));
   NVD_HIP(hipStreamSynchronize(s));
@@ -187,7 +186,7 @@ nvd_status grad_entries(DevGraph* g, int k, const double* X, int64_t ldx, const 
     const int cols = std::min(64, k - c0);
     int L = 1;
     while (L < cols) L *= 2;
-    const int grid = entry_grid((long)((g->nnz + 3) / 4) * L);
+    const int grid = entry_grid(((long)g->nnz + 3) / 4 * L);
     switch (L) {
 #define NVD_E(LL)                                                                                          \
   case LL:                                                                                                 \

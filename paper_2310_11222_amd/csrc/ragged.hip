@@ -6,12 +6,17 @@
 // A row of X is read by the next power of two of lanes, one element a lane
 // (rows of 3 or 5 elements have no 16-byte alignment to use); the lanes past
 // the last column repeat it, so that they ask for no further line, and store
-// nothing.  Rows, the split of long rows and their fixed order of summation
-// are those of k_spmm.
+// nothing.  Rows and the split of long rows are those of k_spmm.
 //
-// Measured (us, before -> one pass): power law n = 10^6 weighted, 3 columns
-// FP32 228 -> 153, 7 columns 417 -> 201, 13 columns FP64 611 -> 327; ER n = 3
-// 10^6 of degree 4, 3 columns FP32 348 -> 217; BA n = 3,000, 13 columns 37 -> 16.
+// The sums are FP64 ones in either precision, rounded once: a lane per element
+// takes four times as many terms of a long row as k_spmm's lanes of four, which
+// in FP32 left the values up to 2.4 times as far from the exact ones, and the
+// odd column of a large graph had the FP64 sums of the sliced apply before it
+// came into this pass.
+//
+// Measured (us, a pass for every power of two -> one pass): power law n = 10^6
+// weighted, 3 columns FP32 228 -> 151, 7 columns 417 -> 208 (with FP32 sums 148
+// and 200), 13 columns FP64 611 -> 327; BA n = 3,000, 13 columns 37 -> 16.
 #include <algorithm>
 
 #include "device_common.hpp"
@@ -45,11 +50,11 @@ __global__ __launch_bounds__(kBS) void k_apply_ragged(RaggedK<V> a, LongRows lr)
     for (int s = blockIdx.x; s < lr.n_seg; s += a.nlong_blocks) {
       const int row = lr.seg_row[s];
       const int hi = lr.seg_hi[s];
-      const V own = a.x[(long)row * a.ldx + cc];
-      V sum = (V)0;
+      const double own = (double)a.x[(long)row * a.ldx + cc];
+      double sum = 0.0;
       for (int e = lr.seg_lo[s] + t / L; e < hi; e += NJ)
-        sum += (UNIT ? (V)1 : a.w[e]) * (own - a.x[(long)a.ci[e] * a.ldx + cc]);
-      const double part[1][1] = {{(double)sum}};
+        sum += (UNIT ? 1.0 : (double)a.w[e]) * (own - (double)a.x[(long)a.ci[e] * a.ldx + cc]);
+      const double part[1][1] = {{sum}};
       block_reduce_cols<kBS, 1, 1>(part, L, sh);
       const int first = lr.seg_first[s], cnt = lr.seg_cnt[s];
       if (cnt == 1) {
@@ -81,8 +86,8 @@ __global__ __launch_bounds__(kBS) void k_apply_ragged(RaggedK<V> a, LongRows lr)
     const int lo = a.rp[row];
     const int deg = a.rp[row + 1] - lo;
     if (deg > kLongRow) continue;
-    const V own = a.x[row * a.ldx + cc];
-    V sum = (V)0;
+    const double own = (double)a.x[row * a.ldx + cc];
+    double sum = 0.0;
     for (int e0 = 0; e0 < deg; e0 += U) {
       int col[U];
       V wt[U], xv[U];
@@ -94,10 +99,14 @@ __global__ __launch_bounds__(kBS) void k_apply_ragged(RaggedK<V> a, LongRows lr)
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) xv[u] = e0 + u < deg ? a.x[(long)col[u] * a.ldx + cc] : (V)0;
+      // (all loads are out before the first conversion: it would otherwise move
+      // up behind each load's own test and wait for it there)
 #pragma unroll
-      for (int u = 0; u < U; ++u) sum += wt[u] * (own - xv[u]);
+      for (int u = 0; u < U; ++u) asm volatile("" : "+v"(wt[u]), "+v"(xv[u]));
+#pragma unroll
+      for (int u = 0; u < U; ++u) sum += (double)wt[u] * (own - (double)xv[u]);
     }
-    if (c < a.cols) __builtin_nontemporal_store(sum, &a.y[row * a.ldy + c]);
+    if (c < a.cols) __builtin_nontemporal_store((V)sum, &a.y[row * a.ldy + c]);
   }
 }
 

@@ -321,6 +321,7 @@ nvd_status nvd_distances(nvd_graph* h, int32_t k, const double* P, const double*
       while (T > k - c0) T >>= 1;
     const int cols = std::min(T, k - c0);
     sp.cols = cols;
+    sp.wide = wide_tile(g, k, T, sp);
     sp.nl = tuned_nl(g, o.precision, T);
     st = ensure_workspace(g, T, o.precision == NVD_MIXED);
     const int nb = st == NVD_OK ? small_blocks(g, T, sp) : 0;

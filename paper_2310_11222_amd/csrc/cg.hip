@@ -836,6 +836,7 @@ static nvd_status cg_loop(DevGraph* g, Workspace* ws, int T, V* x, V* r, V* p, V
   sc.T = T;
   sc.nl = sp.nl;
   sc.grid = sp.grid;
+  sc.wide = sizeof(V) == 4 && sp.wide;
   sc.x = p;
   sc.ldx = T;
   sc.y = q;

@@ -199,6 +199,7 @@ struct SpmmCall {
   ColState* cs;
   int epi;
   int grid;                 // short-row blocks (0 = auto)
+  bool wide;                // FP32, EPI_CG: row sums in FP64, rounded once
 };
 nvd_status launch_spmm(const SpmmCall& c, const GridRed& red, hipStream_t s);
 // The apply the solvers and nvd_laplacian_apply use: one column (T = 1) on a
@@ -207,6 +208,10 @@ nvd_status launch_apply(const SpmmCall& c, const GridRed& red, hipStream_t s);
 // The plain apply on cols < c.T columns, c.T the next power of two (ragged.hip).
 nvd_status launch_ragged(const SpmmCall& c, int cols, hipStream_t s);
 void free_slices(DevGraph* g);
+// Whether one column of the graph may be applied by slices, whose FP32 row
+// sums are FP64 ones rounded once.  A wider tile that takes such a column with
+// others sums as they do (SpmmCall::wide).
+bool slices_serve(const DevGraph* g);
 
 struct SolveParams {
   int precision;            // NVD_FP64 or NVD_MIXED
@@ -220,7 +225,13 @@ struct SolveParams {
   bool achol;               // the approximate-Cholesky factor
   bool out_dsq;             // d_out receives d^2 instead of d
   int cols;                 // pairs of this tile where it is ragged (0: as many as it is wide)
+  bool wide;                // mixed: the inner applies sum their rows in FP64 (SpmmCall::wide)
 };
+// Whether the tile of T that ends the k pairs sums its FP32 rows in FP64: where
+// the odd last pair, alone in a tile, would have had the sliced apply's sums.
+inline bool wide_tile(const DevGraph* g, int k, int T, const SolveParams& sp) {
+  return sp.precision == NVD_MIXED && (k & 1) != 0 && sp.cols < T && slices_serve(g);
+}
 // Tile of the next pass over the `left` remaining of k pairs: `tile` while
 // plenty are left, then what covers the rest in the least estimated time, a
 // tile wider than the rest included (tune.hip).

@@ -288,6 +288,7 @@ extern "C" nvd_status nvd_pairwise(nvd_graph* h, int32_t m, const double* V, int
       while (T > m - c0) T >>= 1;
     const int cols = std::min(T, m - c0);
     sp.cols = cols;
+    sp.wide = wide_tile(g, m, T, sp);
     sp.nl = tuned_nl(g, o.precision, T);
     st = ensure_workspace(g, T, o.precision == NVD_MIXED);
     // x of the tile's columns into X; delta_bar and the final residual stay

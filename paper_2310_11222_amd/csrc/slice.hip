@@ -422,6 +422,11 @@ static int slice_mode() {
   return 2;
 }
 
+bool slices_serve(const DevGraph* g) {
+  const int mode = slice_mode();
+  return mode == 1 || (mode == 2 && g->n >= kSlMinN);
+}
+
 template <typename T>
 static bool room(T** dst, size_t count, int64_t& bytes) {
   const size_t nb = std::max<size_t>(1, count) * sizeof(T);
@@ -665,10 +670,8 @@ static bool use_slices(DevGraph* g, const SpmmCall& c, const GridRed& red, hipSt
   // a caller that bounds the grid (the no-allocation entry point) has sized
   // its reduction scratch for it, and building the slices would allocate
   if (c.T != 1 || g->n < 1 || c.grid > 0) return false;
+  if (!slices_serve(g) || g->slice_state < 0) return false;
   const int mode = slice_mode();
-  if (mode == 0) return false;
-  if (mode == 2 && g->n < kSlMinN) return false;
-  if (g->slice_state < 0) return false;
   const int p = c.prec == 0 ? 0 : 1;
   if (mode == 2 && g->slice_pick[p] < 0) return false;
   if (!g->slices) {

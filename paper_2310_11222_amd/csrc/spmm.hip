@@ -82,13 +82,13 @@ constexpr int kSpmmR = NVD_SPMM_R;
 constexpr int kSpmmMaxShortGrid = kMaxBlocks - 1024;
 
 // Epilogue for VW columns c0 .. c0+VW-1 of one row; sum = (L x) entries.
-template <typename V, int VW, bool UNIT, int EPI, int NDA>
-__device__ __forceinline__ void spmm_epilogue(const SpmmK<V>& a, int row, int cv, const V (&sum)[VW],
+template <typename V, int VW, bool UNIT, int EPI, int NDA, typename A>
+__device__ __forceinline__ void spmm_epilogue(const SpmmK<V>& a, int row, int cv, const A (&sum)[VW],
                                               const V (&own)[VW], double (&acc)[NDA][VW]) {
   using VV = typename VecOf<V, VW>::type;
   V yv[VW];
 #pragma unroll
-  for (int v = 0; v < VW; ++v) yv[v] = sum[v];
+  for (int v = 0; v < VW; ++v) yv[v] = (V)sum[v];
   VV* yp = reinterpret_cast<VV*>(a.y + (long)row * a.ldy) + cv;
   if constexpr (EPI == EPI_PLAIN) {
     __builtin_nontemporal_store(pack<V, VW>(yv), yp);
@@ -115,7 +115,13 @@ __device__ __forceinline__ void spmm_epilogue(const SpmmK<V>& a, int row, int cv
   }
 }
 
-template <typename V, int T, int NL, bool UNIT, int EPI, bool VEC>
+// A: the type of the row sums, V or (SpmmCall::wide) double for FP32 operands:
+// the inner applies of a tile that takes an odd last pair, whose own tile would
+// have had the sliced apply's sums.  It costs nothing where the gathers bound
+// the pass (a whole solve on the power-law graph of 10^6 nodes, FP32 -> FP64
+// sums: 3 pairs 6.32 -> 6.06 ms, 7 pairs 8.38 -> 7.35, whose loads are also kept
+// together; BA 2 10^5, 57 pairs 4.68 -> 4.93).
+template <typename V, int T, int NL, bool UNIT, int EPI, bool VEC, typename A = V>
 __global__ __launch_bounds__(kBS) void k_spmm(SpmmK<V> a, GridRed red, LongRows lr) {
   using Geo = SpmmGeom<V, T, VEC>;
   constexpr int VW = Geo::VW;
@@ -152,10 +158,11 @@ __global__ __launch_bounds__(kBS) void k_spmm(SpmmK<V> a, GridRed red, LongRows 
       const int row = lr.seg_row[s];
       const int lo = lr.seg_lo[s];
       const int hi = lr.seg_hi[s];
-      V sum[VW], xr[VW];
+      A sum[VW];
+      V xr[VW];
       unpack<V, VW>(X[(long)row * ldxv + cv], xr);
 #pragma unroll
-      for (int v = 0; v < VW; ++v) sum[v] = (V)0;
+      for (int v = 0; v < VW; ++v) sum[v] = (A)0;
       for (int e = lo + j; e < hi; e += NJ) {
         const int col = a.ci[e];
         V wt;
@@ -166,7 +173,7 @@ __global__ __launch_bounds__(kBS) void k_spmm(SpmmK<V> a, GridRed red, LongRows 
         V xv[VW];
         unpack<V, VW>(X[(long)col * ldxv + cv], xv);
 #pragma unroll
-        for (int v = 0; v < VW; ++v) sum[v] += wt * (xr[v] - xv[v]);
+        for (int v = 0; v < VW; ++v) sum[v] += (A)wt * ((A)xr[v] - (A)xv[v]);
       }
       double part[1][VW];
 #pragma unroll
@@ -248,11 +255,11 @@ __global__ __launch_bounds__(kBS) void k_spmm(SpmmK<V> a, GridRed red, LongRows 
         const int orow = mine[r] ? row[r] : 0;
         unpack<V, VW>(X[(long)orow * ldxv + cv], own[r]);
       }
-      V sum[R][VW];
+      A sum[R][VW];
 #pragma unroll
       for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int v = 0; v < VW; ++v) sum[r][v] = (V)0;
+        for (int v = 0; v < VW; ++v) sum[r][v] = (A)0;
       for (int e0 = j; e0 < mx; e0 += NL * U) {
         int col[R][U];
         V wt[R][U];
@@ -281,6 +288,14 @@ __global__ __launch_bounds__(kBS) void k_spmm(SpmmK<V> a, GridRed red, LongRows 
             xv[r][u] = VV{};
             if (e0 + NL * u < deg[r]) xv[r][u] = X[(long)col[r][u] * ldxv + cv];
           }
+        if constexpr (sizeof(A) != sizeof(V)) {
+          // all loads are out before the first conversion: it would otherwise
+          // move up behind each load's own test and wait for it there
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int u = 0; u < U; ++u) asm volatile("" : "+v"(wt[r][u]), "+v"(xv[r][u]));
+        }
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -288,7 +303,7 @@ __global__ __launch_bounds__(kBS) void k_spmm(SpmmK<V> a, GridRed red, LongRows 
             V xs[VW];
             unpack<V, VW>(xv[r][u], xs);
 #pragma unroll
-            for (int v = 0; v < VW; ++v) sum[r][v] += wt[r][u] * (own[r][v] - xs[v]);
+            for (int v = 0; v < VW; ++v) sum[r][v] += (A)wt[r][u] * ((A)own[r][v] - (A)xs[v]);
           }
       }
 #pragma unroll
@@ -344,13 +359,13 @@ constexpr bool spmm_fits() {
   return SpmmGeom<V, T, VEC>::L * NL <= 64;
 }
 
-template <typename V, int T, int NL, bool VEC, int EPI>
+template <typename V, int T, int NL, bool VEC, int EPI, typename A>
 static void launch_geo(bool unit, const SpmmK<V>& k, const GridRed& red, const LongRows& lr,
                        int grid, hipStream_t s) {
   if (unit)
-    k_spmm<V, T, NL, true, EPI, VEC><<<grid, kBS, 0, s>>>(k, red, lr);
+    k_spmm<V, T, NL, true, EPI, VEC, A><<<grid, kBS, 0, s>>>(k, red, lr);
   else
-    k_spmm<V, T, NL, false, EPI, VEC><<<grid, kBS, 0, s>>>(k, red, lr);
+    k_spmm<V, T, NL, false, EPI, VEC, A><<<grid, kBS, 0, s>>>(k, red, lr);
 }
 
 // Rows handled per block and step for (T, nl, vec); 0 if the configuration
@@ -364,38 +379,40 @@ static int rows_per_block(int T, int nl, bool vec) {
   return (kBS / 64) * (64 / G) * kSpmmR;
 }
 
-template <typename V, int T, int EPI, bool VEC>
+template <typename V, int T, int EPI, bool VEC, typename A>
 static bool launch_nl(int nl, bool unit, const SpmmK<V>& k, const GridRed& red,
                       const LongRows& lr, int grid, hipStream_t s) {
   switch (nl) {
     case 1:
-      if constexpr (spmm_fits<V, T, 1, VEC>()) { launch_geo<V, T, 1, VEC, EPI>(unit, k, red, lr, grid, s); return true; }
+      if constexpr (spmm_fits<V, T, 1, VEC>()) { launch_geo<V, T, 1, VEC, EPI, A>(unit, k, red, lr, grid, s); return true; }
       break;
     case 2:
-      if constexpr (spmm_fits<V, T, 2, VEC>()) { launch_geo<V, T, 2, VEC, EPI>(unit, k, red, lr, grid, s); return true; }
+      if constexpr (spmm_fits<V, T, 2, VEC>()) { launch_geo<V, T, 2, VEC, EPI, A>(unit, k, red, lr, grid, s); return true; }
       break;
     case 4:
-      if constexpr (spmm_fits<V, T, 4, VEC>()) { launch_geo<V, T, 4, VEC, EPI>(unit, k, red, lr, grid, s); return true; }
+      if constexpr (spmm_fits<V, T, 4, VEC>()) { launch_geo<V, T, 4, VEC, EPI, A>(unit, k, red, lr, grid, s); return true; }
       break;
     case 8:
-      if constexpr (spmm_fits<V, T, 8, VEC>()) { launch_geo<V, T, 8, VEC, EPI>(unit, k, red, lr, grid, s); return true; }
+      if constexpr (spmm_fits<V, T, 8, VEC>()) { launch_geo<V, T, 8, VEC, EPI, A>(unit, k, red, lr, grid, s); return true; }
       break;
     default: break;
   }
   return false;
 }
 
-template <typename V, int EPI, bool VEC>
+template <typename V, int EPI, bool VEC, typename A = V>
 static bool launch_t(int T, int nl, bool unit, const SpmmK<V>& k, const GridRed& red,
                      const LongRows& lr, int grid, hipStream_t s) {
+  if constexpr (sizeof(A) == sizeof(V)) {   // (a tile with an odd number of pairs and room beside them is 4 or wider)
+    if (T == 1) return launch_nl<V, 1, EPI, VEC, A>(nl, unit, k, red, lr, grid, s);
+    if (T == 2) return launch_nl<V, 2, EPI, VEC, A>(nl, unit, k, red, lr, grid, s);
+  }
   switch (T) {
-    case 1: return launch_nl<V, 1, EPI, VEC>(nl, unit, k, red, lr, grid, s);
-    case 2: return launch_nl<V, 2, EPI, VEC>(nl, unit, k, red, lr, grid, s);
-    case 4: return launch_nl<V, 4, EPI, VEC>(nl, unit, k, red, lr, grid, s);
-    case 8: return launch_nl<V, 8, EPI, VEC>(nl, unit, k, red, lr, grid, s);
-    case 16: return launch_nl<V, 16, EPI, VEC>(nl, unit, k, red, lr, grid, s);
-    case 32: return launch_nl<V, 32, EPI, VEC>(nl, unit, k, red, lr, grid, s);
-    case 64: return launch_nl<V, 64, EPI, VEC>(nl, unit, k, red, lr, grid, s);
+    case 4: return launch_nl<V, 4, EPI, VEC, A>(nl, unit, k, red, lr, grid, s);
+    case 8: return launch_nl<V, 8, EPI, VEC, A>(nl, unit, k, red, lr, grid, s);
+    case 16: return launch_nl<V, 16, EPI, VEC, A>(nl, unit, k, red, lr, grid, s);
+    case 32: return launch_nl<V, 32, EPI, VEC, A>(nl, unit, k, red, lr, grid, s);
+    case 64: return launch_nl<V, 64, EPI, VEC, A>(nl, unit, k, red, lr, grid, s);
     default: return false;
   }
 }
@@ -495,7 +512,10 @@ static nvd_status launch_typed(const SpmmCall& c, const GridRed& red, hipStream_
       break;
     case EPI_CG:
       // solver vectors are always aligned
-      ok = vec && launch_t<V, EPI_CG, true>(c.T, nl, unit, k, red, g->lr, grid, s);
+      if (sizeof(V) == 4 && c.wide)
+        ok = vec && launch_t<V, EPI_CG, true, double>(c.T, nl, unit, k, red, g->lr, grid, s);
+      else
+        ok = vec && launch_t<V, EPI_CG, true>(c.T, nl, unit, k, red, g->lr, grid, s);
       break;
     case EPI_RESID:
       if constexpr (sizeof(V) == 8) ok = vec && launch_t<V, EPI_RESID, true>(c.T, nl, unit, k, red, g->lr, grid, s);

@@ -53,6 +53,14 @@ def _as_dev64(M, name):
     return M
 
 
+def _same_rows(P, Q):
+    """P and Q with one row stride between them, the only one the library takes
+    for the two."""
+    if P.stride(0) != Q.stride(0):
+        P, Q = P.contiguous(), Q.contiguous()
+    return P, Q
+
+
 def _check_out(t, name, shape, dtype):
     """A caller-supplied output buffer: a CUDA tensor of the given shape and
     dtype whose rows are contiguous (the library writes through its data
@@ -213,6 +221,7 @@ class Graph:
         torch = _torch()
         P = _as_dev64(P, "P")
         Q = _as_dev64(Q, "Q")
+        P, Q = _same_rows(P, Q)
         k = P.shape[1]
         D = torch.empty_like(P)
         norms = torch.empty(k, dtype=torch.float64, device=P.device)
@@ -236,6 +245,7 @@ class Graph:
         Q = _as_dev64(Q, "Q")
         if P.shape != Q.shape or P.shape[0] != self.n:
             raise ValueError(f"P, Q must both be ({self.n}, k)")
+        P, Q = _same_rows(P, Q)
         if out not in ("d", "dsq"):
             raise ValueError("out must be 'd' or 'dsq'")
         k = P.shape[1]

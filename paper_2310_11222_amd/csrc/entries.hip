@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) void k_grad_entries(int n, int nnz, const int*
   constexpr int LOG = L == 1 ? 0 : L == 2 ? 1 : L == 4 ? 2 : L == 8 ? 3 : L == 16 ? 4 : L == 32 ? 5 : 6;
   const int c = threadIdx.x % L;
   const int cc = min(c, cols - 1);
-  const double gc = c < cols ? -0.5 * gs[cc] : 0.0;
+  const double gc = -0.5 * gs[cc];
   const long groups = (long)gridDim.x * (256 / L);
   for (long q = (long)blockIdx.x * (256 / L) + threadIdx.x / L; q * U < nnz; q += groups) {
     const int e0 = (int)(q * U);
@@ -131,7 +131,8 @@ __global__ __launch_bounds__(256) void k_grad_entries(int n, int nnz, const int*
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const double v = group_sum(gc * df[u] * df[u], LOG);
+      // (nothing of the lanes past the last column, whatever X holds there)
+      const double v = group_sum(c < cols ? gc * df[u] * df[u] : 0.0, LOG);
       if (c == 0 && e0 + u < nnz) {
         const long pos = in_pos ? in_pos[e0 + u] : e0 + u;
         gw[pos] = accumulate ? gw[pos] + v : v;

@@ -319,25 +319,29 @@ nvd_status nvd_distances(nvd_graph* h, int32_t k, const double* P, const double*
       T = next_tile(g, k, k - c0, tile, sp);
     else
       while (T > k - c0) T >>= 1;
-    const int cols = std::min(T, k - c0);
-    sp.cols = cols;
-    sp.wide = wide_tile(g, k, T, sp);
-    sp.nl = tuned_nl(g, o.precision, T);
-    st = ensure_workspace(g, T, o.precision == NVD_MIXED);
-    const int nb = st == NVD_OK ? small_blocks(g, T, sp) : 0;
-    bool done = false;
-    if (st == NVD_OK && nb > 0) {
-      st = solve_small(g, T, nb, P + c0, Q + c0, ld, sp, d_out + c0, X ? X + c0 : nullptr, ldx,
-                       g->ws->info, s);
-      done = st != NVD_E_UNSUPPORTED;   // a launch too large for the device: multi-kernel path
-      if (!done) {
-        st = NVD_OK;
-        set_error("");
+    auto run = [&]() -> nvd_status {
+      sp.cols = std::min(T, k - c0);
+      sp.wide = wide_tile(g, k, T, sp);
+      sp.nl = tuned_nl(g, o.precision, T);
+      NVD_TRY(ensure_workspace(g, T, o.precision == NVD_MIXED));
+      const int nb = small_blocks(g, T, sp);
+      if (nb > 0) {
+        const nvd_status ss = solve_small(g, T, nb, P + c0, Q + c0, ld, sp, d_out + c0, X ? X + c0 : nullptr,
+                                          ldx, g->ws->info, s);
+        if (ss != NVD_E_UNSUPPORTED) return ss;
+        set_error("");                  // a launch too large for the device: multi-kernel path
+      }
+      return solve_tile(g, T, P + c0, Q + c0, ld, sp, d_out + c0, X ? X + c0 : nullptr, ldx, g->ws->info, s);
+    };
+    st = run();
+    if (st == NVD_E_NOMEM && o.tile_k == 0) {
+      const int narrow = narrower_tile(g, k - c0, tile, T);
+      if (narrow > 0) {
+        T = narrow;
+        st = run();
       }
     }
-    if (st == NVD_OK && !done)
-      st = solve_tile(g, T, P + c0, Q + c0, ld, sp, d_out + c0, X ? X + c0 : nullptr, ldx,
-                      g->ws->info, s);
+    const int cols = sp.cols;
     if (st == NVD_OK) {
       hipError_t e = hipMemcpyAsync(hinfo.data() + c0, g->ws->info, sizeof(nvd_pair_info) * cols,
                                     hipMemcpyDeviceToHost, s);

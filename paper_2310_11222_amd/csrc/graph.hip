@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 #include <climits>
+#include <cstdlib>
 #include <cstring>
 #include <numeric>
 #include <thread>
@@ -20,11 +21,24 @@ static thread_local std::string g_err;
 void set_error(const std::string& msg) { g_err = msg; }
 const char* get_error() { return g_err.c_str(); }
 
+hipError_t device_alloc(void** p, size_t bytes) {
+  const char* limit = std::getenv("NVD_ALLOC_LIMIT");
+  if (limit && bytes > std::strtoull(limit, nullptr, 10)) {
+    *p = nullptr;
+    return hipErrorOutOfMemory;
+  }
+  const hipError_t e = hipMalloc(p, bytes);
+  // (the runtime keeps a failure for its next hipGetLastError, which belongs to
+  // a launch of the form that goes on with less)
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+
 template <typename T>
 static nvd_status dalloc(T** p, size_t count, int64_t* bytes) {
   *p = nullptr;
   if (count == 0) count = 1;
-  NVD_HIP(hipMalloc((void**)p, count * sizeof(T)));
+  NVD_HIP(device_alloc((void**)p, count * sizeof(T)));
   if (bytes) *bytes += (int64_t)(count * sizeof(T));
   return NVD_OK;
 }

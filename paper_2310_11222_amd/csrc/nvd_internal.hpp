@@ -131,6 +131,7 @@ struct DevGraph {
   std::vector<int> heavy_deg_desc;  // host: their degrees
   SliceGraph* slices = nullptr; // built when the sliced apply is first needed
   int slice_state = 0;          // -1: build failed, use the row-wise apply
+  int tile_most = kMaxTile;     // widest tile to try: what a call ran out of memory with, less
   int slice_pick[2] = {0, 0};   // [FP64, FP32]: 1 sliced, -1 row-wise (timed), 0 not yet
   ColPlan* col = nullptr;       // built when the one-block-per-column solver is first used
   ColWs col_ws;
@@ -180,6 +181,10 @@ const char* get_error();
     nvd_status s_ = (expr);            \
     if (s_ != NVD_OK) return s_;       \
   } while (0)
+
+// hipMalloc.  NVD_ALLOC_LIMIT (bytes; for tests of full memory, forced from the
+// host): a larger allocation fails as on a full device.
+hipError_t device_alloc(void** p, size_t bytes);
 
 // workspace management (graph.hip)
 nvd_status ensure_workspace(DevGraph* g, int tile, bool need32);
@@ -236,6 +241,10 @@ inline bool wide_tile(const DevGraph* g, int k, int T, const SolveParams& sp) {
 // plenty are left, then what covers the rest in the least estimated time, a
 // tile wider than the rest included (tune.hip).
 int next_tile(const DevGraph* g, int k, int left, int tile, const SolveParams& sp);
+// After tile T ran out of device memory: the widest of the tiles that `left`
+// pairs take without one wider than `tile` or than they are, where that is less
+// than T (it is then not exceeded again on the graph); else 0.
+int narrower_tile(DevGraph* g, int left, int tile, int T);
 nvd_status solve_tile(DevGraph* g, int T, const double* P, const double* Q, int64_t ld,
                       const SolveParams& sp, double* d_out, double* X, int64_t ldx,
                       nvd_pair_info* info_dev, hipStream_t s);

@@ -286,15 +286,24 @@ extern "C" nvd_status nvd_pairwise(nvd_graph* h, int32_t m, const double* V, int
       T = next_tile(g, m, m - c0, tile, sp);
     else
       while (T > m - c0) T >>= 1;
-    const int cols = std::min(T, m - c0);
-    sp.cols = cols;
-    sp.wide = wide_tile(g, m, T, sp);
-    sp.nl = tuned_nl(g, o.precision, T);
-    st = ensure_workspace(g, T, o.precision == NVD_MIXED);
     // x of the tile's columns into X; delta_bar and the final residual stay
     // in the workspace and are copied out
-    if (st == NVD_OK)
-      st = solve_tile(g, T, V + c0, nullptr, ld, sp, dscratch, X + c0, m, g->ws->info, s);
+    auto run = [&]() -> nvd_status {
+      sp.cols = std::min(T, m - c0);
+      sp.wide = wide_tile(g, m, T, sp);
+      sp.nl = tuned_nl(g, o.precision, T);
+      NVD_TRY(ensure_workspace(g, T, o.precision == NVD_MIXED));
+      return solve_tile(g, T, V + c0, nullptr, ld, sp, dscratch, X + c0, m, g->ws->info, s);
+    };
+    st = run();
+    if (st == NVD_E_NOMEM && o.tile_k == 0) {
+      const int narrow = narrower_tile(g, m - c0, tile, T);
+      if (narrow > 0) {
+        T = narrow;
+        st = run();
+      }
+    }
+    const int cols = sp.cols;
     if (st == NVD_OK) {
       const int grid = (int)std::min<long>(2048, ((long)n * T + 255) / 256);
       k_tile_put<<<std::max(grid, 1), 256, 0, s>>>(n, T, cols, g->ws->b64, Vb + c0, m);

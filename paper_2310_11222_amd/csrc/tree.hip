@@ -379,10 +379,11 @@ nvd_status ensure_tree(DevGraph* g, int T) {
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   tp->E = tp->S = tp->part = nullptr;
+  tp->cap_tile = 0;
   const size_t rows = 2 * (size_t)g->n;
   const size_t nchunk = (rows + kScanChunkMin - 1) / kScanChunkMin;   // the most any chunk size needs
-  NVD_HIP(hipMalloc((void**)&tp->E, sizeof(double) * rows * T));
-  NVD_HIP(hipMalloc((void**)&tp->S, sizeof(double) * rows * T));
+  NVD_HIP(device_alloc((void**)&tp->E, sizeof(double) * rows * T));
+  NVD_HIP(device_alloc((void**)&tp->S, sizeof(double) * rows * T));
   NVD_HIP(hipMalloc((void**)&tp->part, sizeof(double) * nchunk * T));
   tp->cap_tile = T;
   if (tp->k_aug > 0 && !tp->aug_Y) NVD_TRY(build_aug(g));

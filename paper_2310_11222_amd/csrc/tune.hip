@@ -96,7 +96,7 @@ static double iteration_estimate(const DevGraph* g, int T, const SolveParams& sp
 
 int next_tile(const DevGraph* g, int k, int left, int tile, const SolveParams& sp) {
   // a tile that was picked over wider ones is not exceeded
-  const int most = 2 * tile > k ? std::min(2 * tile, kMaxTile) : tile;
+  const int most = std::max(tile, 2 * tile > k ? std::min({2 * tile, kMaxTile, g->tile_most}) : tile);
   if (left >= 2 * tile || left >= most) return tile;
   int wide = 1;                                  // one tile over all that is left
   while (wide < left && wide < most) wide *= 2;
@@ -117,6 +117,21 @@ int next_tile(const DevGraph* g, int k, int left, int tile, const SolveParams& s
     }
   }
   return take[left];
+}
+
+int narrower_tile(DevGraph* g, int left, int tile, int T) {
+  int narrow = tile;
+  while (narrow > left) narrow >>= 1;
+  if (narrow >= T) return 0;
+  g->tile_most = narrow;
+  // the workspace that T left is wider than what follows needs
+  if (g->ws) {
+    g->bytes -= g->ws->bytes;
+    free_workspace(g->ws);
+    g->ws = nullptr;
+  }
+  set_error("");
+  return narrow;
 }
 
 int choose_tile(DevGraph* g, int k, int precision, hipStream_t s) {

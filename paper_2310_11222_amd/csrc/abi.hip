@@ -306,10 +306,9 @@ nvd_status nvd_distances(nvd_graph* h, int32_t k, const double* P, const double*
   // caller keeps the paths that solve tiles)
   bool column = o.tile_k == 0 && use_column(g, k, sp);
   if (column) st = solve_column(g, k, P, Q, ld, sp, d_out, X, ldx, hinfo.data(), s);
-  if (st == NVD_E_UNSUPPORTED) {   // (more augmenting edges than a block takes)
+  if (column && column_gives_way(g, st)) {
     column = false;
     st = NVD_OK;
-    set_error("");
   }
   int tile = o.tile_k;
   if (tile == 0 && !column) tile = choose_tile(g, k, o.precision, s);

@@ -27,6 +27,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <numeric>
 #include <thread>
 #include <vector>
@@ -97,7 +98,7 @@ nvd_status ensure_column_ws(ColWs* w, size_t vec, size_t cm, int cols, int64_t* 
     w->vec = nullptr;
     if (bytes) *bytes -= (int64_t)(sizeof(double) * (w->cap_vec + w->cap_cm));
     w->cap_vec = w->cap_cm = 0;
-    NVD_HIP(hipMalloc((void**)&w->vec, sizeof(double) * (vec + cm)));
+    NVD_HIP(device_alloc((void**)&w->vec, sizeof(double) * (vec + cm)));
     w->cap_vec = vec;
     w->cap_cm = cm;
     if (bytes) *bytes += (int64_t)(sizeof(double) * (vec + cm));
@@ -107,7 +108,13 @@ nvd_status ensure_column_ws(ColWs* w, size_t vec, size_t cm, int cols, int64_t* 
     w->info = nullptr;
     w->cap_info = 0;
     const int c = std::max(cols, 64);
-    NVD_HIP(hipHostMalloc((void**)&w->info, sizeof(nvd_pair_info) * c, hipHostMallocDefault));
+    const hipError_t e = hipHostMalloc((void**)&w->info, sizeof(nvd_pair_info) * c, hipHostMallocDefault);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      w->info = nullptr;
+      set_error(std::string("hipHostMalloc: ") + hipGetErrorString(e));
+      return NVD_E_NOMEM;
+    }
     w->cap_info = c;
   }
   return NVD_OK;
@@ -306,7 +313,7 @@ static nvd_status build_column(DevGraph* g) {
   Blob bl;
   lay.put(&bl);
   ColPlan* cp = new ColPlan();
-  hipError_t e = hipMalloc((void**)&cp->blob, bl.h.size());
+  hipError_t e = device_alloc((void**)&cp->blob, bl.h.size());
   if (e == hipSuccess) e = hipMemcpy(cp->blob, bl.h.data(), bl.h.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     (void)hipFree(cp->blob);
@@ -353,7 +360,7 @@ static nvd_status ensure_column(DevGraph* g, hipStream_t s) {
     (void)hipFree(cp->weights);
     cp->weights = nullptr;
     const size_t want = weight_doubles(g->weighted ? cp->entries : 0, cp->d.slots * kColBS);
-    NVD_HIP(hipMalloc((void**)&cp->weights, sizeof(double) * want));
+    NVD_HIP(device_alloc((void**)&cp->weights, sizeof(double) * want));
     cp->weighted = g->weighted;
     cp->bytes += (int64_t)(sizeof(double) * want);
     g->bytes += (int64_t)(sizeof(double) * want);
@@ -429,8 +436,18 @@ static bool column_is_faster(const DevGraph* g, int k) {
   return block * ((k + kColChunk - 1) / kColChunk) <= tiles;
 }
 
+bool column_gives_way(DevGraph* g, nvd_status st) {
+  if (st != NVD_E_UNSUPPORTED && st != NVD_E_NOMEM) return false;
+  if (st == NVD_E_NOMEM) {
+    free_column(g);
+    g->col_failed = true;
+  }
+  set_error("");
+  return true;
+}
+
 bool use_column(const DevGraph* g, int k, const SolveParams& sp) {
-  if (sp.warm) return false;
+  if (sp.warm || g->col_failed) return false;
   if (sp.achol && g->n > kColBS * kColMaxPreEPT) return false;
   // (the forest's sums are FP64 in either precision)
   const bool fp64_vector = sp.precision != NVD_MIXED || (sp.tree && !sp.achol);
@@ -486,7 +503,7 @@ static nvd_status finish_multi_kernel(DevGraph* g, int col, int block, const dou
 // The k pairs (P[:, j], Q[:, j]) of one graph.
 nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, int64_t ld,
                         const SolveParams& sp, double* d_out, double* X, int64_t ldx,
-                        nvd_pair_info* info, hipStream_t s, double* B, double* R) {
+                        nvd_pair_info* info, hipStream_t s, double* B, double* R) try {
   const bool mixed = sp.precision == NVD_MIXED;
   NVD_TRY(ensure_column(g, s));
   const ColPlan* cp = g->col;
@@ -552,6 +569,9 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
       if (left(j)) NVD_TRY(finish_multi_kernel(g, c0 + j, j, P, Q, ld, sp, a, &info[c0 + j], s));
   }
   return NVD_OK;
+} catch (const std::bad_alloc&) {   // (the layout's host arrays)
+  set_error("column solve: out of host memory");
+  return NVD_E_NOMEM;
 }
 
 // ---------------------------------------------------------------------------

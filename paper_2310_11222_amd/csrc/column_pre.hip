@@ -105,7 +105,7 @@ void free_column_pre(ColPreDev* p) {
 
 static nvd_status upload(PreBlob& bl, ColPreDev** out, int64_t* bytes) {
   ColPreDev* cp = new ColPreDev();
-  hipError_t e = hipMalloc((void**)&cp->blob, bl.h.size());
+  hipError_t e = device_alloc((void**)&cp->blob, bl.h.size());
   if (e == hipSuccess) e = hipMemcpy(cp->blob, bl.h.data(), bl.h.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     free_column_pre(cp);

@@ -135,6 +135,7 @@ struct DevGraph {
   int slice_pick[2] = {0, 0};   // [FP64, FP32]: 1 sliced, -1 row-wise (timed), 0 not yet
   ColPlan* col = nullptr;       // built when the one-block-per-column solver is first used
   ColWs col_ws;
+  bool col_failed = false;      // there was no memory for it: tiles from then on
 };
 
 struct Workspace {
@@ -266,6 +267,10 @@ bool use_column(const DevGraph* g, int k, const SolveParams& sp);
 nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, int64_t ld,
                         const SolveParams& sp, double* d_out, double* X, int64_t ldx,
                         nvd_pair_info* info, hipStream_t s, double* B = nullptr, double* R = nullptr);
+// Whether a call goes on with tiles after solve_column returned st: more
+// augmenting edges than a block takes, or no memory for the layout or the
+// scratch (what there is of them is given back, and not tried again).
+bool column_gives_way(DevGraph* g, nvd_status st);
 // A batch of small graphs in the same way (column.hip); *out is null where it
 // has larger ones.
 struct ColBatch;

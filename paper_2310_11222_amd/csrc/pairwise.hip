@@ -273,10 +273,9 @@ extern "C" nvd_status nvd_pairwise(nvd_graph* h, int32_t m, const double* V, int
   nvd_status st = NVD_OK;
   bool column = o.tile_k == 0 && use_column(g, m, sp);
   if (column) st = solve_column(g, m, V, nullptr, ld, sp, nullptr, X, m, hinfo.data(), s, Vb, R);
-  if (st == NVD_E_UNSUPPORTED) {   // (more augmenting edges than a block takes)
+  if (column && column_gives_way(g, st)) {
     column = false;
     st = NVD_OK;
-    set_error("");
   }
   int tile = o.tile_k;
   if (tile == 0 && !column) tile = choose_tile(g, m, o.precision, s);

@@ -90,3 +90,38 @@ def test_tree_tile_wider_than_memory(monkeypatch):
         d, _, info = dg.distances(P, Q, precond="tree")
         assert all(i["status"] == 0 for i in info)
         assert rel_err(d.cpu().numpy(), want).max() <= TOL["fp64"]
+
+
+@pytest.mark.parametrize("what", ["layout", "scratch", "preconditioner"])
+def test_one_block_solver_without_memory(monkeypatch, what):
+    """A small graph whose layout, or the vectors of its columns, do not fit
+    is solved by tiles, that call and the later ones; other graphs are not
+    concerned."""
+    n, k = 6000, 40
+    rng = np.random.default_rng(4)
+    g = _ring(n, rng)
+    P, Q = rng.random((n, k)), rng.random((n, k))
+    precond = "achol" if what == "preconditioner" else "jacobi"
+    say("one block, memory", what)
+    ref = oracle.ge_pcg(n, g.row_ptr, g.col_idx, None, P, Q)
+    dg = dev_graph(g)
+    monkeypatch.setenv("NVD_COLUMN", "0")              # the tiles' workspace (and the factor) first
+    tiled, _, _ = dg.distances(P, Q, precision="mixed", precond=precond)
+    before = dg.stats()["device_bytes"]
+    monkeypatch.setenv("NVD_COLUMN", "1")
+    # the layout takes some 400 KB, the factor's as much, the vectors 8 MB
+    monkeypatch.setenv("NVD_ALLOC_LIMIT", str(4000 if what == "layout" else 4 << 20))
+    for _ in range(2):
+        d, X, info = dg.distances(P, Q, precision="mixed", rtol=1e-10, return_x=True, precond=precond)
+        assert all(i["status"] == 0 for i in info)
+        assert rel_err(d.cpu().numpy(), ref["d"]).max() <= TOL["mixed"]
+        np.testing.assert_allclose(X.cpu().numpy(), ref["x"], rtol=0, atol=1e-5 * np.abs(ref["x"]).max())
+    D = dg.pairwise(P[:, :5], precision="fp64")[0].cpu().numpy()
+    monkeypatch.delenv("NVD_ALLOC_LIMIT")
+    if what != "preconditioner":
+        assert dg.stats()["device_bytes"] == before    # nothing of it is left
+    again, _, _ = dg.distances(P, Q, precision="mixed", precond=precond)
+    assert rel_err(again.cpu().numpy(), tiled.cpu().numpy()).max() <= 1e-12
+    other = dev_graph(g)
+    assert rel_err(other.pairwise(P[:, :5])[0].cpu().numpy(), D).max() <= TOL["fp64"]
+    assert other.stats()["device_bytes"] > 0

@@ -403,6 +403,7 @@ nvd_status nvd_graph_set_weights(nvd_graph* h, const double* w, void* stream) {
   g->weighted = true;
   // the spanning forest (tree preconditioner) holds 1/w of its edges and is
   // built from the host copy of the weights: drop the forest
+  if (g->tree) g->bytes -= g->tree->col_bytes;
   free_tree(g->tree);
   g->tree = nullptr;
   if (g->achol) g->bytes -= g->achol->bytes;

@@ -87,7 +87,8 @@ struct ColPlan {
   int entries = 0;
   bool weighted = false;           // the copies are those of explicit weights
   bool stale = true;               // the graph's weights changed since
-  int64_t bytes = 0;
+  int64_t bytes = 0;               // of both
+  int64_t weight_bytes = 0;
 };
 
 // Scratch (`vec` doubles of vectors, then `cm` of component means) and result
@@ -359,11 +360,15 @@ static nvd_status ensure_column(DevGraph* g, hipStream_t s) {
   if (!cp->weights || cp->weighted != g->weighted) {
     (void)hipFree(cp->weights);
     cp->weights = nullptr;
+    cp->bytes -= cp->weight_bytes;
+    g->bytes -= cp->weight_bytes;
+    cp->weight_bytes = 0;
     const size_t want = weight_doubles(g->weighted ? cp->entries : 0, cp->d.slots * kColBS);
     NVD_HIP(device_alloc((void**)&cp->weights, sizeof(double) * want));
     cp->weighted = g->weighted;
-    cp->bytes += (int64_t)(sizeof(double) * want);
-    g->bytes += (int64_t)(sizeof(double) * want);
+    cp->weight_bytes = (int64_t)(sizeof(double) * want);
+    cp->bytes += cp->weight_bytes;
+    g->bytes += cp->weight_bytes;
   }
   NVD_TRY(put_weights(g, &cp->d, cp->entries, cp->src, cp->weights, s));
   cp->stale = false;

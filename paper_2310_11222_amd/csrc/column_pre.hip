@@ -260,8 +260,8 @@ static nvd_status build_tree_order(DevGraph* g, const std::vector<int>& perm, in
   const size_t o_w = bl.put(tw), o_tour = bl.put(tour), o_auv = bl.put(auv), o_C = bl.put(Cinv);
   const size_t o_aoff = bl.put(aoff), o_aend = bl.put(aend), o_aedge = bl.put(aedge);
   ColPreDev* cp = nullptr;
-  int64_t bytes = 0;
-  NVD_TRY(upload(bl, &cp, &bytes));
+  NVD_TRY(upload(bl, &cp, &tp->col_bytes));
+  g->bytes += tp->col_bytes;
   auto us = [&](size_t o) { return reinterpret_cast<const unsigned short*>(cp->blob + o); };
   cp->d.kind = kColPreTree;
   cp->d.tpre = us(o_pre);

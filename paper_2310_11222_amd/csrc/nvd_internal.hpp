@@ -46,6 +46,7 @@ struct TreePre {
   double* aug_Cinv = nullptr;     // [k][k] C^-1
   double* aug_st = nullptr;       // [2][k][kMaxTile] U^T z, then C^-1 U^T z
   ColPreDev* col = nullptr;       // the forest as the one-block solver walks it
+  int64_t col_bytes = 0;          // (counted with the graph's)
 };
 
 // Approximate-Cholesky factor for its preconditioner (built on first use):

@@ -1044,23 +1044,7 @@ static nvd_status run_batch(nvd_batch* b, const std::vector<int>& ks, const doub
     set_error("batched solver: no resident blocks");
     return NVD_E_DEVICE;
   }
-  // workspace
-  const size_t vsz = sizeof(V);
-  if (b->cap_T < T || b->cap_vsize < (int)vsz) {
-    void* ptrs[] = {b->b64, b->x64, b->r64, b->cv, b->rv, b->pv, b->qv};
-    for (void* p : ptrs)
-      if (p) (void)hipFree(p);
-    const size_t ne = (size_t)b->tot_n * T;
-    NVD_TRY(balloc(b, &b->b64, ne));
-    NVD_TRY(balloc(b, &b->x64, ne));
-    NVD_TRY(balloc(b, &b->r64, ne));
-    NVD_HIP(hipMalloc(&b->cv, ne * vsz));
-    NVD_HIP(hipMalloc(&b->rv, ne * vsz));
-    NVD_HIP(hipMalloc(&b->pv, ne * vsz));
-    NVD_HIP(hipMalloc(&b->qv, ne * vsz));
-    b->cap_T = T;
-    b->cap_vsize = (int)vsz;
-  }
+  NVD_TRY((batch_vectors<T, V>(b)));
   if (!b->part) NVD_TRY(balloc(b, &b->part, (size_t)2 * 2048 * kRedStride));
   int K = 0;
   std::vector<BGraph> gd(G);
@@ -1083,6 +1067,8 @@ static nvd_status run_batch(nvd_batch* b, const std::vector<int>& ks, const doub
   }
   if (b->info_cap < K) {
     if (b->info) (void)hipFree(b->info);
+    b->info = nullptr;
+    b->info_cap = 0;
     NVD_TRY(balloc(b, &b->info, K));
     b->info_cap = K;
   }
@@ -1095,6 +1081,8 @@ static nvd_status run_batch(nvd_batch* b, const std::vector<int>& ks, const doub
   const size_t plan_ints = (size_t)B + 3 * pl.nteams + pl.pool.size() + pl.nteams;
   if ((size_t)b->plan_cap < plan_ints) {
     if (b->plan_buf) (void)hipFree(b->plan_buf);
+    b->plan_buf = nullptr;
+    b->plan_cap = 0;
     NVD_TRY(balloc(b, &b->plan_buf, plan_ints));
     b->plan_cap = (int)plan_ints;
   }
@@ -1311,25 +1299,31 @@ extern "C" nvd_status nvd_batch_distances(nvd_batch* b, const int32_t* k_per_gra
   while (T < kmax) T *= 2;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   std::vector<nvd_pair_info> hinfo(K);
-  nvd_status st = NVD_E_UNSUPPORTED;
   const bool mixed = o.precision == NVD_MIXED;
-  if (!(o.flags & NVD_BATCH_PERSISTENT)) {
-    if (b->col && use_column_batch(b->col, mixed))
-      st = solve_column_batch(b->col, ks, o, P, Q, d_out, X_out, hinfo.data(), s);
-    else
-      st = run_sweep(b, ks, T, o, P, Q, d_out, X_out, hinfo.data(), s);
-    T = 0;    // skip the persistent solver below
-  }
+  auto solve = [&]() -> nvd_status {
+    if (!(o.flags & NVD_BATCH_PERSISTENT)) {
+      if (b->col && use_column_batch(b->col, mixed))
+        return solve_column_batch(b->col, ks, o, P, Q, d_out, X_out, hinfo.data(), &b->bytes, s);
+      return run_sweep(b, ks, T, o, P, Q, d_out, X_out, hinfo.data(), s);
+    }
 #define NVD_BT(TT)                                                                          \
   case TT:                                                                                  \
-    st = mixed ? run_batch<TT, float>(b, ks, P, Q, o, d_out, X_out, hinfo.data(), s)        \
-               : run_batch<TT, double>(b, ks, P, Q, o, d_out, X_out, hinfo.data(), s);      \
-    break;
-  switch (T) {
-    NVD_BT(1) NVD_BT(2) NVD_BT(4) NVD_BT(8) NVD_BT(16) NVD_BT(32) NVD_BT(64)
-    default: break;   // T == 0: solved by the sweep
-  }
+    return mixed ? run_batch<TT, float>(b, ks, P, Q, o, d_out, X_out, hinfo.data(), s)      \
+                 : run_batch<TT, double>(b, ks, P, Q, o, d_out, X_out, hinfo.data(), s);
+    switch (T) {
+      NVD_BT(1) NVD_BT(2) NVD_BT(4) NVD_BT(8) NVD_BT(16) NVD_BT(32) NVD_BT(64)
+      default: return NVD_E_UNSUPPORTED;
+    }
 #undef NVD_BT
+  };
+  nvd_status st = solve();
+  if (st == NVD_E_NOMEM && b->col) {
+    // without the layouts for one block per pair: what they hold is given back
+    free_column_batch(b->col, &b->bytes);
+    b->col = nullptr;
+    set_error("");
+    st = solve();
+  }
   if (st != NVD_OK) return st;
   nvd_status agg = NVD_OK;
   for (int j = 0; j < K; ++j) {

@@ -106,7 +106,7 @@ static inline void batch_free(nvd_batch* b) {
                   b->ch_buf, b->sg_dev, b->spart, b->sstate};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
-  nvd::free_column_batch(b->col);
+  nvd::free_column_batch(b->col, &b->bytes);
   if (b->h_err) (void)hipHostFree(b->h_err);
   if (b->h_poll) (void)hipHostFree(b->h_poll);
 }
@@ -114,8 +114,29 @@ static inline void batch_free(nvd_batch* b) {
 template <typename T>
 static nvd_status balloc(nvd_batch* b, T** p, size_t count) {
   if (count == 0) count = 1;
-  NVD_HIP(hipMalloc((void**)p, count * sizeof(T)));
+  NVD_HIP(nvd::device_alloc((void**)p, count * sizeof(T)));
   b->bytes += (int64_t)(count * sizeof(T));
+  return NVD_OK;
+}
+
+// The solver's vectors of a tile, T columns of type V (n_total x T), grown on
+// demand; both solvers of larger graphs use them.
+template <int T, typename V>
+static nvd_status batch_vectors(nvd_batch* b) {
+  if (b->cap_T >= T && b->cap_vsize >= (int)sizeof(V)) return NVD_OK;
+  void** vs[] = {(void**)&b->b64, (void**)&b->x64, (void**)&b->r64, &b->cv, &b->rv, &b->pv, &b->qv};
+  for (void** p : vs) {
+    (void)hipFree(*p);
+    *p = nullptr;
+  }
+  b->cap_T = b->cap_vsize = 0;         // (none are there until all are)
+  const size_t ne = (size_t)b->tot_n * T;
+  NVD_TRY(balloc(b, &b->b64, ne));
+  NVD_TRY(balloc(b, &b->x64, ne));
+  NVD_TRY(balloc(b, &b->r64, ne));
+  for (void** p : {&b->cv, &b->rv, &b->pv, &b->qv}) NVD_HIP(nvd::device_alloc(p, ne * sizeof(V)));
+  b->cap_T = T;
+  b->cap_vsize = (int)sizeof(V);
   return NVD_OK;
 }
 

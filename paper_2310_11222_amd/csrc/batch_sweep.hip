@@ -961,31 +961,14 @@ static nvd_status sweep_t(nvd_batch* b, const std::vector<int>& ks, const nvd_op
                           nvd_pair_info* info_host, hipStream_t s) {
   const int G = b->G;
   NVD_TRY(build_chunks(b, s));
-  // vectors (shared with the persistent solver's workspace)
-  const size_t vsz = sizeof(V);
-  if (b->cap_T < T || b->cap_vsize < (int)vsz) {
-    void* ptrs[] = {b->b64, b->x64, b->r64, b->cv, b->rv, b->pv, b->qv};
-    for (void* p : ptrs)
-      if (p) (void)hipFree(p);
-    b->b64 = b->x64 = b->r64 = nullptr;
-    b->cv = b->rv = b->pv = b->qv = nullptr;
-    const size_t ne = (size_t)b->tot_n * T;
-    NVD_TRY(balloc(b, &b->b64, ne));
-    NVD_TRY(balloc(b, &b->x64, ne));
-    NVD_TRY(balloc(b, &b->r64, ne));
-    NVD_HIP(hipMalloc(&b->cv, ne * vsz));
-    NVD_HIP(hipMalloc(&b->rv, ne * vsz));
-    NVD_HIP(hipMalloc(&b->pv, ne * vsz));
-    NVD_HIP(hipMalloc(&b->qv, ne * vsz));
-    b->cap_T = T;
-    b->cap_vsize = (int)vsz;
-  }
+  NVD_TRY((batch_vectors<T, V>(b)));
   // per-chunk partials and per-(graph, column) state
   const int pstride = 5 * T;
   const size_t need_part = (size_t)b->n_chunks * pstride;
   if (b->spart_cap < need_part) {
     if (b->spart) (void)hipFree(b->spart);
     b->spart = nullptr;
+    b->spart_cap = 0;
     NVD_TRY(balloc(b, &b->spart, need_part));
     b->spart_cap = need_part;
   }
@@ -995,6 +978,7 @@ static nvd_status sweep_t(nvd_batch* b, const std::vector<int>& ks, const nvd_op
   if (b->sstate_cap < state_bytes) {
     if (b->sstate) (void)hipFree(b->sstate);
     b->sstate = nullptr;
+    b->sstate_cap = 0;
     NVD_TRY(balloc(b, &b->sstate, state_bytes));
     NVD_HIP(hipMemset(b->sstate, 0, state_bytes));   // arrival counters start at zero
     b->sstate_cap = state_bytes;
@@ -1025,13 +1009,14 @@ static nvd_status sweep_t(nvd_batch* b, const std::vector<int>& ks, const nvd_op
     K += d.k;
   }
   if (!b->sg_dev) {
-    NVD_HIP(hipMalloc(&b->sg_dev, sizeof(SGraph) * G));
+    NVD_HIP(device_alloc(&b->sg_dev, sizeof(SGraph) * G));
     b->bytes += (int64_t)(sizeof(SGraph) * G);
   }
   NVD_HIP(hipMemcpyAsync(b->sg_dev, sg.data(), sizeof(SGraph) * G, hipMemcpyHostToDevice, s));
   if (b->info_cap < K) {
     if (b->info) (void)hipFree(b->info);
     b->info = nullptr;
+    b->info_cap = 0;
     NVD_TRY(balloc(b, &b->info, K));
     b->info_cap = K;
   }

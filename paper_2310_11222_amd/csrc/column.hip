@@ -591,6 +591,16 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
 // swept whole.  Beyond 24 slots a block's iteration takes longer than the
 // sweep's (n = 32,000, weighted: 32 us / 26).
 constexpr int kColBatchNodes = 24 * kColBS;
+// Scratch of one launch at most: far fewer pairs are in flight (two a CU) than
+// a batch may have (10^5 graphs of 64 pairs: 210 GB for all at once), and the
+// next launch uses the same vectors.  1,365 pairs of the largest graphs.
+constexpr size_t kColBatchScratch = (size_t)1 << 30;
+
+// Jobs of one launch.
+struct ColChunk {
+  int first, count, weighted;
+  int slots, nv;                   // the most of its graphs
+};
 
 struct ColBatch {
   std::vector<ColGraph> h;         // the graphs' layouts (on the host)
@@ -601,36 +611,45 @@ struct ColBatch {
   ColGraph* dev = nullptr;
   // jobs of the last call, kept while the pair counts stay the same
   std::vector<int> ks;
-  std::vector<ColJob> jobs[2];     // [unit, weighted]
+  std::vector<ColChunk> chunks;
   ColJob* jobs_dev = nullptr;
   size_t cap_jobs = 0, work = 0;
   ColWs ws;
+  int64_t bytes = 0;
 };
 
-void free_column_batch(ColBatch* c) {
+void free_column_batch(ColBatch* c, int64_t* bytes) {
   if (!c) return;
+  *bytes -= c->bytes + (int64_t)(sizeof(double) * (c->ws.cap_vec + c->ws.cap_cm));
   void* ptrs[] = {c->blob, c->weights, c->dev, c->jobs_dev};
   for (void* p : ptrs) (void)hipFree(p);
   free_column_ws(&c->ws);
   delete c;
 }
 
-nvd_status make_column_batch(int G, const DevGraph* const* graphs, hipStream_t s, ColBatch** out,
-                             int64_t* bytes) {
-  *out = nullptr;
+static nvd_status lay_out_batch(int G, const DevGraph* const* graphs, hipStream_t s, ColBatch** out,
+                                int64_t* bytes) {
   int most = 0;
   for (int i = 0; i < G; ++i) most = std::max(most, graphs[i]->n_comp == 1 ? graphs[i]->n : INT32_MAX);
   if (most > kColBatchNodes) return NVD_OK;
   std::vector<ColLayout> lay(G);
   const int nt = (int)std::max(1u, std::min(std::min(16u, std::thread::hardware_concurrency()), (unsigned)G));
   std::atomic<int> next{0};
+  std::atomic<bool> failed{false};
   auto run = [&]() {
-    for (int i = next++; i < G; i = next++) layout_column(graphs[i], &lay[i]);
+    try {
+      for (int i = next++; i < G && !failed; i = next++) layout_column(graphs[i], &lay[i]);
+    } catch (const std::bad_alloc&) {
+      failed = true;
+    }
   };
   std::vector<std::thread> th;
-  for (int t = 1; t < nt; ++t) th.emplace_back(run);
+  try {
+    for (int t = 1; t < nt; ++t) th.emplace_back(run);
+  } catch (const std::exception&) {}   // (fewer threads, then)
   run();
   for (auto& x : th) x.join();
+  if (failed) return NVD_E_NOMEM;
   Blob bl;
   size_t nw = 0;
   for (int i = 0; i < G; ++i) {
@@ -640,9 +659,9 @@ nvd_status make_column_batch(int G, const DevGraph* const* graphs, hipStream_t s
   ColBatch* c = new ColBatch();
   c->most = most;
   nvd_status st = NVD_OK;
-  hipError_t e = hipMalloc((void**)&c->blob, bl.h.size());
-  if (e == hipSuccess) e = hipMalloc((void**)&c->weights, sizeof(double) * nw);
-  if (e == hipSuccess) e = hipMalloc((void**)&c->dev, sizeof(ColGraph) * G);
+  hipError_t e = device_alloc((void**)&c->blob, bl.h.size());
+  if (e == hipSuccess) e = device_alloc((void**)&c->weights, sizeof(double) * nw);
+  if (e == hipSuccess) e = device_alloc((void**)&c->dev, sizeof(ColGraph) * G);
   if (e == hipSuccess) e = hipMemcpyAsync(c->blob, bl.h.data(), bl.h.size(), hipMemcpyHostToDevice, s);
   size_t at = 0;
   for (int i = 0; e == hipSuccess && st == NVD_OK && i < G; ++i) {
@@ -662,12 +681,29 @@ nvd_status make_column_batch(int G, const DevGraph* const* graphs, hipStream_t s
     st = e == hipErrorOutOfMemory ? NVD_E_NOMEM : NVD_E_DEVICE;
   }
   if (st != NVD_OK) {
-    free_column_batch(c);
+    free_column_batch(c, bytes);
     return st;
   }
-  *bytes += (int64_t)(bl.h.size() + sizeof(double) * nw + sizeof(ColGraph) * G);
+  c->bytes = (int64_t)(bl.h.size() + sizeof(double) * nw + sizeof(ColGraph) * G);
+  *bytes += c->bytes;
   *out = c;
   return NVD_OK;
+}
+
+nvd_status make_column_batch(int G, const DevGraph* const* graphs, hipStream_t s, ColBatch** out,
+                             int64_t* bytes) {
+  *out = nullptr;
+  nvd_status st = NVD_OK;
+  try {
+    st = lay_out_batch(G, graphs, s, out, bytes);
+  } catch (const std::bad_alloc&) {
+    st = NVD_E_NOMEM;
+  }
+  if (st == NVD_E_NOMEM) {         // the batch is swept
+    set_error("");
+    st = NVD_OK;
+  }
+  return st;
 }
 
 bool use_column_batch(const ColBatch* c, bool mixed) {
@@ -676,7 +712,8 @@ bool use_column_batch(const ColBatch* c, bool mixed) {
 }
 
 nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd_opts& o, const double* P,
-                              const double* Q, double* d_out, double* X, nvd_pair_info* info, hipStream_t s) {
+                              const double* Q, double* d_out, double* X, nvd_pair_info* info, int64_t* bytes,
+                              hipStream_t s) {
   const int G = (int)c->h.size();
   int K = 0;
   for (const int k : ks) K += k;
@@ -695,32 +732,55 @@ nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd
     }
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return c->h[x].n > c->h[y].n; });
+    // unit graphs, then weighted ones (another kernel), in launches whose
+    // vectors fit the scratch
     c->work = 0;
-    for (auto& j : c->jobs) j.clear();
-    for (const int g : order)
-      for (int j = 0; j < ks[g]; ++j) {
-        ColJob job{};
-        job.graph = g;
-        job.out = out[g] + j;
-        job.voff = job.xoff = voff[g] + j;
-        job.ld = job.ldx = ks[g];
-        job.work = (long)c->work;
-        c->work += (size_t)4 * c->h[g].slots * kColBS;
-        c->jobs[c->weighted[g]].push_back(job);
+    c->chunks.clear();
+    std::vector<ColJob> all;
+    all.reserve(K);
+    for (int w = 0; w < 2; ++w) {
+      size_t work = 0;
+      bool open = false;
+      for (const int g : order) {
+        if (c->weighted[g] != w) continue;
+        const size_t need = (size_t)4 * c->h[g].slots * kColBS;
+        for (int j = 0; j < ks[g]; ++j) {
+          if (!open || sizeof(double) * (work + need) > kColBatchScratch) {
+            c->chunks.push_back({(int)all.size(), 0, w, 0, 0});
+            work = 0;
+            open = true;
+          }
+          ColJob job{};
+          job.graph = g;
+          job.out = out[g] + j;
+          job.voff = job.xoff = voff[g] + j;
+          job.ld = job.ldx = ks[g];
+          job.work = (long)work;
+          all.push_back(job);
+          work += need;
+          c->work = std::max(c->work, work);
+          ColChunk& ch = c->chunks.back();
+          ch.count += 1;
+          ch.slots = std::max(ch.slots, c->h[g].slots);
+          ch.nv = std::max(ch.nv, c->h[g].nv);
+        }
       }
-    std::vector<ColJob> all(c->jobs[0]);
-    all.insert(all.end(), c->jobs[1].begin(), c->jobs[1].end());
+    }
     if (c->cap_jobs < all.size()) {
       (void)hipFree(c->jobs_dev);
       c->jobs_dev = nullptr;
+      c->bytes -= (int64_t)(sizeof(ColJob) * c->cap_jobs);
+      *bytes -= (int64_t)(sizeof(ColJob) * c->cap_jobs);
       c->cap_jobs = 0;
-      NVD_HIP(hipMalloc((void**)&c->jobs_dev, sizeof(ColJob) * all.size()));
+      NVD_HIP(device_alloc((void**)&c->jobs_dev, sizeof(ColJob) * all.size()));
       c->cap_jobs = all.size();
+      c->bytes += (int64_t)(sizeof(ColJob) * c->cap_jobs);
+      *bytes += (int64_t)(sizeof(ColJob) * c->cap_jobs);
     }
     NVD_HIP(hipMemcpy(c->jobs_dev, all.data(), sizeof(ColJob) * all.size(), hipMemcpyHostToDevice));
     c->ks = ks;
   }
-  NVD_TRY(ensure_column_ws(&c->ws, c->work, 0, K, nullptr));
+  NVD_TRY(ensure_column_ws(&c->ws, c->work, 0, K, bytes));
   ColArgs a{};
   a.graphs = c->dev;
   a.vecs = 4;
@@ -737,21 +797,12 @@ nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd
   a.X = X;
   a.info = c->ws.info;
   a.vec = c->ws.vec;
-  size_t first = 0;
-  for (int w = 0; w < 2; ++w) {
-    const std::vector<ColJob>& jobs = c->jobs[w];
-    if (jobs.empty()) continue;
-    int slots = 0, nv = 0;
-    for (const ColJob& j : jobs) {
-      slots = std::max(slots, c->h[j.graph].slots);
-      nv = std::max(nv, c->h[j.graph].nv);
-    }
-    const size_t fit = ((size_t)kColLds - parts_bytes(nv)) / (sizeof(double) * kColBS);
-    a.lds_n = (int)std::min<size_t>(slots, fit) * kColBS;
-    a.jobs = c->jobs_dev + first;
-    first += jobs.size();
-    NVD_TRY(launch_column_jacobi(a, o.precision == NVD_MIXED, w == 0, slots * kColBS, (int)jobs.size(),
-                                 parts_bytes(nv) + sizeof(double) * (size_t)a.lds_n, s));
+  for (const ColChunk& ch : c->chunks) {
+    const size_t fit = ((size_t)kColLds - parts_bytes(ch.nv)) / (sizeof(double) * kColBS);
+    a.lds_n = (int)std::min<size_t>(ch.slots, fit) * kColBS;
+    a.jobs = c->jobs_dev + ch.first;
+    NVD_TRY(launch_column_jacobi(a, o.precision == NVD_MIXED, ch.weighted == 0, ch.slots * kColBS, ch.count,
+                                 parts_bytes(ch.nv) + sizeof(double) * (size_t)a.lds_n, s));
   }
   NVD_HIP(hipStreamSynchronize(s));
   std::copy(c->ws.info, c->ws.info + K, info);

@@ -6,7 +6,8 @@
 // 5.5 ms, the degrees 0.42 and the adjoint over 32 columns 1.9, of a training
 // step of 20.  By entry they need an entry's row and the place of its mirror
 // entry; both are found when weights are first replaced, by bisection, and kept
-// (8 bytes an entry).  That step then took 12.3 ms.
+// (8 bytes an entry; without the memory for them they are found in each call).
+// That step then took 12.3 ms.
 #include <algorithm>
 
 #include "column_pre_dev.hpp"
@@ -27,33 +28,40 @@ __device__ __forceinline__ int row_of(int n, const int* __restrict__ rp, int e) 
   return lo;
 }
 
-// Row of every entry, and the entry (j, i) of every entry (i, j).
+// The entry (j, i) of an entry (i, j) (the graph was checked to be symmetric).
+__device__ __forceinline__ int mirror_of(const int* __restrict__ rp, const int* __restrict__ ci, int i, int j) {
+  int a = rp[j], b = rp[j + 1];
+  while (a < b) {
+    const int mid = a + (b - a) / 2;
+    if (ci[mid] < i)
+      a = mid + 1;
+    else
+      b = mid;
+  }
+  return a;
+}
+
+// Row and mirror entry of every entry.
 __global__ __launch_bounds__(kEntryBS) void k_entries(int n, int nnz, const int* __restrict__ rp,
                                                       const int* __restrict__ ci, int* __restrict__ erow,
                                                       int* __restrict__ mirror) {
   for_entries(blockIdx.x, gridDim.x, threadIdx.x, nnz, [&](int e) {
-    const int i = row_of(n, rp, e), j = ci[e];
+    const int i = row_of(n, rp, e);
     erow[e] = i;
-    int a = rp[j], b = rp[j + 1];
-    while (a < b) {
-      const int mid = a + (b - a) / 2;
-      if (ci[mid] < i)
-        a = mid + 1;
-      else
-        b = mid;
-    }
-    mirror[e] = a;                     // (the graph was checked to be symmetric)
+    mirror[e] = mirror_of(rp, ci, i, ci[e]);
   });
 }
 
 // New weights in input order: bit 1 where one is not finite and positive, bit 2
-// where an entry's and its mirror's differ.
-__global__ __launch_bounds__(kEntryBS) void k_check_entries(int nnz, const int* __restrict__ in_pos,
+// where an entry's and its mirror's differ.  mirror may be null.
+__global__ __launch_bounds__(kEntryBS) void k_check_entries(int n, int nnz, const int* __restrict__ rp,
+                                                            const int* __restrict__ ci,
+                                                            const int* __restrict__ in_pos,
                                                             const int* __restrict__ mirror,
                                                             const double* __restrict__ w, int* flag) {
   int bad = 0;
   for_entries(blockIdx.x, gridDim.x, threadIdx.x, nnz, [&](int e) {
-    const int m = mirror[e];
+    const int m = mirror ? mirror[e] : mirror_of(rp, ci, row_of(n, rp, e), ci[e]);
     const double v = w[in_pos ? in_pos[e] : e];
     if (!(v > 0.0) || !isfinite(v)) bad |= 1;
     if (w[in_pos ? in_pos[m] : m] != v) bad |= 2;
@@ -150,7 +158,7 @@ static nvd_status ensure_entries(DevGraph* g, hipStream_t s) {
   if (g->erow) return NVD_OK;
   int* p = nullptr;
   const size_t count = 2 * (size_t)std::max(g->nnz, 1) + 1;
-  NVD_HIP(hipMalloc((void**)&p, sizeof(int) * count));
+  NVD_HIP(device_alloc((void**)&p, sizeof(int) * count));
   if (g->nnz > 0) k_entries<<<entry_grid(g->nnz), kEntryBS, 0, s>>>(g->n, g->nnz, g->rp, g->ci, p, p + g->nnz);
   // (other streams may use them from the next call on)
   hipError_t e = hipGetLastError();
@@ -168,15 +176,25 @@ static nvd_status ensure_entries(DevGraph* g, hipStream_t s) {
 
 // Bits of k_check_entries for the new weights w (input order); waits for s.
 nvd_status check_weights(DevGraph* g, const double* w, int* bits, hipStream_t s) {
-  NVD_TRY(ensure_entries(g, s));
-  int* flag = g->erow + 2 * (size_t)std::max(g->nnz, 1);
+  const nvd_status st = ensure_entries(g, s);
+  if (st != NVD_OK && st != NVD_E_NOMEM) return st;
+  int* own = nullptr;              // the word of a call without the map
+  if (st == NVD_E_NOMEM) {
+    set_error("");
+    NVD_HIP(device_alloc((void**)&own, sizeof(int)));
+  }
+  int* flag = own ? own : g->erow + 2 * (size_t)std::max(g->nnz, 1);
   *bits = 0;
-  NVD_HIP(hipMemcpyAsync(flag, bits, sizeof(int), hipMemcpyHostToDevice, s));
-  if (g->nnz > 0)
-    k_check_entries<<<std::min(entry_grid(g->nnz), 2048), kEntryBS, 0, s>>>(g->nnz, g->in_pos, g->mirror, w, flag);
-  NVD_HIP(hipGetLastError());
-  NVD_HIP(hipMemcpyAsync(bits, flag, sizeof(int), hipMemcpyDeviceToHost, s));
-  NVD_HIP(hipStreamSynchronize(s));
+  hipError_t e = hipMemcpyAsync(flag, bits, sizeof(int), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess && g->nnz > 0) {
+    k_check_entries<<<std::min(entry_grid(g->nnz), 2048), kEntryBS, 0, s>>>(g->n, g->nnz, g->rp, g->ci, g->in_pos,
+                                                                            g->mirror, w, flag);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipMemcpyAsync(bits, flag, sizeof(int), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  (void)hipFree(own);
+  NVD_HIP(e);
   return NVD_OK;
 }
 

@@ -273,14 +273,15 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
 // scratch (what there is of them is given back, and not tried again).
 bool column_gives_way(DevGraph* g, nvd_status st);
 // A batch of small graphs in the same way (column.hip); *out is null where it
-// has larger ones.
+// has larger ones, or where there is no memory for their layouts.
 struct ColBatch;
 nvd_status make_column_batch(int G, const DevGraph* const* graphs, hipStream_t s, ColBatch** out,
                              int64_t* bytes);
 bool use_column_batch(const ColBatch* c, bool mixed);
 nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd_opts& o, const double* P,
-                              const double* Q, double* d_out, double* X, nvd_pair_info* info, hipStream_t s);
-void free_column_batch(ColBatch* c);
+                              const double* Q, double* d_out, double* X, nvd_pair_info* info, int64_t* bytes,
+                              hipStream_t s);
+void free_column_batch(ColBatch* c, int64_t* bytes);
 // By CSR entry (entries.hip): weighted degrees, the check of new weights (bit 1:
 // one not finite and positive, bit 2: one differs from its mirror's), the
 // adjoint for the weights, the host's copy of replaced weights.

@@ -125,3 +125,33 @@ def test_one_block_solver_without_memory(monkeypatch, what):
     other = dev_graph(g)
     assert rel_err(other.pairwise(P[:, :5])[0].cpu().numpy(), D).max() <= TOL["fp64"]
     assert other.stats()["device_bytes"] > 0
+
+
+def test_new_weights_without_memory_for_the_entry_map(monkeypatch):
+    """Weights are checked and taken, and their gradient formed, without the
+    map of rows and mirror entries."""
+    import torch
+    import paper_2310_11222_amd as nvd
+    n = 3000
+    rng = np.random.default_rng(5)
+    g = _ring(n, rng)
+    gw = g.with_weights(rng.uniform(0.5, 2.0, g.num_edges))
+    say("entry map, memory")
+    dg = dev_graph(g.with_weights(np.ones(g.num_edges)))
+    monkeypatch.setenv("NVD_ALLOC_LIMIT", "1000")
+    for _ in range(2):
+        dg.set_weights(gw.w)
+        deg = np.zeros(n)
+        np.add.at(deg, np.repeat(np.arange(n), np.diff(g.row_ptr)), gw.w)
+        assert rel_err(dg.query()[1], deg).max() <= 1e-13
+        for at, value in ((0, np.nan), (-1, gw.w[-1] * 1.5), (g.nnz // 2, -1.0)):
+            bad = gw.w.copy()
+            bad[at] = value
+            with pytest.raises(nvd.NvdError) as ei:
+                dg.set_weights(bad)
+            assert ei.value.status == 2          # NVD_E_GRAPH
+    X = torch.from_numpy(rng.standard_normal((n, 3))).cuda()
+    without = dg.grad_weights(X, np.ones(3))
+    monkeypatch.delenv("NVD_ALLOC_LIMIT")
+    dg.set_weights(gw.w)
+    assert torch.equal(dg.grad_weights(X, np.ones(3)), without)

@@ -1065,13 +1065,7 @@ static nvd_status run_batch(nvd_batch* b, const std::vector<int>& ks, const doub
     in_off += (long)d.n * d.k;
     K += d.k;
   }
-  if (b->info_cap < K) {
-    if (b->info) (void)hipFree(b->info);
-    b->info = nullptr;
-    b->info_cap = 0;
-    NVD_TRY(balloc(b, &b->info, K));
-    b->info_cap = K;
-  }
+  NVD_TRY(batch_info(b, K));
   BatchPlan pl = make_plan(b, ks, T, B);
   std::vector<long> key = {T, (long)sizeof(V), (long)(intptr_t)P, (long)(intptr_t)Q,
                            (long)(intptr_t)d_out, (long)(intptr_t)X, B, o.max_iter, o.max_refine,

@@ -124,6 +124,8 @@ static nvd_status balloc(nvd_batch* b, T** p, size_t count) {
 template <int T, typename V>
 static nvd_status batch_vectors(nvd_batch* b) {
   if (b->cap_T >= T && b->cap_vsize >= (int)sizeof(V)) return NVD_OK;
+  batch_drop_graph(b);                 // (captured launches hold the present ones)
+  batch_drop_sweep_graph(b);
   void** vs[] = {(void**)&b->b64, (void**)&b->x64, (void**)&b->r64, &b->cv, &b->rv, &b->pv, &b->qv};
   for (void** p : vs) {
     (void)hipFree(*p);
@@ -140,6 +142,18 @@ static nvd_status batch_vectors(nvd_batch* b) {
   return NVD_OK;
 }
 
+// Results of K pairs on the device, for either of them.
+static inline nvd_status batch_info(nvd_batch* b, int K) {
+  if (b->info_cap >= K) return NVD_OK;
+  batch_drop_graph(b);
+  batch_drop_sweep_graph(b);
+  if (b->info) (void)hipFree(b->info);
+  b->info = nullptr;
+  b->info_cap = 0;
+  NVD_TRY(balloc(b, &b->info, K));
+  b->info_cap = K;
+  return NVD_OK;
+}
 
 namespace nvd {
 // Sweep solver: all graphs of the batch as one block-diagonal operator,

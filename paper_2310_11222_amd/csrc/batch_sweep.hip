@@ -1013,13 +1013,7 @@ static nvd_status sweep_t(nvd_batch* b, const std::vector<int>& ks, const nvd_op
     b->bytes += (int64_t)(sizeof(SGraph) * G);
   }
   NVD_HIP(hipMemcpyAsync(b->sg_dev, sg.data(), sizeof(SGraph) * G, hipMemcpyHostToDevice, s));
-  if (b->info_cap < K) {
-    if (b->info) (void)hipFree(b->info);
-    b->info = nullptr;
-    b->info_cap = 0;
-    NVD_TRY(balloc(b, &b->info, K));
-    b->info_cap = K;
-  }
+  NVD_TRY(batch_info(b, K));
   SArgs a{};
   a.G = G;
   a.T = T;

@@ -389,7 +389,7 @@ nvd_status nvd_batch_destroy(nvd_batch* b);
 /* Counts of how batched calls ran: launches captured into a hipGraph,
  * replays of a captured graph (calls whose arguments matched the previous
  * capture), and direct launches (capture off via NVD_BATCH_GRAPH=0, or
- * refused by the runtime). */
+ * refused by the runtime; every call solved by one block per pair). */
 nvd_status nvd_batch_query(const nvd_batch* b, int64_t* captures,
                            int64_t* replays, int64_t* eager);
 /* Per-graph timing of the last nvd_batch_distances call made with the

@@ -1210,15 +1210,7 @@ static nvd_status run_batch(nvd_batch* b, const std::vector<int>& ks, const doub
     set_error("batched solver: a team barrier timed out (blocks not co-resident?)");
     return NVD_E_DEVICE;
   }
-  if (info_host) {
-    int off = 0;
-    for (int i = 0; i < G; ++i) {
-      int itmax = 0;
-      for (int j = 0; j < ks[i]; ++j) itmax = std::max(itmax, info_host[off + j].iters);
-      if (itmax > 0) b->it_est[i] = itmax;
-      off += ks[i];
-    }
-  }
+  if (info_host) note_iterations(b, ks, info_host);
   return NVD_OK;
 }
 
@@ -1296,8 +1288,12 @@ extern "C" nvd_status nvd_batch_distances(nvd_batch* b, const int32_t* k_per_gra
   const bool mixed = o.precision == NVD_MIXED;
   auto solve = [&]() -> nvd_status {
     if (!(o.flags & NVD_BATCH_PERSISTENT)) {
-      if (b->col && use_column_batch(b->col, mixed))
-        return solve_column_batch(b->col, ks, o, P, Q, d_out, X_out, hinfo.data(), &b->bytes, s);
+      if (b->col && use_column_batch(b->col, mixed)) {
+        NVD_TRY(solve_column_batch(b->col, ks, o, P, Q, d_out, X_out, hinfo.data(), &b->bytes, s));
+        ++b->eager;
+        note_iterations(b, ks, hinfo.data());
+        return NVD_OK;
+      }
       return run_sweep(b, ks, T, o, P, Q, d_out, X_out, hinfo.data(), s);
     }
 #define NVD_BT(TT)                                                                          \

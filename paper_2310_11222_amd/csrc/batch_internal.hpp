@@ -2,6 +2,7 @@
 // solver (batch.hip) and the sweep solver (batch_sweep.hip).
 #pragma once
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -117,6 +118,18 @@ static nvd_status balloc(nvd_batch* b, T** p, size_t count) {
   NVD_HIP(nvd::device_alloc((void**)p, count * sizeof(T)));
   b->bytes += (int64_t)(count * sizeof(T));
   return NVD_OK;
+}
+
+// The iterations a call took, for the next call's work plan (whichever solver
+// makes it).
+static inline void note_iterations(nvd_batch* b, const std::vector<int>& ks, const nvd_pair_info* info) {
+  int off = 0;
+  for (int g = 0; g < b->G; ++g) {
+    int most = 0;
+    for (int j = 0; j < ks[g]; ++j) most = std::max(most, info[off + j].iters);
+    if (most > 0) b->it_est[g] = most;
+    off += ks[g];
+  }
 }
 
 // The solver's vectors of a tile, T columns of type V (n_total x T), grown on

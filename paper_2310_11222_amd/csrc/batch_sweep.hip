@@ -1135,15 +1135,7 @@ static nvd_status sweep_t(nvd_batch* b, const std::vector<int>& ks, const nvd_op
     NVD_HIP(hipMemcpyAsync(info_host, b->info, sizeof(nvd_pair_info) * K, hipMemcpyDeviceToHost, s));
   NVD_HIP(hipStreamSynchronize(s));
   ++b->sweeps;
-  if (info_host) {
-    int off = 0;
-    for (int g = 0; g < G; ++g) {
-      int itmax = 0;
-      for (int j = 0; j < ks[g]; ++j) itmax = std::max(itmax, info_host[off + j].iters);
-      if (itmax > 0) b->it_est[g] = itmax;
-      off += ks[g];
-    }
-  }
+  if (info_host) note_iterations(b, ks, info_host);
   return NVD_OK;
 }
 

@@ -375,6 +375,12 @@ static nvd_status ensure_column(DevGraph* g, hipStream_t s) {
   return NVD_OK;
 }
 
+// Slots of the instantiations: the fewer, the fewer registers and elements past
+// n.  Up to 8, powers of two (vectors wholly in registers).  Beyond, in mixed
+// precision (us per 8 pairs, this instantiation / the next one kept: 18 for 10
+// and 14, 33 for 24): 10 slots, the last with x and 1 / degree in registers, WS
+// n = 10,000 738 / 1005, BA 285 / 342; 14 slots, WS n = 13,000 1068 / 1094, BA
+// 366 / 379; 24 slots, WS n = 22,000 1875 / 1962, BA 710 / 732.
 template <bool MIXED, bool UNIT>
 static nvd_status launch_column_n(const ColArgs& a, int n, int blocks, size_t bytes, hipStream_t s) {
   const int ept = (n + kColBS - 1) / kColBS;
@@ -387,7 +393,10 @@ static nvd_status launch_column_n(const ColArgs& a, int n, int blocks, size_t by
     if (ept <= 14) return launch_column_k<MIXED, UNIT, 14, false>(a, blocks, bytes, s);
     if (ept <= 18) return launch_column_k<MIXED, UNIT, 18, false>(a, blocks, bytes, s);
     if (ept <= 24) return launch_column_k<MIXED, UNIT, 24, false>(a, blocks, bytes, s);
-    return launch_column_k<MIXED, UNIT, 32, false>(a, blocks, bytes, s);
+    // (33, one more than there are: arrays of 31 or 32 floats are kept as one
+    // register tuple, which on weighted graphs was spilled as a whole, 4 KB a
+    // thread: an iteration on 28,000 nodes of degree 8 took 252 us, now 28)
+    return launch_column_k<MIXED, UNIT, 33, false>(a, blocks, bytes, s);
   } else {
     // (arrays of 9 to 16 doubles are kept as one register tuple each and
     // spill as a whole)

@@ -39,21 +39,30 @@ struct ProjSrc {
   long lda;
   const double* b;   // optional second operand subtracted (ldb), may be null
   long ldb;
-  int cols;          // columns there are (0: the whole tile); the rest of a
-                     // ragged tile reads as zero
 };
 
+// (One expression, with which both loads are out before the first is waited for:
+// subtracting the second under a test, k_proj_init took 385 us a tile of 64
+// columns on 10^6 nodes, so 344.)
 __device__ __forceinline__ double proj_value(const ProjSrc& src, long i, int c) {
-  if (src.cols > 0 && c >= src.cols) return 0.0;
-  double v = src.a[i * src.lda + c];
-  if (src.b) v -= src.b[i * src.ldb + c];
-  return v;
+  return src.a[i * src.lda + c] - (src.b ? src.b[i * src.ldb + c] : 0.0);
+}
+
+// A ragged tile's source: columns past the last of cols read as zero.  (A type
+// of its own, so that full tiles do without the test.)
+struct RaggedSrc {
+  ProjSrc src;
+  int cols;
+};
+
+__device__ __forceinline__ double proj_value(const RaggedSrc& r, long i, int c) {
+  return c < r.cols ? proj_value(r.src, i, c) : 0.0;
 }
 
 // Column sums of (a - b) over all rows; the grid's last block stores
 // mean[c] = sum / n (single-component graphs).
-template <int T>
-__global__ __launch_bounds__(kBS) void k_colsum(int n, ProjSrc src, ColState* cs, GridRed red) {
+template <int T, typename Src>
+__global__ __launch_bounds__(kBS) void k_colsum(int n, Src src, ColState* cs, GridRed red) {
   __shared__ double sh[kBS];
   __shared__ double vals[kMaxTile];
   const int t = threadIdx.x;
@@ -71,9 +80,9 @@ __global__ __launch_bounds__(kBS) void k_colsum(int n, ProjSrc src, ColState* cs
 }
 
 // Per-component means of (a - b): one block per component.
-template <int T>
-__global__ __launch_bounds__(kBS) void k_comp_mean(int ncomp, const int* perm, const int* off,
-                                                   ProjSrc src, double* cmean) {
+template <int T, typename Src>
+__global__ __launch_bounds__(kBS) void k_comp_mean(int ncomp, const int* perm, const int* off, Src src,
+                                                   double* cmean) {
   __shared__ double sh[kBS];
   const int t = threadIdx.x;
   const int c = t % T;
@@ -110,8 +119,8 @@ __device__ __forceinline__ double mean_of(const MeanSrc& m, long i, int c) {
 // delta_bar = (P - Q) - mean; b = delta_bar; x = 0; for the FP64 solver also
 // r = delta_bar, p = D^-1 r, q = 0 and rho = r^T D^-1 r.  Padding beyond n*T
 // is zeroed.
-template <int T>
-__global__ __launch_bounds__(kBS) void k_proj_init(int n, long cap, ProjSrc src, MeanSrc m,
+template <int T, typename Src>
+__global__ __launch_bounds__(kBS) void k_proj_init(int n, long cap, Src src, MeanSrc m,
                                                    const double* invd, double* b64, double* x64,
                                                    double* r64, double* p64, double* q64,
                                                    int fp64cg, ColState* cs, GridRed red) {
@@ -1018,17 +1027,17 @@ nvd_status time_cg_iteration(DevGraph* g, int prec, int T, int nl, hipStream_t s
   return prec == 0 ? time_iteration_t<double>(g, T, nl, s, ms) : time_iteration_t<float>(g, T, nl, s, ms);
 }
 
-static nvd_status mean_into(DevGraph* g, Workspace* ws, int T, ProjSrc src, MeanSrc* m,
-                            hipStream_t s) {
+template <typename Src>
+static nvd_status mean_into(DevGraph* g, Workspace* ws, int T, const Src& src, MeanSrc* m, hipStream_t s) {
   *m = MeanSrc{};
   m->n = g->n;
   if (g->n_comp == 1) {
     const int grid = stream_grid((long)g->n * T);
-    NVD_TILE_SWITCH(T, (k_colsum<TT><<<grid, kBS, 0, s>>>(g->n, src, ws->cs, ws->red)));
+    NVD_TILE_SWITCH(T, (k_colsum<TT, Src><<<grid, kBS, 0, s>>>(g->n, src, ws->cs, ws->red)));
     m->colmean = ws->cs->mean;
   } else {
     const int grid = std::min(g->n_comp, 4096);
-    NVD_TILE_SWITCH(T, (k_comp_mean<TT><<<grid, kBS, 0, s>>>(g->n_comp, g->comp_perm, g->comp_off,
+    NVD_TILE_SWITCH(T, (k_comp_mean<TT, Src><<<grid, kBS, 0, s>>>(g->n_comp, g->comp_perm, g->comp_off,
                                                             src, ws->comp_mean)));
     m->cmean = ws->comp_mean;
     m->comp = g->comp;
@@ -1079,11 +1088,17 @@ nvd_status solve_tile_ws(DevGraph* g, Workspace* ws, int T, const double* P, con
 
   // (a2) delta_bar = (P - Q) minus its per-component mean
   MeanSrc m{};
-  NVD_TRY(mean_into(g, ws, T, ProjSrc{P, ld, Q, ld, cols}, &m, s));
-  NVD_TILE_SWITCH(T, (k_proj_init<TT><<<grid, kBS, 0, s>>>(
-                         n, cap, ProjSrc{P, ld, Q, ld, cols}, m, g->invd64, ws->b64, ws->x64, ws->r64,
-                         ws->p64, ws->q64, mixed ? 0 : 1, ws->cs, ws->red)));
-  NVD_HIP(hipGetLastError());
+  auto project = [&](const auto& src) -> nvd_status {
+    using Src = std::decay_t<decltype(src)>;
+    NVD_TRY(mean_into(g, ws, T, src, &m, s));
+    NVD_TILE_SWITCH(T, (k_proj_init<TT, Src><<<grid, kBS, 0, s>>>(n, cap, src, m, g->invd64, ws->b64, ws->x64,
+                                                                  ws->r64, ws->p64, ws->q64, mixed ? 0 : 1, ws->cs,
+                                                                  ws->red)));
+    NVD_HIP(hipGetLastError());
+    return NVD_OK;
+  };
+  const ProjSrc src{P, ld, Q, ld};
+  NVD_TRY(cols < T ? project(RaggedSrc{src, cols}) : project(src));
   if (sp.tree && !mixed) NVD_TRY(tree_start<double>(g, ws, T, ws->r64, ws->p64, sp, s));
 
   SpmmCall resid{};

@@ -41,11 +41,19 @@ struct ProjSrc {
   long ldb;
 };
 
-// (One expression, with which both loads are out before the first is waited for:
-// subtracting the second under a test, k_proj_init took 385 us a tile of 64
-// columns on 10^6 nodes, so 344.)
+// BOTH: the two loads are out before the first is waited for (in k_proj_init,
+// 344 us a tile of 64 columns on 10^6 nodes, 385 with the second under a test).
+// The sums, which mostly read one operand, have the test: k_comp_mean took a
+// tenth longer without it.
+template <bool BOTH>
 __device__ __forceinline__ double proj_value(const ProjSrc& src, long i, int c) {
-  return src.a[i * src.lda + c] - (src.b ? src.b[i * src.ldb + c] : 0.0);
+  if constexpr (BOTH) {
+    return src.a[i * src.lda + c] - (src.b ? src.b[i * src.ldb + c] : 0.0);
+  } else {
+    double v = src.a[i * src.lda + c];
+    if (src.b) v -= src.b[i * src.ldb + c];
+    return v;
+  }
 }
 
 // A ragged tile's source: columns past the last of cols read as zero.  (A type
@@ -55,8 +63,9 @@ struct RaggedSrc {
   int cols;
 };
 
+template <bool BOTH>
 __device__ __forceinline__ double proj_value(const RaggedSrc& r, long i, int c) {
-  return c < r.cols ? proj_value(r.src, i, c) : 0.0;
+  return c < r.cols ? proj_value<BOTH>(r.src, i, c) : 0.0;
 }
 
 // Column sums of (a - b) over all rows; the grid's last block stores
@@ -70,7 +79,7 @@ __global__ __launch_bounds__(kBS) void k_colsum(int n, Src src, ColState* cs, Gr
   constexpr int RPB = kBS / T;
   double acc[1][1] = {{0.0}};
   for (long i = (long)blockIdx.x * RPB + t / T; i < n; i += (long)gridDim.x * RPB) {
-    acc[0][0] += proj_value(src, i, c);
+    acc[0][0] += proj_value<false>(src, i, c);
   }
   block_reduce_cols<kBS, 1, 1>(acc, T, sh);
   if (t < T) vals[t] = sh[t];
@@ -92,7 +101,7 @@ __global__ __launch_bounds__(kBS) void k_comp_mean(int ncomp, const int* perm, c
     double acc[1][1] = {{0.0}};
     for (int p = lo + t / T; p < hi; p += RPB) {
       const long i = perm[p];
-      acc[0][0] += proj_value(src, i, c);
+      acc[0][0] += proj_value<false>(src, i, c);
     }
     block_reduce_cols<kBS, 1, 1>(acc, T, sh);
     if (t < T) cmean[(long)k * kMaxTile + t] = sh[t] / (double)(hi - lo);
@@ -133,7 +142,7 @@ __global__ __launch_bounds__(kBS) void k_proj_init(int n, long cap, Src src, Mea
     const int c = (int)(e % T);
     double v = 0.0;
     if (i < n) {
-      v = proj_value(src, i, c) - mean_of(m, i, c);
+      v = proj_value<true>(src, i, c) - mean_of(m, i, c);
       acc[0][0] += v * v;
       acc[1][0] += v * v * invd[i];
     }

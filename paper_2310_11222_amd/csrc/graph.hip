@@ -395,6 +395,7 @@ static nvd_status build_graph(int64_t n64, int64_t nnz64, const int64_t* row_ptr
     comp[i] = comp_id[comp[i]];
     ++comp_off[comp[i] + 1];
   }
+  const int max_comp = ncomp > 0 ? *std::max_element(comp_off.begin() + 1, comp_off.end()) : 0;
   for (int c = 0; c < ncomp; ++c) comp_off[c + 1] += comp_off[c];
   std::vector<int> perm(n), fill(comp_off.begin(), comp_off.end() - 1);
   for (int i = 0; i < n; ++i) perm[fill[comp[i]]++] = i;   // ascending ids within a component
@@ -422,6 +423,7 @@ static nvd_status build_graph(int64_t n64, int64_t nnz64, const int64_t* row_ptr
   g->nnz_in = nnz64;
   g->weighted = wts != nullptr;
   g->n_comp = ncomp;
+  g->max_comp = max_comp;
   g->n_isolated = nisol;
   g->max_deg = maxdeg;
   g->self_loops = self_loops;

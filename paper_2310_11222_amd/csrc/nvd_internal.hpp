@@ -95,6 +95,7 @@ struct DevGraph {
   int64_t nnz_in = 0;          // nnz as passed in
   bool weighted = false;
   int n_comp = 0;
+  int max_comp = 0;            // nodes of the largest component
   int n_isolated = 0;
   int max_deg = 0;
   int self_loops = 0;

@@ -91,7 +91,12 @@ static double iteration_estimate(const DevGraph* g, int T, const SolveParams& sp
   if (g->n_comp == 1 && !sp.tree && !sp.warm && n * T <= 262144.0) return 22.0 + 8.0e-5 * n * T;   // one launch
   // (an explicit preconditioner's solve costs some twenty passes in FP64)
   const double passes = sp.tree ? 10.0 + 160.0 / es : 10.0;
-  return (sp.tree ? 60.0 : 18.0) + 2.0e-5 * g->nnz * std::max(1.0, row / 84.0) + n * row * passes / 5.5e6;
+  // several components: their means are taken by a block each, around every
+  // inner solve, and the largest one's time, most of a tile's where it is a giant
+  // one, grows with the columns (ER n = 3 10^5 of degree 10, 14 components, mixed:
+  // 2.8 ms a column; 5 pairs 22.7 ms as a tile of 8, 16.0 as 4 and 1)
+  const double means = g->n_comp > 1 ? (sp.precision == NVD_MIXED ? 4.0e-4 : 2.6e-4) * g->max_comp * T : 0.0;
+  return (sp.tree ? 60.0 : 18.0) + means + 2.0e-5 * g->nnz * std::max(1.0, row / 84.0) + n * row * passes / 5.5e6;
 }
 
 int next_tile(const DevGraph* g, int k, int left, int tile, const SolveParams& sp) {

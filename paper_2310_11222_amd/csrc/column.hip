@@ -424,27 +424,50 @@ static bool column_fits(int n, bool mixed) {
 }
 
 // Which solver takes k pairs of a graph that fits: the one with the smaller
-// estimated time of a CG iteration (us), both fitted to measured times of
-// 45 graphs (BA, WS, ER, power law; n = 10^4 .. 3.2 10^4, average degree 4 to
-// 63, k = 1, 8, 64, both precisions).
-//   A block's iteration grows with its slots (vector work) and with the
-//   graph's entries (LDS gathers), not with k: its columns run side by side.
-//   The tiled paths pay a latency for every tile of the ragged k, more with
-//   long rows and hubs, then work that grows with n and k.
-// E.g. (us per pair set, block / tiled, mixed): ER n = 10^4 d = 4 k = 8
-// 379 / 1761; WS n = 10^4 d = 32 k = 1 829 / 1377; WS n = 3.2 10^4 d = 6 k = 8
-// 3312 / 2688, k = 64 3506 / 5994; BA n = 2.4 10^4 m = 8 k = 1 820 / 705.
-static bool column_is_faster(const DevGraph* g, int k) {
-  const double nnz = g->nnz, n = g->n;
+// estimated time of a CG iteration, both fitted to measured times of 960 calls
+// (BA, WS, ER, power law; n = 500 .. 3.2 10^4, average degree 4 to 64, unit and
+// weighted, k = 1 .. 64, both precisions; half of them within 16%, nine in ten
+// within 40%).  The faster one is taken but for 1% of the time in all, 4% of the
+// calls being more than 5% slower than they could be.
+//
+// A block's iteration (us) grows with its slots (vector work) and with the
+// graph's entries (LDS gathers), not with k: its columns run side by side.  The
+// entries are read from the XCD's 4 MB L2 in every iteration, 2 bytes of index
+// and the weight each; what does not fit there costs three to four times as much
+// (n = 17,000 of degree 48, weighted, mixed: 143 us, of degree 24: 46).
+static double block_iteration(int n, int nnz, int max_deg, bool weighted, bool fp64) {
+  const double slots = (n + kColBS - 1) / kColBS, entries = nnz;
+  const double stream = entries * (weighted ? (fp64 ? 10.0 : 6.0) : 2.0);
+  return 2.6 + (fp64 ? 0.29 : 0.25) * slots + 3.6e-4 * std::max(0, n - 10 * kColBS) +
+         entries * (6.0e-5 + (weighted ? 3.4e-5 : 0.0) + (max_deg > kColHubDeg ? 4.4e-5 : 0.0)) +
+         2.3e-5 * std::max(0.0, stream - 3.5e6);
+}
+
+// An iteration of one tile of the other paths: the single launch (barriers, more
+// with long rows and hubs, which its threads and waves walk), or the multi-kernel
+// path (launches, one line per gather, and with several components their means).
+static double tile_iteration(const DevGraph* g, int T, bool fp64) {
+  const double n = g->n, nnz = g->nnz, nT = n * T, es = fp64 ? 8.0 : 4.0;
   const bool hubs = g->max_deg > kColHubDeg;
-  const double slots = (g->n + kColBS - 1) / kColBS;
-  const double block = 2.0 + 0.6 * slots + nnz * ((g->weighted ? 1.0e-4 : 6.0e-5) + (hubs ? 2.0e-5 : 0.0));
-  const double pass = g->n_comp > 1 ? 25.0 + 1.0e-3 * n : 13.0 + 0.5 * nnz / n + (hubs ? 10.0 : 0.0);
+  if (g->n_comp == 1 && nT <= 524288.0)
+    return (nT <= 2048.0 ? 2.5 : 8.0) + 0.67 * std::min(nnz / n, 40.0) + (hubs ? 14.0 : 0.0) + 7.0e-5 * nT +
+           1.2e-7 * nnz * T;
+  const double one = 29.0 + (hubs ? 18.0 : 0.0) + (1.5e-7 * nnz + 2.6e-6 * n) * T * es;
+  return g->n_comp == 1 ? one : one - 7.0 + 1.4e-4 * g->max_comp * T;
+}
+
+// E.g. (us a call, block / tiles, mixed): ER n = 10^4 d = 4 k = 8 398 / 1975; WS
+// n = 3.2 10^4 d = 8, weighted, k = 3 2246 / 2044, k = 48 2520 / 4801; BA n = 2.4
+// 10^4 m = 8 k = 1 820 / 705; ER n = 1.7 10^4 d = 64, weighted, k = 7 2405 / 606.
+static bool column_is_faster(const DevGraph* g, int k, const SolveParams& sp) {
+  const bool fp64 = sp.precision != NVD_MIXED;
+  const double block = block_iteration(g->n, g->nnz, g->max_deg, g->weighted, fp64);
+  int tile = 1;                        // (not the timed one: results repeat)
+  while (2 * tile <= std::min(k, 32)) tile *= 2;
   double tiles = 0.0;
   for (int left = k; left > 0;) {
-    int T = 64;
-    while (T > left) T >>= 1;
-    tiles += pass + (T >= 16 ? 3.0e-6 : 2.0e-6) * nnz * T;
+    const int T = next_tile(g, k, left, tile, sp);
+    tiles += tile_iteration(g, T, fp64);
     left -= T;
   }
   return block * ((k + kColChunk - 1) / kColChunk) <= tiles;
@@ -478,7 +501,7 @@ bool use_column(const DevGraph* g, int k, const SolveParams& sp) {
   // iteration, block / tiled: 5 slots 48 / 86, 17 slots and 7 pairs 115 / 113).
   if (sp.achol) return true;
   if (sp.tree) return g->n <= 14 * kColBS || k > 8;
-  return column_is_faster(g, k);
+  return column_is_faster(g, k, sp);
 }
 
 // A pair that FP32 cannot finish on a graph whose FP64 vector does not fit:

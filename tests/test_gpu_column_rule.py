@@ -1,0 +1,32 @@
+"""The choice between a block per column and tiles, where both were timed and
+one is faster by half or more: dense weighted graphs, whose entries do not stay
+in the L2 that a block reads them from, against sparse and small ones."""
+import numpy as np
+import pytest
+
+from gpu_helpers import dev_graph, say
+from nvdgen.graphs import barabasi_albert, watts_strogatz
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("model,n,d,weighted,precision,k,blocks", [
+    ("ws", 17000, 48, True, "mixed", 7, False), ("ws", 20000, 48, True, "mixed", 27, False),
+    ("ws", 13000, 48, True, "fp64", 5, False), ("ws", 28000, 48, True, "mixed", 27, False),
+    ("ws", 500, 8, False, "fp64", 1, True), ("ws", 10007, 16, True, "fp64", 5, True),
+    ("ba", 10000, 8, False, "mixed", 8, True), ("ws", 28000, 6, False, "mixed", 48, True),
+    ("ba", 17000, 4, True, "mixed", 16, True), ("ws", 4000, 24, True, "mixed", 1, True)])
+def test_faster_solver_is_taken(monkeypatch, model, n, d, weighted, precision, k, blocks):
+    rng = np.random.default_rng(n + k)
+    g = watts_strogatz(n, d, 0.1, rng) if model == "ws" else barabasi_albert(n, d, rng)
+    if weighted:
+        g = g.with_weights(rng.uniform(0.5, 2.0, g.num_edges))
+    P, Q = rng.random((n, k)), rng.random((n, k))
+    say("column rule", model, n, d, weighted, precision, k)
+    dg = dev_graph(g)
+    dg.distances(P, Q, precision=precision, rtol=1e-6)
+    first = dg.stats()["device_bytes"]
+    monkeypatch.setenv("NVD_COLUMN", "0")
+    dg.distances(P, Q, precision=precision, rtol=1e-6)
+    # (tiles need a workspace that a call by blocks does not make)
+    assert (dg.stats()["device_bytes"] > first) == blocks

@@ -473,6 +473,20 @@ static bool column_is_faster(const DevGraph* g, int k, const SolveParams& sp) {
   return block * ((k + kColChunk - 1) / kColChunk) <= tiles;
 }
 
+// The same with the forest: a block's iteration grows with its slots (two forest
+// solves where there are off-forest edges to augment it with), that of tiles of up
+// to eight pairs hardly with anything (us, block / tiles of 1, of 3 and of 8 pairs;
+// BA m = 2 n = 11,000 mixed 83 / 121, 101, 107, n = 14,000 100 / 117, 97, 103, FP64
+// 104 / 119, 94, 102, n = 17,000 114 / 119, 104, 114, FP64 119 / 120, 102, 112); of
+// sixteen pairs 120 to 140, where the block still takes 114 (FP64 120).
+static bool forest_is_faster(const DevGraph* g, int k, const SolveParams& sp) {
+  const long off = (long)g->nnz / 2 - g->n + g->n_comp;
+  if (k > 8 || off == 0) return true;
+  const double slots = (g->n + kColBS - 1) / kColBS;
+  const double block = 19.0 + (sp.precision == NVD_MIXED ? 5.7 : 6.1) * slots;
+  return block <= (k == 1 ? 118.0 : (k <= 4 ? 98.0 : 103.0));
+}
+
 bool column_gives_way(DevGraph* g, nvd_status st) {
   if (st != NVD_E_UNSUPPORTED && st != NVD_E_NOMEM) return false;
   if (st == NVD_E_NOMEM) {
@@ -495,12 +509,12 @@ bool use_column(const DevGraph* g, int k, const SolveParams& sp) {
   if (std::getenv("NVD_MID_BLOCKS")) return false;
   if (const char* c = std::getenv("NVD_COLUMN")) return c[0] != '0';   // 0 never, 1 wherever it fits
   // An explicit preconditioner costs the tiled path ten to hundreds of launches
-  // an iteration (the factor two for every round: BA n = 10^4, 8 pairs, 16.5
-  // ms; in blocks 2.0), so the block is taken wherever it fits, except for a
-  // few pairs with the augmented forest on its largest graphs (us an
-  // iteration, block / tiled: 5 slots 48 / 86, 17 slots and 7 pairs 115 / 113).
+  // an iteration.  The factor has two for every round (BA n = 10^4, 8 pairs, 16.5
+  // ms; in blocks 2.0), and the block is taken wherever it fits: also on the
+  // densest graphs measured (ER n = 14,000 of degree 32, 1.1M entries in the
+  // factor, one pair, FP64) it took 16.0 ms against 27.9.
   if (sp.achol) return true;
-  if (sp.tree) return g->n <= 14 * kColBS || k > 8;
+  if (sp.tree) return forest_is_faster(g, k, sp);
   return column_is_faster(g, k, sp);
 }
 

@@ -30,3 +30,20 @@ def test_faster_solver_is_taken(monkeypatch, model, n, d, weighted, precision, k
     dg.distances(P, Q, precision=precision, rtol=1e-6)
     # (tiles need a workspace that a call by blocks does not make)
     assert (dg.stats()["device_bytes"] > first) == blocks
+
+
+@pytest.mark.parametrize("n,precision,k,blocks", [
+    (14183, "mixed", 4, False), (14183, "fp64", 4, False), (17000, "fp64", 8, False), (17000, "mixed", 3, False),
+    (14183, "mixed", 1, True), (10000, "fp64", 4, True), (17000, "fp64", 16, True), (6000, "mixed", 8, True)])
+def test_faster_solver_is_taken_with_a_forest(monkeypatch, n, precision, k, blocks):
+    """Two edges a node: the forest is augmented, and costs a block two solves."""
+    rng = np.random.default_rng(n + k)
+    g = barabasi_albert(n, 2, rng)
+    P, Q = rng.random((n, k)), rng.random((n, k))
+    say("forest rule", n, precision, k)
+    dg = dev_graph(g)
+    dg.distances(P, Q, precision=precision, rtol=1e-6, precond="tree")
+    first = dg.stats()["device_bytes"]
+    monkeypatch.setenv("NVD_COLUMN", "0")
+    dg.distances(P, Q, precision=precision, rtol=1e-6, precond="tree")
+    assert (dg.stats()["device_bytes"] > first) == blocks

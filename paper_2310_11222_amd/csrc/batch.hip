@@ -1288,7 +1288,7 @@ extern "C" nvd_status nvd_batch_distances(nvd_batch* b, const int32_t* k_per_gra
   const bool mixed = o.precision == NVD_MIXED;
   auto solve = [&]() -> nvd_status {
     if (!(o.flags & NVD_BATCH_PERSISTENT)) {
-      if (b->col && use_column_batch(b->col, mixed)) {
+      if (b->col && use_column_batch(b->col, ks, mixed)) {
         NVD_TRY(solve_column_batch(b->col, ks, o, P, Q, d_out, X_out, hinfo.data(), &b->bytes, s));
         ++b->eager;
         note_iterations(b, ks, hinfo.data());

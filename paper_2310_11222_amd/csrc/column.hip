@@ -433,14 +433,18 @@ static bool column_fits(int n, bool mixed) {
 // A block's iteration (us) grows with its slots (vector work) and with the
 // graph's entries (LDS gathers), not with k: its columns run side by side.  The
 // entries are read from the XCD's 4 MB L2 in every iteration, 2 bytes of index
-// and the weight each; what does not fit there costs three to four times as much
-// (n = 17,000 of degree 48, weighted, mixed: 143 us, of degree 24: 46).
+// and the weight each; beyond it an entry costs two to three times as much,
+// however many there are (n = 17,000 weighted, mixed, of degree 24: 46 us, of
+// degree 48: 143; n = 6,000, unit, of degree 200: 71, of degree 500: 440).
+static double stream_bytes(int nnz, bool weighted, bool fp64) {
+  return (double)nnz * (weighted ? (fp64 ? 10.0 : 6.0) : 2.0);
+}
 static double block_iteration(int n, int nnz, int max_deg, bool weighted, bool fp64) {
-  const double slots = (n + kColBS - 1) / kColBS, entries = nnz;
-  const double stream = entries * (weighted ? (fp64 ? 10.0 : 6.0) : 2.0);
+  const double slots = (n + kColBS - 1) / kColBS;
+  const double near = 6.0e-5 + (weighted ? 3.4e-5 : 0.0) + (max_deg > kColHubDeg ? 4.4e-5 : 0.0);
+  const double beyond = std::min(1.0, std::max(0.0, (stream_bytes(nnz, weighted, fp64) - 3.5e6) / 2.0e6));
   return 2.6 + (fp64 ? 0.29 : 0.25) * slots + 3.6e-4 * std::max(0, n - 10 * kColBS) +
-         entries * (6.0e-5 + (weighted ? 3.4e-5 : 0.0) + (max_deg > kColHubDeg ? 4.4e-5 : 0.0)) +
-         2.3e-5 * std::max(0.0, stream - 3.5e6);
+         nnz * (near + beyond * (1.9e-4 - near));
 }
 
 // An iteration of one tile of the other paths: the single launch (barriers, more
@@ -629,9 +633,7 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
 // batches of small graphs
 // ---------------------------------------------------------------------------
 // Every (graph, pair) is a block, the longest first.  Taken where every graph
-// of the batch fits (ms a call, block / sweep: 12 graphs of up to 6,600 nodes,
-// 7 pairs mixed 0.65 / 4.8; 47 up to 9,900, 5 pairs 1.2 / 6.4; 64 up to 17,000,
-// 16 pairs 4.5 / 13.0).
+// of the batch fits, by the rule of batch_is_faster.
 // Beside a sweep over larger graphs the blocks took from it what they saved
 // (62 graphs up to 37,000 nodes, 14 pairs: 18.6 / 18.0): such batches are
 // swept whole.  Beyond 24 slots a block's iteration takes longer than the
@@ -650,7 +652,7 @@ struct ColChunk {
 
 struct ColBatch {
   std::vector<ColGraph> h;         // the graphs' layouts (on the host)
-  std::vector<int> weighted;
+  std::vector<int> weighted, nnz, max_deg;
   int most = 0;                    // nodes of the largest
   unsigned char* blob = nullptr;
   double* weights = nullptr;
@@ -718,6 +720,8 @@ static nvd_status lay_out_batch(int G, const DevGraph* const* graphs, hipStream_
     at += weight_doubles(g->weighted ? lay[i].src.size() : 0, d.slots * kColBS);
     c->h.push_back(d);
     c->weighted.push_back(g->weighted ? 1 : 0);
+    c->nnz.push_back(g->nnz);
+    c->max_deg.push_back(g->max_deg);
   }
   if (e == hipSuccess && st == NVD_OK)
     e = hipMemcpyAsync(c->dev, c->h.data(), sizeof(ColGraph) * G, hipMemcpyHostToDevice, s);
@@ -752,9 +756,45 @@ nvd_status make_column_batch(int G, const DevGraph* const* graphs, hipStream_t s
   return st;
 }
 
-bool use_column_batch(const ColBatch* c, bool mixed) {
-  const char* e = std::getenv("NVD_COLUMN");
-  return !(e && e[0] == '0') && column_fits(c->most, mixed);
+// Blocks or the sweep: the smaller of an iteration's estimates (us), of blocks the
+// longest pair's or what all pairs take on 256 CUs, of the sweep its launches and
+// its gathers over all graphs, and again over the largest, which one XCD has.
+// Blocks win nearly everywhere (392 batches of 2 to 64 graphs up to 24,000 nodes
+// of degree 4 to 120, 1 to 64 pairs: 0.03 to 0.8 of the sweep's time; ms a call,
+// block / sweep: 47 graphs up to 9,900 nodes, 5 pairs 1.2 / 6.4; 64 up to 17,000,
+// 16 pairs 4.5 / 13.0), also on dense graphs whose rows the sweep cuts into
+// segments (n = 20,000 of degree 200, one pair 20 / 43).  They lose with few pairs
+// on a few graphs whose entries leave the L2 in rows that the sweep does not cut
+// (2 of n = 16,000, degree 120, 4 pairs: 8.6 / 3.3).  Both estimates are off by half
+// at times, so blocks are left only where they look slower by as much.
+static bool batch_is_faster(const ColBatch* c, const std::vector<int>& ks, bool fp64) {
+  double longest = 0.0, all = 0.0, entries = 0.0, cut = 0.0;
+  int kmax = 1;
+  size_t big = 0;
+  for (size_t g = 0; g < c->h.size(); ++g) {
+    const double t = block_iteration(c->h[g].n, c->nnz[g], c->max_deg[g], c->weighted[g] != 0, fp64);
+    if (t > longest) {
+      longest = t;
+      big = g;
+    }
+    all += t * ks[g];
+    entries += c->nnz[g];
+    kmax = std::max(kmax, ks[g]);
+    if ((double)c->nnz[g] > (double)kLongRow * c->h[g].n) cut = std::max(cut, (double)c->h[g].n);
+  }
+  if (stream_bytes(c->nnz[big], c->weighted[big] != 0, fp64) <= 3.5e6) return true;
+  int T = 1;
+  while (T < kmax) T *= 2;
+  const double es = fp64 ? 8.0 : 4.0;
+  const double sweep = 22.0 + 1.5 * T + (2.0e-7 * entries + 1.0e-6 * c->nnz[big]) * T * es +
+                       (cut > 0.0 ? cut * (T < 4 ? 0.066 : 0.095) : 3.7e-5 * c->nnz[big]);
+  return std::max(longest, all / 256.0) <= (cut > 0.0 ? 1.3 : 1.6) * sweep;
+}
+
+bool use_column_batch(const ColBatch* c, const std::vector<int>& ks, bool mixed) {
+  if (!column_fits(c->most, mixed)) return false;
+  if (const char* e = std::getenv("NVD_COLUMN")) return e[0] != '0';   // 0 never, 1 wherever it fits
+  return batch_is_faster(c, ks, !mixed);
 }
 
 nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd_opts& o, const double* P,

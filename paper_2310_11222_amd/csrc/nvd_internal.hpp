@@ -278,7 +278,7 @@ bool column_gives_way(DevGraph* g, nvd_status st);
 struct ColBatch;
 nvd_status make_column_batch(int G, const DevGraph* const* graphs, hipStream_t s, ColBatch** out,
                              int64_t* bytes);
-bool use_column_batch(const ColBatch* c, bool mixed);
+bool use_column_batch(const ColBatch* c, const std::vector<int>& ks, bool mixed);
 nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd_opts& o, const double* P,
                               const double* Q, double* d_out, double* X, nvd_pair_info* info, int64_t* bytes,
                               hipStream_t s);

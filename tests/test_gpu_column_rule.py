@@ -47,3 +47,19 @@ def test_faster_solver_is_taken_with_a_forest(monkeypatch, n, precision, k, bloc
     monkeypatch.setenv("NVD_COLUMN", "0")
     dg.distances(P, Q, precision=precision, rtol=1e-6, precond="tree")
     assert (dg.stats()["device_bytes"] > first) == blocks
+
+
+@pytest.mark.parametrize("n,d,k,G,blocks", [(16000, 120, 4, 2, False), (16000, 120, 64, 4, True),
+                                            (9000, 12, 1, 2, True), (6000, 200, 4, 2, True)])
+def test_faster_solver_is_taken_for_a_batch(n, d, k, G, blocks):
+    """Few pairs on few graphs whose entries leave the L2 are swept (a call by
+    blocks counts as launched directly)."""
+    import paper_2310_11222_amd as nvd
+    rng = np.random.default_rng(n + d)
+    g = watts_strogatz(n, d, 0.1, rng)
+    dg = dev_graph(g)
+    batch = nvd.Batch([dg] * G)
+    say("batch rule", n, d, k, G)
+    P = [rng.random((n, k)) for _ in range(G)]
+    batch.distances(P, [p[::-1].copy() for p in P])
+    assert batch.query()["eager"] == (1 if blocks else 0)

@@ -203,16 +203,27 @@ nvd_status nvd_graph_query(const nvd_graph* h, int32_t* labels, double* degree) 
   return NVD_OK;
 }
 
-// Whether `left` columns go into one pass L = 2 T lanes wide rather than a pass
-// for the widest power of two and others for the rest.  One lane an element
-// is no loss up to 16 lanes.  Wider, two passes with 16-byte vectors are as
-// fast or faster (us, one / two passes, FP32 on a 3 10^5-node power-law graph:
-// 24 columns 135 / 108, 48 columns 245 / 126), three are not (28 columns 139 /
-// 175).  A small graph's passes cost their launches alone (3,000 nodes, 48
-// columns: 16 / 28).
-static bool one_ragged_pass(const DevGraph* g, int left, int L) {
+// Whether `left` columns go into one pass L lanes wide (the next power of two)
+// rather than a pass for the widest power of two in them and others for the
+// rest.  A small graph's passes cost their launches alone (3,000 nodes, 48
+// columns: 16 us as one / 28).  Beyond (us, one / passes):
+//  * neighbours anywhere: every pass asks for the same lines beyond the L2, and
+//    one lane an element is no loss up to 16 lanes (power law n = 3 10^5: 3
+//    columns FP32 46 / 58, FP64 57 / 77; 12 columns FP64 97 / 107).  Wider, two
+//    passes with 16-byte vectors are as fast or faster (FP32, 24 columns 135 /
+//    108, 48 columns 245 / 126), three are not (28 columns FP32 146 / 175, FP64
+//    157 / 197).
+//  * neighbours near their rows: a pass finds them in the L2 and is bound by its
+//    instructions, of which one lane an element has up to four times as many
+//    (WS n = 5 10^5 of degree 8: 3 columns FP32 22 / 28, FP64 25 / 33; 5 columns
+//    39 / 31 and 42 / 40; 7 columns 40 / 48 and 41 / 65; 12 columns 69 / 40 and 72
+//    / 50; 13 columns 70 / 66 and 73 / 92; 15 columns 69 / 90; 28 columns 127 / 88
+//    and 134 / 105; 31 columns 127 / 162): it has to save two or three passes.
+static bool one_ragged_pass(const DevGraph* g, int left, int L, bool fp64) {
   if ((long)g->nnz * L <= 2L << 20) return true;
-  return L <= 16 || (L == 32 && __builtin_popcount(left) >= 3);
+  const int passes = __builtin_popcount(left);
+  if (g->near) return L <= 4 || (L <= 32 && passes >= (L <= 8 || (L <= 16 && fp64) ? 3 : 4));
+  return L <= 16 || (L == 32 && passes >= 3);
 }
 
 nvd_status nvd_laplacian_apply(nvd_graph* h, int32_t dtype, int32_t k, const void* X,
@@ -242,7 +253,7 @@ nvd_status nvd_laplacian_apply(nvd_graph* h, int32_t dtype, int32_t k, const voi
     sc.ldy = ldy;
     sc.epi = EPI_PLAIN;
     const int left = k - c0;
-    if (left > T && left < 64 && one_ragged_pass(g, left, 2 * T)) {
+    if (left > T && left < 64 && one_ragged_pass(g, left, 2 * T, dtype == NVD_DT_F64)) {
       sc.T = 2 * T;
       NVD_TRY(launch_ragged(sc, left, as_stream(stream)));
       return NVD_OK;

@@ -424,6 +424,19 @@ static nvd_status build_graph(int64_t n64, int64_t nnz64, const int64_t* row_ptr
   g->weighted = wts != nullptr;
   g->n_comp = ncomp;
   g->max_comp = max_comp;
+  {
+    // a sample of the rows: are their neighbours within a thirty-second of the nodes?
+    const int within = std::min(16384, n / 32);
+    long seen = 0, inside = 0;
+    for (int i = 0; i < 1024; ++i) {
+      const int r = (int)((long)i * n / 1024);
+      for (int e = rp[r]; e < rp[r + 1] && e < rp[r] + 64; ++e) {
+        ++seen;
+        inside += std::abs((long)ci[e] - r) <= within;
+      }
+    }
+    g->near = 2 * inside > seen;
+  }
   g->n_isolated = nisol;
   g->max_deg = maxdeg;
   g->self_loops = self_loops;

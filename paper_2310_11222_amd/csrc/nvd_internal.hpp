@@ -96,6 +96,7 @@ struct DevGraph {
   bool weighted = false;
   int n_comp = 0;
   int max_comp = 0;            // nodes of the largest component
+  bool near = false;           // most neighbours lie near their row in the node order (a lattice, a road network)
   int n_isolated = 0;
   int max_deg = 0;
   int self_loops = 0;

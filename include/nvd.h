@@ -221,9 +221,10 @@ nvd_status nvd_graph_query(const nvd_graph* g, int32_t* labels_host,
  * of at least 2^20 nodes may be applied by column slices: the nodes are cut
  * into slices whose part of X fits in LDS, the entries' values of X are
  * gathered there and written in slice order, and the rows are then summed
- * from them in CSR order.  The first such call of each precision builds the slice structure
- * on the host, times both forms of the apply on its X and keeps the faster
- * for the graph (that call waits for the device and then enqueues).  The
+ * from them in CSR order.  The first such call of each precision builds the
+ * slice structure on the host, times both forms of the apply on its X and
+ * takes the slices for the graph where they are a tenth faster (that call
+ * waits for the device and then enqueues).  The
  * structure is kept with the graph while one precision uses it (device
  * memory: about 12 bytes per CSR entry), across nvd_graph_set_weights, and
  * dropped by nvd_graph_destroy.  nvd_distances_noalloc never

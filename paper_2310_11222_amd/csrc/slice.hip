@@ -62,7 +62,12 @@ constexpr int kSlChunk = 16384;
 // Entries above which a row is summed by a group of 16 lanes, and by its wave.
 constexpr int kSlGroupRow = 16;
 constexpr int kSlWaveRow = 256;
-constexpr int kSlMinN = 1 << 20;     // graphs this large try the slices by default
+// Graphs this large try the slices by default.  Below, x stays near enough (us row
+// by row / sliced: power law n = 5.2 10^5 FP64 45 / 47, FP32 35 / 40, n = 2.6 10^5
+// 25 / 58 and 22 / 53; ER n = 5.2 10^5 of degree 6 23 / 43); from here on it
+// depends on the graph, and both are timed (power law n = 1.05 10^6 93 / 63 and 66
+// / 43; BA n = 1.3 10^6 87 / 152 and 59 / 89).
+constexpr int kSlMinN = 1 << 20;
 // Blocks of both kernels: what 256 CUs hold at once.
 template <typename V>
 constexpr int kSlBlocks = sizeof(V) == 8 ? 256 : 512;
@@ -473,7 +478,9 @@ static nvd_status build_slices(DevGraph* g) {
     r = e;
   }
   const int nch = (int)row0.size() - 1;
-  if ((long)S * (nch + 1) > (1L << 28)) {   // the runs would average less than a few entries
+  // Runs of three to four entries (10^8 nodes, 7.6 10^8 entries) no longer pay: n =
+  // 1.3 10^8, ms sliced / row by row, FP32 23.2 / 19.9, FP64 17.9 / 19.0.
+  if ((long)S * (nch + 1) > (1L << 28)) {
     set_error("slices: graph too large for the sliced apply");
     return NVD_E_UNSUPPORTED;
   }
@@ -627,9 +634,14 @@ static nvd_status launch_sliced(const SpmmCall& c, const GridRed& red, hipStream
   return st;
 }
 
+// The sliced form has to be faster by a tenth: on one x again and again, both run
+// from warm caches, which the row-wise one is the less dependent on (ER n = 1.065
+// 10^6 of degree 3, weighted, FP64: timed so 42.7 against 41.0 us, 43.0 against
+// 45.7 with a new x each time).
+constexpr float kSlGain = 0.9f;
+
 // Time the row-wise and the sliced apply of this call's x (EPI_PLAIN into a
-// scratch y, 3 launches each after a warm-up) and keep the faster per
-// precision.
+// scratch y, 3 launches each after a warm-up).
 template <typename V>
 static nvd_status time_forms(DevGraph* g, const SpmmCall& c, const GridRed& red, hipStream_t s, float* t_row,
                              float* t_sliced) {
@@ -685,7 +697,7 @@ static bool use_slices(DevGraph* g, const SpmmCall& c, const GridRed& red, hipSt
     float tr = 0.0f, ts = 0.0f;
     const nvd_status st = c.prec == 0 ? time_forms<double>(g, c, red, s, &tr, &ts)
                                       : time_forms<float>(g, c, red, s, &tr, &ts);
-    g->slice_pick[p] = (st == NVD_OK && ts < tr) ? 1 : -1;
+    g->slice_pick[p] = (st == NVD_OK && ts < kSlGain * tr) ? 1 : -1;
     if (g->slice_pick[0] < 0 && g->slice_pick[1] < 0) {
       free_slices(g);
       return false;

@@ -943,7 +943,7 @@ nvd_status nvd_batch_create(int32_t G, nvd_graph* const* graphs, void* stream, n
   if (st == NVD_OK) {
     std::vector<const DevGraph*> gs(G);
     for (int i = 0; i < G; ++i) gs[i] = graphs[i]->g;
-    st = make_column_batch(G, gs.data(), s, &b->col, &b->bytes);
+    b->col = make_column_batch(G, gs.data());
   }
   if (st != NVD_OK) {
     batch_free(b);
@@ -1289,7 +1289,8 @@ extern "C" nvd_status nvd_batch_distances(nvd_batch* b, const int32_t* k_per_gra
   auto solve = [&]() -> nvd_status {
     if (!(o.flags & NVD_BATCH_PERSISTENT)) {
       if (b->col && use_column_batch(b->col, ks, mixed)) {
-        NVD_TRY(solve_column_batch(b->col, ks, o, P, Q, d_out, X_out, hinfo.data(), &b->bytes, s));
+        const ColBatchArrays arrays{b->w64, b->invd64, b->invd32, b->nnz_off.data(), b->node_off.data()};
+        NVD_TRY(solve_column_batch(b->col, arrays, ks, o, P, Q, d_out, X_out, hinfo.data(), &b->bytes, s));
         ++b->eager;
         note_iterations(b, ks, hinfo.data());
         return NVD_OK;

@@ -27,6 +27,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <numeric>
 #include <thread>
@@ -334,20 +335,20 @@ static nvd_status build_column(DevGraph* g) {
 // Doubles that the weights and 1 / degrees of a layout take (FP64 and FP32).
 static size_t weight_doubles(size_t entries, int npad) { return (12 * (entries + (size_t)npad) + 7) / 8; }
 
-// Where they go: at `at` (weight_doubles of it), and filled from the graph's.
-static nvd_status put_weights(const DevGraph* g, ColGraph* d, size_t entries, const int* src, double* at,
-                              hipStream_t s) {
+// Where they go: at `at` (weight_doubles of it), and filled from the graph's
+// (w64 null: unit weights).
+static nvd_status put_weights(const double* w64, const double* invd64, const float* invd32, ColGraph* d,
+                              size_t entries, const int* src, double* at, hipStream_t s) {
   const int npad = d->slots * kColBS;
-  const size_t sw = g->weighted ? entries : 0;
+  const size_t sw = w64 ? entries : 0;
   float* f = reinterpret_cast<float*>(at + sw + npad);
-  d->w64 = g->weighted ? reinterpret_cast<const double2*>(at) : nullptr;
+  d->w64 = w64 ? reinterpret_cast<const double2*>(at) : nullptr;
   d->inv64 = at + sw;
-  d->w32 = g->weighted ? reinterpret_cast<const float2*>(f) : nullptr;
+  d->w32 = w64 ? reinterpret_cast<const float2*>(f) : nullptr;
   d->inv32 = f + sw;
   const int work = std::max((int)entries, npad);
-  k_column_weights<<<std::min(1024, (work + 255) / 256), 256, 0, s>>>(
-      (int)entries, src, g->n, npad, d->perm, g->weighted ? g->w64 : nullptr, g->invd64, g->invd32, at, f,
-      at + sw, f + sw);
+  k_column_weights<<<std::min(1024, (work + 255) / 256), 256, 0, s>>>((int)entries, src, d->n, npad, d->perm, w64,
+                                                                      invd64, invd32, at, f, at + sw, f + sw);
   NVD_HIP(hipGetLastError());
   return NVD_OK;
 }
@@ -370,7 +371,8 @@ static nvd_status ensure_column(DevGraph* g, hipStream_t s) {
     cp->bytes += cp->weight_bytes;
     g->bytes += cp->weight_bytes;
   }
-  NVD_TRY(put_weights(g, &cp->d, cp->entries, cp->src, cp->weights, s));
+  NVD_TRY(put_weights(g->weighted ? g->w64 : nullptr, g->invd64, g->invd32, &cp->d, cp->entries, cp->src,
+                      cp->weights, s));
   cp->stale = false;
   return NVD_OK;
 }
@@ -651,7 +653,11 @@ struct ColChunk {
 };
 
 struct ColBatch {
-  std::vector<ColGraph> h;         // the graphs' layouts (on the host)
+  // the graphs' layouts: their counts, and their arrays in host memory until a
+  // call is solved by blocks (others hold nothing of them on the device)
+  std::vector<ColGraph> h;
+  std::vector<unsigned char> host;
+  std::vector<size_t> o_src, entries;
   std::vector<int> weighted, nnz, max_deg;
   int most = 0;                    // nodes of the largest
   unsigned char* blob = nullptr;
@@ -675,8 +681,7 @@ void free_column_batch(ColBatch* c, int64_t* bytes) {
   delete c;
 }
 
-static nvd_status lay_out_batch(int G, const DevGraph* const* graphs, hipStream_t s, ColBatch** out,
-                                int64_t* bytes) {
+static nvd_status lay_out_batch(int G, const DevGraph* const* graphs, ColBatch** out) {
   int most = 0;
   for (int i = 0; i < G; ++i) most = std::max(most, graphs[i]->n_comp == 1 ? graphs[i]->n : INT32_MAX);
   if (most > kColBatchNodes) return NVD_OK;
@@ -699,61 +704,78 @@ static nvd_status lay_out_batch(int G, const DevGraph* const* graphs, hipStream_
   for (auto& x : th) x.join();
   if (failed) return NVD_E_NOMEM;
   Blob bl;
-  size_t nw = 0;
-  for (int i = 0; i < G; ++i) {
-    lay[i].put(&bl);
-    nw += weight_doubles(graphs[i]->weighted ? lay[i].src.size() : 0, lay[i].d.slots * kColBS);
-  }
-  ColBatch* c = new ColBatch();
+  std::unique_ptr<ColBatch> c(new ColBatch());
   c->most = most;
-  nvd_status st = NVD_OK;
-  hipError_t e = device_alloc((void**)&c->blob, bl.h.size());
-  if (e == hipSuccess) e = device_alloc((void**)&c->weights, sizeof(double) * nw);
-  if (e == hipSuccess) e = device_alloc((void**)&c->dev, sizeof(ColGraph) * G);
-  if (e == hipSuccess) e = hipMemcpyAsync(c->blob, bl.h.data(), bl.h.size(), hipMemcpyHostToDevice, s);
-  size_t at = 0;
-  for (int i = 0; e == hipSuccess && st == NVD_OK && i < G; ++i) {
+  for (int i = 0; i < G; ++i) {
     const DevGraph* g = graphs[i];
-    ColGraph d = place(lay[i].d, c->blob);
-    st = put_weights(g, &d, lay[i].src.size(), reinterpret_cast<const int*>(c->blob + lay[i].o_src),
-                     c->weights + at, s);
-    at += weight_doubles(g->weighted ? lay[i].src.size() : 0, d.slots * kColBS);
-    c->h.push_back(d);
+    lay[i].put(&bl);
+    c->h.push_back(lay[i].d);
+    c->o_src.push_back(lay[i].o_src);
+    c->entries.push_back(lay[i].src.size());
     c->weighted.push_back(g->weighted ? 1 : 0);
     c->nnz.push_back(g->nnz);
     c->max_deg.push_back(g->max_deg);
+    lay[i] = ColLayout();
   }
-  if (e == hipSuccess && st == NVD_OK)
-    e = hipMemcpyAsync(c->dev, c->h.data(), sizeof(ColGraph) * G, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess && st == NVD_OK) {
-    set_error(std::string("nvd_batch_create: ") + hipGetErrorString(e));
-    st = e == hipErrorOutOfMemory ? NVD_E_NOMEM : NVD_E_DEVICE;
-  }
-  if (st != NVD_OK) {
-    free_column_batch(c, bytes);
-    return st;
-  }
-  c->bytes = (int64_t)(bl.h.size() + sizeof(double) * nw + sizeof(ColGraph) * G);
-  *bytes += c->bytes;
-  *out = c;
+  c->host = std::move(bl.h);
+  *out = c.release();
   return NVD_OK;
 }
 
-nvd_status make_column_batch(int G, const DevGraph* const* graphs, hipStream_t s, ColBatch** out,
-                             int64_t* bytes) {
-  *out = nullptr;
+// The layouts on the device, with the weights of the batch's graphs.
+static nvd_status upload_batch(ColBatch* c, const ColBatchArrays& b, int64_t* bytes, hipStream_t s) {
+  if (c->dev) return NVD_OK;
+  const size_t G = c->h.size();
+  auto doubles = [&](size_t i) {
+    return weight_doubles(c->weighted[i] ? c->entries[i] : 0, c->h[i].slots * kColBS);
+  };
+  size_t nw = 0;
+  for (size_t i = 0; i < G; ++i) nw += doubles(i);
+  ColGraph* dev = nullptr;
   nvd_status st = NVD_OK;
+  hipError_t e = device_alloc((void**)&c->blob, c->host.size());
+  if (e == hipSuccess) e = device_alloc((void**)&c->weights, sizeof(double) * nw);
+  if (e == hipSuccess) e = device_alloc((void**)&dev, sizeof(ColGraph) * G);
+  if (e == hipSuccess) e = hipMemcpyAsync(c->blob, c->host.data(), c->host.size(), hipMemcpyHostToDevice, s);
+  std::vector<ColGraph> placed;
+  size_t at = 0;
+  for (size_t i = 0; e == hipSuccess && st == NVD_OK && i < G; ++i) {
+    ColGraph d = place(c->h[i], c->blob);
+    st = put_weights(c->weighted[i] ? b.w64 + b.nnz_off[i] : nullptr, b.invd64 + b.node_off[i],
+                     b.invd32 + b.node_off[i], &d, c->entries[i],
+                     reinterpret_cast<const int*>(c->blob + c->o_src[i]), c->weights + at, s);
+    at += doubles(i);
+    placed.push_back(d);
+  }
+  if (e == hipSuccess && st == NVD_OK)
+    e = hipMemcpyAsync(dev, placed.data(), sizeof(ColGraph) * G, hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess && st == NVD_OK) {
+    set_error(std::string("batch layouts: ") + hipGetErrorString(e));
+    st = e == hipErrorOutOfMemory ? NVD_E_NOMEM : NVD_E_DEVICE;
+  }
+  if (st != NVD_OK) {
+    for (void* p : {(void*)c->blob, (void*)c->weights, (void*)dev}) (void)hipFree(p);
+    c->blob = nullptr;
+    c->weights = nullptr;
+    return st;
+  }
+  c->dev = dev;
+  const int64_t held = (int64_t)(c->host.size() + sizeof(double) * nw + sizeof(ColGraph) * G);
+  c->bytes += held;
+  *bytes += held;
+  std::vector<unsigned char>().swap(c->host);
+  return NVD_OK;
+}
+
+ColBatch* make_column_batch(int G, const DevGraph* const* graphs) {
+  ColBatch* c = nullptr;
   try {
-    st = lay_out_batch(G, graphs, s, out, bytes);
+    if (lay_out_batch(G, graphs, &c) != NVD_OK) return nullptr;
   } catch (const std::bad_alloc&) {
-    st = NVD_E_NOMEM;
+    return nullptr;                // (out of host memory: the batch is swept)
   }
-  if (st == NVD_E_NOMEM) {         // the batch is swept
-    set_error("");
-    st = NVD_OK;
-  }
-  return st;
+  return c;
 }
 
 // Blocks or the sweep: the smaller of an iteration's estimates (us), of blocks the
@@ -797,9 +819,11 @@ bool use_column_batch(const ColBatch* c, const std::vector<int>& ks, bool mixed)
   return batch_is_faster(c, ks, !mixed);
 }
 
-nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd_opts& o, const double* P,
+nvd_status solve_column_batch(ColBatch* c, const ColBatchArrays& arrays, const std::vector<int>& ks,
+                              const nvd_opts& o, const double* P,
                               const double* Q, double* d_out, double* X, nvd_pair_info* info, int64_t* bytes,
-                              hipStream_t s) {
+                              hipStream_t s) try {
+  NVD_TRY(upload_batch(c, arrays, bytes, s));
   const int G = (int)c->h.size();
   int K = 0;
   for (const int k : ks) K += k;
@@ -893,6 +917,9 @@ nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd
   NVD_HIP(hipStreamSynchronize(s));
   std::copy(c->ws.info, c->ws.info + K, info);
   return NVD_OK;
+} catch (const std::bad_alloc&) {
+  set_error("batch solve: out of host memory");
+  return NVD_E_NOMEM;
 }
 
 }  // namespace nvd

@@ -274,14 +274,22 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
 // augmenting edges than a block takes, or no memory for the layout or the
 // scratch (what there is of them is given back, and not tried again).
 bool column_gives_way(DevGraph* g, nvd_status st);
-// A batch of small graphs in the same way (column.hip); *out is null where it
-// has larger ones, or where there is no memory for their layouts.
+// A batch of small graphs in the same way (column.hip); null where it has larger
+// ones, or where there is no memory for their layouts.
 struct ColBatch;
-nvd_status make_column_batch(int G, const DevGraph* const* graphs, hipStream_t s, ColBatch** out,
-                             int64_t* bytes);
+ColBatch* make_column_batch(int G, const DevGraph* const* graphs);
+// The batch's packed weights and inverse degrees (on the device) and where each
+// graph's start.
+struct ColBatchArrays {
+  const double* w64;
+  const double* invd64;
+  const float* invd32;
+  const long* nnz_off;
+  const long* node_off;
+};
 bool use_column_batch(const ColBatch* c, const std::vector<int>& ks, bool mixed);
-nvd_status solve_column_batch(ColBatch* c, const std::vector<int>& ks, const nvd_opts& o, const double* P,
-                              const double* Q, double* d_out, double* X, nvd_pair_info* info, int64_t* bytes,
+nvd_status solve_column_batch(ColBatch* c, const ColBatchArrays& arrays, const std::vector<int>& ks,
+                              const nvd_opts& o, const double* P, const double* Q, double* d_out, double* X, nvd_pair_info* info, int64_t* bytes,
                               hipStream_t s);
 void free_column_batch(ColBatch* c, int64_t* bytes);
 // By CSR entry (entries.hip): weighted degrees, the check of new weights (bit 1:

@@ -250,11 +250,15 @@ nvd_status nvd_project(nvd_graph* g, int32_t k, const double* P,
  *   delta_j (mean zero on every component).  With NVD_WARM_START it also
  *   supplies the starting guess.
  * info: host array of k nvd_pair_info or NULL.
- * Synchronous with respect to `stream` (see Streams).  With the Jacobi
- * preconditioner, no warm start and tile_k = 0, graphs whose vector fits one
- * CU's LDS (up to 32,768 nodes in mixed precision, 17,408 in FP64) are solved
- * by one block per pair where that is estimated faster (environment:
- * NVD_COLUMN=0 never, NVD_COLUMN=1 wherever it fits).  Else on a connected graph
+ * Synchronous with respect to `stream` (see Streams).  Without a warm start
+ * and with tile_k = 0, graphs whose vector fits one CU's LDS are solved by one
+ * block per pair where that is estimated faster (environment: NVD_COLUMN=0
+ * never, NVD_COLUMN=1 wherever it fits): with the Jacobi preconditioner up to
+ * 32,768 nodes in mixed precision and 17,408 in FP64, with
+ * NVD_PRECOND_TREE up to 17,408 in either, with NVD_PRECOND_ACHOL up to 24,576
+ * and 17,408.  A graph for which the device has no room for that form (its
+ * layout is kept with the handle) is solved by tiles from then on.  Else on a
+ * connected graph
  * with the Jacobi preconditioner and no warm start, a tile of up to about
  * 1e6 vector elements (n times the tile) is solved by one kernel launch
  * (one block, or a cooperative launch of up to 256 blocks); NVD_E_DEVICE if
@@ -289,7 +293,7 @@ nvd_status nvd_distances_noalloc(nvd_graph* g, int32_t k, const double* P,
 /* ---- all pairwise distances among m node vectors --------------------------
  * D[i][j] = d(v_i, v_j) (section 3.1 distance) for the m columns of V, from
  * ONE solve with m right-hand sides: X = L^+ V_bar (section 3.2 solve, the
- * tiles and precision of nvd_distances), R = V_bar - L X its final FP64
+ * blocks or tiles and the precision of nvd_distances), R = V_bar - L X its final FP64
  * residuals, and
  *     Gt = V_bar^T X + X^T R,   D_ij^2 = Gt_ii + Gt_jj - Gt_ij - Gt_ji,
  * which equals, by linearity, the quadratic form delta^T x + x^T r of the
@@ -327,8 +331,10 @@ nvd_status nvd_tune_query(nvd_graph* g, int32_t k, int32_t precision,
  * finite and positive and equal to its mirror entry's (NVD_E_GRAPH
  * otherwise; the graph then keeps its previous weights).
  * Synchronous with respect to `stream`.  Batches made earlier keep their
- * own copy; a spanning forest built for the tree preconditioner is dropped
- * and rebuilt from the new weights when next needed. */
+ * own copy; a spanning forest or factor built for a preconditioner is dropped
+ * and rebuilt from the new weights when next needed.  The first call builds a
+ * map of the entries (8 bytes each, kept with the handle; without room for it
+ * every call finds what it needs by bisection). */
 nvd_status nvd_graph_set_weights(nvd_graph* g, const double* w, void* stream);
 
 /* ---- adjoint of d^2 with respect to the edge weights ---------------------
@@ -368,10 +374,15 @@ nvd_status nvd_grad_scale_from_d(int32_t k, const double* g_d, const double* d,
  * nvd_batch_create packs G graphs into one device structure (the graphs may
  * be destroyed afterwards).  nvd_batch_distances solves k_g pairs on every
  * graph g: FP32 CG with FP64 iterative refinement (opts->precision
- * NVD_MIXED, the default for batches) or FP64 CG.  Two solvers:
+ * NVD_MIXED, the default for batches) or FP64 CG.  Three solvers:
  *  - sweep (default): the graphs form one block-diagonal operator; every
  *    phase is one kernel over the rows of all graphs still open, each graph
  *    and pair keeping its own CG scalars (a few launches per iteration).
+ *  - one block per (graph, pair), in place of the sweep where no graph has
+ *    more than 24,576 nodes (17,408 with FP64) and it is estimated faster
+ *    (NVD_COLUMN as for nvd_distances).  Its layouts go to the device with the
+ *    first such call, its vectors take up to 1 GiB; without room for them the
+ *    batch is swept.
  *  - persistent (opts->flags & NVD_BATCH_PERSISTENT): one cooperative
  *    launch in which blocks or teams of blocks take graphs from a work plan.
  * k_per_graph: host int32 [G] (each 1..64).

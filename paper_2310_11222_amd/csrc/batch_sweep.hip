@@ -34,7 +34,7 @@ constexpr int SBS = 256;          // threads per block of the sweep kernels
 #endif
 constexpr int kChunkRows = NVD_CHUNK_ROWS;   // rows per short chunk
 // Below this many rows in all, chunks of half the size: 64 graphs of 3,300 to
-// 10^5 nodes (2.1M rows) have some 260 full chunks to an XCD's 32 CUs, and the
+// 10^5 nodes (1.84M rows) have some 260 full chunks to an XCD's 32 CUs, and the
 // apply, whose gathers want more waves in flight than that, took 21.4 ms a
 // call, 19.5 with half chunks (62 graphs up to 37,000 nodes, 14 pairs: 18.0 and
 // 13.8).  Quarter chunks gave 20.2 and 13.3; the 10^7 rows of 512 graphs are

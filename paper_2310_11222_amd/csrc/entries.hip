@@ -1,8 +1,8 @@
-// Work by CSR entry: checking and taking new edge weights, weighted degrees,
-// and the adjoint for the weights.
+// Work by CSR entry: checking new edge weights and the adjoint for the weights;
+// and weighted degrees, sixteen lanes a row.
 //
-// A thread (or lane group) per row left each of these as long as its longest
-// row: on a BA graph of 2 10^5 nodes (m = 5, hubs of thousands) the check took
+// A thread (or lane group) per row left the first two as long as their longest
+// row, and the degrees sixteen times as long as they are now: on a BA graph of 2 10^5 nodes (m = 5, hubs of thousands) the check took
 // 5.5 ms, the degrees 0.42 and the adjoint over 32 columns 1.9, of a training
 // step of 20.  By entry they need an entry's row and the place of its mirror
 // entry; both are found when weights are first replaced, by bisection, and kept

@@ -83,7 +83,7 @@ struct ColPlan;      // the graph as the one-block-per-column solver walks it (c
 
 // Scratch vectors and host result words of the one-block-per-column solver.
 struct ColWs {
-  double* vec = nullptr;           // [columns][5][n], then the component means
+  double* vec = nullptr;           // [columns][4, with a preconditioner 8][n], then the component means
   size_t cap_vec = 0, cap_cm = 0;  // doubles
   nvd_pair_info* info = nullptr;   // pinned
   int cap_info = 0;

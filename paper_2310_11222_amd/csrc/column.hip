@@ -586,6 +586,7 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
   a.max_iter = sp.max_iter;
   a.max_refine = sp.max_refine;
   a.out_dsq = sp.out_dsq ? 1 : 0;
+  a.runs = 3;
   const size_t hb = parts_bytes(cp->d.nv);
   const size_t most = ((size_t)kColLds - hb) / (sizeof(double) * kColBS) * kColBS;
   a.lds_n = (int)std::min<size_t>(stride, most);
@@ -902,6 +903,8 @@ nvd_status solve_column_batch(ColBatch* c, const ColBatchArrays& arrays, const s
   a.max_iter = o.max_iter;
   a.max_refine = o.max_refine;
   a.out_dsq = 0;
+  a.runs = std::max(2, std::min(o.max_refine, 3));
+  a.go_on = 1;
   a.handover = 0;                  // batches leave a pair that FP32 cannot finish as it is
   a.d_out = d_out;
   a.X = X;

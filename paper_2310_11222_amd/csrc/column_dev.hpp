@@ -125,6 +125,8 @@ struct ColArgs {
   double rtol2, irtol2, stall_ratio2;
   int max_iter, max_refine, out_dsq;
   int lds_n;                 // FP64 values that fit the gathered vector's LDS
+  int runs;                  // FP64: CG runs at most, the first and its restarts
+  int go_on;                 // a run that ends at max_iter counts, and the next goes on from its x (batches)
   int handover;              // mixed: pairs that FP32 cannot finish are left to an FP64 launch
   int resume;                // FP64: only those pairs, from their x in vec
   double* d_out;

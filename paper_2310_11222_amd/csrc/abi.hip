@@ -255,6 +255,7 @@ nvd_status nvd_laplacian_apply(nvd_graph* h, int32_t dtype, int32_t k, const voi
     const int left = k - c0;
     if (left > T && left < 64 && one_ragged_pass(g, left, 2 * T, dtype == NVD_DT_F64)) {
       sc.T = 2 * T;
+      sc.wide = dtype == NVD_DT_F32 && (left & 1) != 0 && slices_serve(g);
       NVD_TRY(launch_ragged(sc, left, as_stream(stream)));
       return NVD_OK;
     }

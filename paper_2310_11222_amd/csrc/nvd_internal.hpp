@@ -208,7 +208,7 @@ struct SpmmCall {
   ColState* cs;
   int epi;
   int grid;                 // short-row blocks (0 = auto)
-  bool wide;                // FP32, EPI_CG: row sums in FP64, rounded once
+  bool wide;                // FP32 (EPI_CG, or ragged): row sums in FP64, rounded once
 };
 nvd_status launch_spmm(const SpmmCall& c, const GridRed& red, hipStream_t s);
 // The apply the solvers and nvd_laplacian_apply use: one column (T = 1) on a
@@ -218,7 +218,7 @@ nvd_status launch_apply(const SpmmCall& c, const GridRed& red, hipStream_t s);
 nvd_status launch_ragged(const SpmmCall& c, int cols, hipStream_t s);
 void free_slices(DevGraph* g);
 // Whether one column of the graph may be applied by slices, whose FP32 row
-// sums are FP64 ones rounded once.  A wider tile that takes such a column with
+// sums are FP64 ones rounded once.  A wider pass that takes such a column with
 // others sums as they do (SpmmCall::wide).
 bool slices_serve(const DevGraph* g);
 

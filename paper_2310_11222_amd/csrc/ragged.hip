@@ -8,15 +8,16 @@
 // the last column repeat it, so that they ask for no further line, and store
 // nothing.  Rows and the split of long rows are those of k_spmm.
 //
-// The sums are FP64 ones in either precision, rounded once: a lane per element
-// takes four times as many terms of a long row as k_spmm's lanes of four, which
-// in FP32 left the values up to 2.4 times as far from the exact ones, and the
-// odd column of a large graph had the FP64 sums of the sliced apply before it
-// came into this pass.
+// FP32 sums are those of k_spmm, in its order, but for two kinds that are FP64
+// sums rounded once: of long rows, of which a lane per element takes up to four
+// times as many terms as k_spmm's lanes (in FP32 hubs were 2.4 times as far from
+// the exact values), and (SpmmCall::wide) of every row where the odd column had the
+// sums of the sliced apply before it came into this pass.
 //
 // Measured (us, a pass for every power of two -> one pass): power law n = 10^6
-// weighted, 3 columns FP32 228 -> 151, 7 columns 417 -> 208 (with FP32 sums 148
-// and 200), 13 columns FP64 611 -> 327; BA n = 3,000, 13 columns 37 -> 16.
+// weighted, FP32 3 columns 230 -> 155, 7 columns 419 -> 203, 15 columns 667 -> 278
+// (all sums in FP64 159, 209 and 291), FP64 13 columns 609 -> 333; BA n = 3,000,
+// 13 columns 37 -> 16.
 #include <algorithm>
 
 #include "device_common.hpp"
@@ -37,7 +38,8 @@ struct RaggedK {
   int nlong_blocks;
 };
 
-template <typename V, int L, bool UNIT>
+// A: the type of the short rows' sums.
+template <typename V, typename A, int L, bool UNIT>
 __global__ __launch_bounds__(kBS) void k_apply_ragged(RaggedK<V> a, LongRows lr) {
   __shared__ double sh[kBS];
   __shared__ int s_last;
@@ -86,8 +88,8 @@ __global__ __launch_bounds__(kBS) void k_apply_ragged(RaggedK<V> a, LongRows lr)
     const int lo = a.rp[row];
     const int deg = a.rp[row + 1] - lo;
     if (deg > kLongRow) continue;
-    const double own = (double)a.x[row * a.ldx + cc];
-    double sum = 0.0;
+    const A own = (A)a.x[row * a.ldx + cc];
+    A sum = (A)0;
     for (int e0 = 0; e0 < deg; e0 += U) {
       int col[U];
       V wt[U], xv[U];
@@ -99,18 +101,20 @@ __global__ __launch_bounds__(kBS) void k_apply_ragged(RaggedK<V> a, LongRows lr)
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) xv[u] = e0 + u < deg ? a.x[(long)col[u] * a.ldx + cc] : (V)0;
-      // (all loads are out before the first conversion: it would otherwise move
-      // up behind each load's own test and wait for it there)
+      if constexpr (sizeof(A) != sizeof(V)) {
+        // all loads are out before the first conversion: it would otherwise move
+        // up behind each load's own test and wait for it there
 #pragma unroll
-      for (int u = 0; u < U; ++u) asm volatile("" : "+v"(wt[u]), "+v"(xv[u]));
+        for (int u = 0; u < U; ++u) asm volatile("" : "+v"(wt[u]), "+v"(xv[u]));
+      }
 #pragma unroll
-      for (int u = 0; u < U; ++u) sum += (double)wt[u] * (own - (double)xv[u]);
+      for (int u = 0; u < U; ++u) sum += (A)wt[u] * (own - (A)xv[u]);
     }
     if (c < a.cols) __builtin_nontemporal_store((V)sum, &a.y[row * a.ldy + c]);
   }
 }
 
-template <typename V>
+template <typename V, typename A>
 static nvd_status launch_ragged_t(const SpmmCall& c, int cols, hipStream_t s) {
   const DevGraph* g = c.g;
   RaggedK<V> k{};
@@ -138,9 +142,9 @@ static nvd_status launch_ragged_t(const SpmmCall& c, int cols, hipStream_t s) {
 #define NVD_R(LL)                                                        \
   case LL:                                                               \
     if (unit)                                                            \
-      k_apply_ragged<V, LL, true><<<grid, kBS, 0, s>>>(k, g->lr);        \
+      k_apply_ragged<V, A, LL, true><<<grid, kBS, 0, s>>>(k, g->lr);        \
     else                                                                 \
-      k_apply_ragged<V, LL, false><<<grid, kBS, 0, s>>>(k, g->lr);       \
+      k_apply_ragged<V, A, LL, false><<<grid, kBS, 0, s>>>(k, g->lr);       \
     break;
     NVD_R(4) NVD_R(8) NVD_R(16) NVD_R(32) NVD_R(64)
 #undef NVD_R
@@ -152,7 +156,8 @@ static nvd_status launch_ragged_t(const SpmmCall& c, int cols, hipStream_t s) {
 }
 
 nvd_status launch_ragged(const SpmmCall& c, int cols, hipStream_t s) {
-  return c.prec == 0 ? launch_ragged_t<double>(c, cols, s) : launch_ragged_t<float>(c, cols, s);
+  if (c.prec == 0) return launch_ragged_t<double, double>(c, cols, s);
+  return c.wide ? launch_ragged_t<float, double>(c, cols, s) : launch_ragged_t<float, float>(c, cols, s);
 }
 
 }  // namespace nvd

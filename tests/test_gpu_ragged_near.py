@@ -1,6 +1,5 @@
-"""The rule of the ragged apply on graphs whose neighbours lie near their rows:
-where one pass does not pay there, a call is bit for bit its passes over the
-powers of two in its columns (FP32: one pass sums in FP64, theirs in FP32)."""
+"""The rule of the ragged apply on graphs whose neighbours lie near their rows,
+and on others: how many launches a call makes."""
 import numpy as np
 import pytest
 
@@ -17,6 +16,7 @@ pytestmark = pytest.mark.gpu
                                          ("shuffled", 5, True)])
 def test_one_pass_or_several(model, k, one):
     import torch
+    import paper_2310_11222_amd as nvd
     n = 120000
     rng = np.random.default_rng(k)
     g = erdos_renyi(n, 4 * n, rng) if model == "er" else watts_strogatz(n, 8, 0.1, rng)
@@ -27,12 +27,13 @@ def test_one_pass_or_several(model, k, one):
     dg = dev_graph(g)
     X = torch.from_numpy(rng.standard_normal((n, k)).astype(np.float32)).cuda()
     Y = dg.laplacian_apply(X)
-    parts, c = [], 0
-    while c < k:
-        T = 1 << ((k - c).bit_length() - 1)
-        parts.append(dg.laplacian_apply(X[:, c:c + T]))
-        c += T
-    assert torch.equal(Y, torch.cat(parts, 1)) == (not one)
+    nvd.prof_enable(True)
+    dg.laplacian_apply(X, out=Y)
+    torch.cuda.synchronize()
+    launches = nvd.prof_read()["spmm_f32"]["launches"]
+    nvd.prof_enable(False)
+    # a pass for every power of two in k, the last ones perhaps as one
+    assert (launches == 1) == one and launches <= bin(k).count("1")
     L = oracle.laplacian_sparse(n, g.row_ptr, g.col_idx, None)
     Xh = X.cpu().numpy().astype(np.float64)
     assert not (np.abs(Y.cpu().numpy() - L @ Xh) > 2e-6 * (abs(L) @ np.abs(Xh))).any()

@@ -46,6 +46,26 @@ def test_odd_column_of_an_fp32_apply(monkeypatch, k, weighted):
 
 
 @pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("k", [3, 7, 12, 15, 28])
+def test_long_rows_of_a_ragged_fp32_apply(k, weighted):
+    """Rows of more than 128 neighbours in one pass over a ragged number of
+    columns, by default: FP64 sums rounded once, a segment of the row to FP64."""
+    import torch
+    rng = np.random.default_rng(70 + k + weighted)
+    g = _graph(rng, 3000, weighted)
+    deg = np.diff(g.row_ptr)
+    say("long row sums", k, weighted)
+    x = rng.standard_normal((g.n, k)).astype(np.float32)
+    y = dev_graph(g).laplacian_apply(torch.from_numpy(x).cuda()).cpu().numpy().astype(np.float64)
+    w = None if g.w is None else g.w.astype(np.float32).astype(np.float64)
+    L = oracle.laplacian_sparse(g.n, g.row_ptr, g.col_idx, w)
+    want = L @ x.astype(np.float64)
+    bound = 2.0 ** -24 * np.abs(want) + 1500 * 2.0 ** -53 * (abs(L) @ np.abs(x.astype(np.float64))) + 1e-37
+    assert (deg > 128).any()
+    assert (np.abs(y - want) <= 1.01 * bound)[deg > 128].all()
+
+
+@pytest.mark.parametrize("weighted", [False, True])
 @pytest.mark.parametrize("k", [3, 5, 7, 11])
 def test_odd_pair_of_a_mixed_tile(monkeypatch, k, weighted):
     """The residual that one FP32 solve reaches, of the last pair among k and

@@ -586,7 +586,7 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
   a.max_iter = sp.max_iter;
   a.max_refine = sp.max_refine;
   a.out_dsq = sp.out_dsq ? 1 : 0;
-  a.runs = 3;
+  a.call = kColOwn;
   const size_t hb = parts_bytes(cp->d.nv);
   const size_t most = ((size_t)kColLds - hb) / (sizeof(double) * kColBS) * kColBS;
   a.lds_n = (int)std::min<size_t>(stride, most);
@@ -603,7 +603,6 @@ nvd_status solve_column(DevGraph* g, int k, const double* P, const double* Q, in
   a.stride = stride;
   a.cmean = g->col_ws.vec + g->col_ws.cap_vec;
   a.cstride = cstride;
-  a.handover = mixed ? 1 : 0;
   auto launch = [&](bool in_fp64, size_t lds, int cols) -> nvd_status {
     return (sp.tree ? launch_column_pre : launch_column_jacobi)(a, !in_fp64, !g->weighted, g->n, cols, lds, s);
   };
@@ -903,9 +902,7 @@ nvd_status solve_column_batch(ColBatch* c, const ColBatchArrays& arrays, const s
   a.max_iter = o.max_iter;
   a.max_refine = o.max_refine;
   a.out_dsq = 0;
-  a.runs = std::max(2, std::min(o.max_refine, 3));
-  a.go_on = 1;
-  a.handover = 0;                  // batches leave a pair that FP32 cannot finish as it is
+  a.call = o.precision != NVD_MIXED && o.max_refine < 3 ? kColBatchTwo : kColBatch;
   a.d_out = d_out;
   a.X = X;
   a.info = c->ws.info;

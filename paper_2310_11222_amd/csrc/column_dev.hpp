@@ -112,6 +112,15 @@ struct ColJob {
   long work;     // its vectors in vec
 };
 
+// Whose pairs a launch solves.  A graph's own call: a pair whose CG run ends at
+// max_iter has not converged, one that FP32 cannot finish is left to an FP64
+// launch, and FP64 takes up to three runs.  A batch's: a run that ends at max_iter
+// counts, and the next goes on from its x; FP64 takes up to three, or two (mixed
+// precision: kColBatch).  One value, and a constant bound on the runs, as every
+// scalar more that the kernel holds costs its FP64 form registers (n = 10^4 of
+// degree 16, weighted, 5 pairs: 1122 us with the runs and the rest apart, 1106).
+enum ColCall : int { kColBatch = 0, kColOwn, kColBatchTwo };
+
 struct ColArgs {
   ColGraph g;                // the graph, unless `graphs` is set
   ColPre pre;                // its preconditioner (one graph only)
@@ -123,11 +132,9 @@ struct ColArgs {
   long ld;
   int col0;
   double rtol2, irtol2, stall_ratio2;
-  int max_iter, max_refine, out_dsq;
+  int max_iter, out_dsq, max_refine;
   int lds_n;                 // FP64 values that fit the gathered vector's LDS
-  int runs;                  // FP64: CG runs at most, the first and its restarts
-  int go_on;                 // a run that ends at max_iter counts, and the next goes on from its x (batches)
-  int handover;              // mixed: pairs that FP32 cannot finish are left to an FP64 launch
+  int call;                  // ColCall
   int resume;                // FP64: only those pairs, from their x in vec
   double* d_out;
   double* X;                 // null, or n x k (ldx) for the solutions; the same

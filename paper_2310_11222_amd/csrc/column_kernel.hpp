@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kColBS) void k_column(ColArgs a) {
       }
       col_sum<3>(s3, S, turn);
       const double rr = s3[0];
-      if (step > 0 && a.handover) stall = refine_stall_count(orr, rr, stall, a.stall_ratio2);
+      if (step > 0 && a.call) stall = refine_stall_count(orr, rr, stall, a.stall_ratio2);
       orr = rr;
       if (uniform(step > 0 && rr <= a.rtol2 * bb)) {
         open = 0;
@@ -171,11 +171,11 @@ __global__ __launch_bounds__(kColBS) void k_column(ColArgs a) {
       else
         run = col_cg<float, UNIT, EPT>(g, p32, hq, f, x32, s3[1], s3[2], it2, a.max_iter, S, turn);
       iters += run.iters;
-      if (run.status == kStOk || (run.status == kStNoconv && a.go_on)) {
+      if (run.status == kStOk || (run.status == kStNoconv && !a.call)) {
         for (int e = t; e < n; e += kColBS) x[e] += (double)x32[e];
       } else {
         open = 0;
-        if (run.status == kStNoconv && a.handover)
+        if (run.status == kStNoconv)
           fb = 1;               // FP64 finishes from the last good x
         else
           status = run.status;
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kColBS) void k_column(ColArgs a) {
         else
           run = col_cg<double, UNIT, EPT>(g, buf, hq, rv, x, rho, bb, a.rtol2, a.max_iter, S, turn);
         iters += run.iters;
-        status = run.status == kStNoconv && a.go_on ? kStOk : run.status;
+        status = run.status == kStNoconv && a.call != kColOwn ? kStOk : run.status;
       }
       const double mx = col_means(g, x, cm, S, turn);
       for (int e = t; e < n; e += kColBS) x[e] -= col_mean(g, cm, mx, e);
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kColBS) void k_column(ColArgs a) {
       col_sum<2>(s2, S, turn);
       rho = s2[1];
       open = status == kStOk && uniform(s2[0] > a.rtol2 * bb);
-      if (restarts + 1 >= a.runs) break;
+      if (restarts >= 2 || (restarts == 1 && a.call == kColBatchTwo)) break;
     }
   }
 

@@ -223,13 +223,13 @@ nvd_status nvd_graph_query(const nvd_graph* g, int32_t* labels_host,
  * gathered there and written in slice order, and the rows are then summed
  * from them in CSR order.  The first such call of each precision builds the
  * slice structure on the host, times both forms of the apply on its X and
- * takes the slices for the graph where they are a tenth faster (that call
- * waits for the device and then enqueues).  The
- * structure is kept with the graph while one precision uses it (device
- * memory: about 12 bytes per CSR entry), across nvd_graph_set_weights, and
- * dropped by nvd_graph_destroy.  nvd_distances_noalloc never
- * uses it.  Environment: NVD_SLICE=0 never uses it, NVD_SLICE=1 uses it at
- * any size without timing. */
+ * takes the slices for the graph's solves where they are faster, for
+ * nvd_laplacian_apply where they are faster by a tenth (that call waits for
+ * the device and then enqueues).  The structure is kept with the graph while
+ * one precision uses it (device memory: about 12 bytes per CSR entry), across
+ * nvd_graph_set_weights, and dropped by nvd_graph_destroy.
+ * nvd_distances_noalloc never uses it.  Environment: NVD_SLICE=0 never uses
+ * it, NVD_SLICE=1 uses it at any size without timing. */
 nvd_status nvd_laplacian_apply(nvd_graph* g, int32_t dtype, int32_t k,
                                const void* X, int64_t ldx, void* Y,
                                int64_t ldy, void* stream);

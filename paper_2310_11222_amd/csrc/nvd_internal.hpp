@@ -135,7 +135,7 @@ struct DevGraph {
   SliceGraph* slices = nullptr; // built when the sliced apply is first needed
   int slice_state = 0;          // -1: build failed, use the row-wise apply
   int tile_most = kMaxTile;     // widest tile to try: what a call ran out of memory with, less
-  int slice_pick[2] = {0, 0};   // [FP64, FP32]: 1 sliced, -1 row-wise (timed), 0 not yet
+  int slice_pick[2] = {0, 0};   // [FP64, FP32]: 0 not timed yet, -1 row-wise, 1 sliced in solves, 2 everywhere
   ColPlan* col = nullptr;       // built when the one-block-per-column solver is first used
   ColWs col_ws;
   bool col_failed = false;      // there was no memory for it: tiles from then on

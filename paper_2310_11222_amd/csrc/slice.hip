@@ -634,10 +634,13 @@ static nvd_status launch_sliced(const SpmmCall& c, const GridRed& red, hipStream
   return st;
 }
 
-// The sliced form has to be faster by a tenth: on one x again and again, both run
-// from warm caches, which the row-wise one is the less dependent on (ER n = 1.065
-// 10^6 of degree 3, weighted, FP64: timed so 42.7 against 41.0 us, 43.0 against
-// 45.7 with a new x each time).
+// For nvd_laplacian_apply the sliced form has to be faster by a tenth: on one x
+// again and again, both run from warm caches, which the row-wise one is the less
+// dependent on (ER n = 1.065 10^6 of degree 3, weighted, FP64, us row by row /
+// sliced: timed so 42.7 / 41.0, with a new x each time 43.0 / 45.7).  A solve's x
+// was written by the kernel before, and there the faster one is taken (whole calls
+// on that graph 16.1 / 14.9 ms; power law n = 1.16 10^6, weighted, FP64, timed 138 /
+// 137 us, in its solve 138 / 131 and the call 6.53 / 6.28 ms).
 constexpr float kSlGain = 0.9f;
 
 // Time the row-wise and the sliced apply of this call's x (EPI_PLAIN into a
@@ -697,13 +700,13 @@ static bool use_slices(DevGraph* g, const SpmmCall& c, const GridRed& red, hipSt
     float tr = 0.0f, ts = 0.0f;
     const nvd_status st = c.prec == 0 ? time_forms<double>(g, c, red, s, &tr, &ts)
                                       : time_forms<float>(g, c, red, s, &tr, &ts);
-    g->slice_pick[p] = (st == NVD_OK && ts < kSlGain * tr) ? 1 : -1;
+    g->slice_pick[p] = st != NVD_OK || ts >= tr ? -1 : (ts < kSlGain * tr ? 2 : 1);
     if (g->slice_pick[0] < 0 && g->slice_pick[1] < 0) {
       free_slices(g);
       return false;
     }
   }
-  return mode == 1 || g->slice_pick[p] > 0;
+  return mode == 1 || g->slice_pick[p] > (c.epi == EPI_PLAIN ? 1 : 0);
 }
 
 nvd_status launch_apply(const SpmmCall& c, const GridRed& red, hipStream_t s) {
